@@ -8,6 +8,8 @@
 //   k_finish   stress and counters from the partials, stress sample (only on steps that take
 //              a stress sample and on the last step of a dss_step call)
 // The history rows written by k_pairs become the committed history of the step.
+// Runs of five and more steps go as windows on pair lists (dss_lists.hpp): k_list_begin, one
+// k_list per step, and a step as above at the end.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -23,6 +25,7 @@
 #include "dss_kernels.hpp"
 #include "dss_adjoint.hpp"
 #include "dss_sized.hpp"
+#include "dss_lists.hpp"
 #include "dss_observe.hpp"
 
 using namespace dss;
@@ -99,6 +102,20 @@ struct DevList {
 };
 
 struct AdjointScratch;
+
+// Steps of a window on pair lists.  A window of n steps costs a search, n - 1 list steps and a full
+// step (N = 100k, FP64: 53 + 24 (n - 1) + 65 us against 64 n): longer is better until the margin is
+// used up (a sheared box of N = 100k uses a third of it in 64 steps), and below five steps full
+// ones are as fast.
+constexpr int kListWindow = 64;
+constexpr int kListWindowMin = 5;
+// Margin of the lists of a box beyond its cutoff, in smallest radii: what particles moving at a
+// few shear rates use up over a window of kListWindow steps, with a floor.
+inline double list_skin(double shear_rate, double dt)
+{
+    return std::min(0.1 + 10.0 * std::fabs(shear_rate) * dt * kListWindow, 0.6);
+}
+constexpr size_t kMaxOpenRuns = 4096;  // runs enqueued without a read of the clock
 }  // namespace
 
 struct dss_handle {
@@ -124,11 +141,15 @@ struct dss_handle {
     double max_mean_row = 0.0;        // mean particles per cell row of the densest box
     dss_tuning tune{1.0, 1.0, 1, 1, 0, 0, 0, 0};
     bool tune_pending = false;        // lattice to rebuild before the next time step
+    // a window on pair lists may begin at the current state: cell_start is that of the particles'
+    // order (not of a lattice that no counting sort has used yet), and the history rows are those
+    // of its contacts (not of another Lees-Edwards offset)
+    bool listable = false;
     // HIP graphs of one time step, keyed by (current buffers, committed history buffers,
     // half-step velocities, stress summation), and of runs of steps (the same key for the
     // first step, the run length and which of its steps sum the stress)
     hipGraphExec_t graph[16] = {};
-    std::vector<std::pair<uint64_t, hipGraphExec_t>> run_graphs;
+    std::vector<std::pair<std::pair<uint64_t, uint64_t>, hipGraphExec_t>> run_graphs;
     bool graph_broken = false;
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -179,7 +200,7 @@ struct dss_handle {
     DevRun run_host{};
 
     // kernel timing with events on the stream
-    static constexpr int kKernels = 8;
+    static constexpr int kKernels = 9;
     unsigned timing = 0;       // bit k: time kernel k
     std::vector<hipEvent_t> ev_pool;
     std::vector<std::pair<int, std::pair<int, int>>> ev_marks;  // (kernel, (start event, stop event))
@@ -194,6 +215,25 @@ struct dss_handle {
     double *tape_x = nullptr, *tape_u = nullptr, *tape_w = nullptr;
     int *tape_zero = nullptr;  // while set, k_predict also clears these N counts
     DevList obs_ws;  // work buffers of the observables, kept between calls
+
+    // windows on pair lists: the blocks, the lists and the particle records of a window
+    ListBlock *lblocks = nullptr;
+    int2 *lent = nullptr;
+    double *lxi = nullptr, *lxr = nullptr, *ldsum = nullptr, *lpartials = nullptr;
+    int *ln = nullptr, *lcross = nullptr;
+    ListRec *lrec[2] = {nullptr, nullptr};
+    int list_blocks = 0, list_own_cap = 0;
+    int list_window = kListWindow;   // longest window (0: off); halved when one stopped early
+    int list_good = 0;               // calls since then without a stop
+    // the runs of steps enqueued since the host last read the clock: the state each began from,
+    // where the host resumes when a window stopped; and the end and sampling of the last call
+    struct Run {
+        int64_t step;
+        int cur, hh;
+        bool vel_is_half;
+    };
+    std::vector<Run> runs;
+    int64_t call_every = 0;
 };
 
 namespace {
@@ -239,6 +279,13 @@ void free_lattice(dss_handle *h)
         if (p) (void)hipFree(p);
     };
     destroy_graphs(h);
+    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross);
+    F(h->lrec[0]); F(h->lrec[1]);
+    h->lblocks = nullptr;
+    h->lent = nullptr;
+    h->lxi = h->lxr = h->ldsum = h->lpartials = nullptr;
+    h->ln = h->lcross = nullptr;
+    h->lrec[0] = h->lrec[1] = nullptr;
     F(h->count); F(h->cell_start); F(h->tile_sum); F(h->cs_local); F(h->partials); F(h->d_boxes); F(h->d_row_box);
     h->cs_local = nullptr;
     h->count = h->cell_start = h->tile_sum = h->d_row_box = nullptr;
@@ -278,6 +325,9 @@ void free_all(dss_handle *h)
     h->run = nullptr;
     h->sigma_last = h->samples = nullptr;
     h->sample_cap_alloc = 0;
+    h->runs.clear();
+    h->list_window = kListWindow;
+    h->list_good = 0;
     h->loaded = false;
 }
 
@@ -318,11 +368,13 @@ dss_status read_diag(dss_handle *h, std::vector<double> &d)
     return DSS_OK;
 }
 
+dss_status settle(dss_handle *h, DevClock *out = nullptr);
+
 dss_status check_flags(dss_handle *h)
 {
     DevClock c;
-    HIPTRY(hipMemcpyAsync(&c, h->clk, sizeof(c), hipMemcpyDeviceToHost, h->stream));
-    HIPTRY(hipStreamSynchronize(h->stream));
+    dss_status st = settle(h, &c);
+    if (st) return st;
     if (c.err & kErrNonFinite) return fail(h, DSS_ERR_UNSTABLE, "non-finite force or torque");
     if (c.err & kErrRowOverflow) {
         std::vector<double> d;
@@ -386,11 +438,12 @@ dss_status collect_timing(dss_handle *h)
     return DSS_OK;
 }
 
-dss_status require_loaded(dss_handle *h)
+dss_status require_loaded(dss_handle *h, bool settled = true)
 {
     if (!h) return DSS_ERR_ARG;
     if (!h->loaded) return fail(h, DSS_ERR_STATE, "no particles loaded (call dss_set_particles first)");
-    return DSS_OK;
+    // time steps still under way may have to be resumed before anything looks at the state
+    return settled && !h->runs.empty() ? settle(h) : DSS_OK;
 }
 
 // Size classes of the stencil path: class of radius a = floor(a cls_mul + cls_add), ncls
@@ -530,6 +583,7 @@ dss_status setup_lattice(dss_handle *h)
                     h->tune.cell_scale, sized, h->tune.tiled ? 4 * h->n_cu : 0, sc, why))
         return fail(h, DSS_ERR_BOX, why);
     free_lattice(h);
+    h->listable = false;
     const int B = h->nbox;
     int64_t ncell = 0;
     int nrow = 0, max_rows_box = 0;
@@ -771,7 +825,7 @@ dss_status launch_pairs(dss_handle *h, int buf, const int *prev, int sample, boo
     if (!finish) return DSS_OK;
     TimedLaunch t(h, 4);
     hipExtLaunchKernelGGL(k_finish, dim3(12 * h->nbox), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->d_boxes,
-                          h->partials, h->P.pstride, h->clk, h->run, sample);
+                          h->partials, h->P.pstride, h->clk, h->run, sample, 0);
     return DSS_OK;
 }
 
@@ -787,12 +841,16 @@ void commit_eval(dss_handle *h, bool advance)
     }
 }
 
-dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
+// steps: time steps the clock advances by (EVAL_STEP; more than one when the steps before were
+// taken on pair lists, which leave the whole force in the own records).
+dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true, int steps = 1)
 {
     const int N = (int)h->N;
     const int grid = (N + kBlock - 1) / kBlock;
     const int c = h->cur, o = 1 - h->cur;
-    const int advance = mode == EVAL_STEP ? 1 : 0;
+    const int advance = mode == EVAL_STEP ? steps : 0;
+    ForceBufs B = h->fb();
+    if (advance > 1) B.nnb = 0;
     if (mode == EVAL_INPLACE) {
         if (h->vel_is_half) {
             TimedLaunch t(h, 0);
@@ -810,8 +868,7 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
     {
         TimedLaunch t(h, 0);
         hipExtLaunchKernelGGL(k_predict, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->P, h->d_boxes,
-                              h->pa[c], h->vel[c], h->omg[c], h->fb(), h->vel_is_half ? 1 : 0, advance, h->clk,
-                              h->cell, h->rank, h->count, h->img, h->boxes[0],
+                              h->pa[c], h->vel[c], h->omg[c], B, h->vel_is_half ? 1 : 0, advance, h->clk, h->cell, h->rank, h->count, h->img, h->boxes[0],
                               h->P.record_pairs ? h->pair_count : (unsigned long long *)nullptr, h->tape_x,
                               h->tape_u, h->tape_w, h->tape_zero);
     }
@@ -835,6 +892,7 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
                               tiles ? h->cs_local : h->cell_start, h->tile_sum, tiles ? h->scan_c4 : 0,
                               h->ncell_total + 1, h->cell_start, h->clk, advance, h->pa[c], h->vel[c], h->omg[c],
                               h->pa[o], h->vel[o], h->omg[o], h->prev);
+        if (mode != EVAL_RESORT) h->listable = true;
     }
     if (mode == EVAL_RESORT) {
         // the committed rows follow their particles; the pair kernels then find them in place
@@ -849,6 +907,7 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
     if (s) return s;
     HIPTRY(hipGetLastError());
     commit_eval(h, advance != 0);
+    if (advance > 1) h->step += advance - 1;
     return DSS_OK;
 }
 
@@ -888,17 +947,141 @@ dss_status graph_step(dss_handle *h, bool finish)
     return DSS_OK;
 }
 
-// n consecutive time steps (n <= kRunSteps) through one HIP graph: bit k of `finish` sums the
-// stress at step k.  One launch for the run, so the steps follow each other without the gap
+// Whether the time steps of the handle can go as windows on pair lists: the plain row-tile search
+// (not the size-class stencils, whose pairs are few against their searches' kernels, nor the pass
+// of the electro-chemical far pairs), no recording of pairs, no wavy shear.
+bool lists_on(const dss_handle *h)
+{
+    return h->list_window >= kListWindowMin && h->tune.tiled && !h->P.sized && !h->P.ec && !h->P.record_pairs &&
+           h->P.wave_amp == 0.0;
+}
+
+// Blocks of the pair lists and the memory of a window, on the handle's first window.  A block
+// holds about as many particles as fill the workgroup slots once (1 / 64 of them kept free, as
+// for the cell rows), at least 16 and at most kListOwnMax; the blocks of a box are of one size.
+dss_status setup_lists(dss_handle *h)
+{
+    if (h->lrec[1]) return DSS_OK;  // allocated last
+    const int slots = 4 * h->n_cu - 4 * h->n_cu / 64;
+    const int64_t even = (h->N + slots - 1) / slots;
+    const int own = (int)std::min<int64_t>(std::max<int64_t>(even, 16), kListOwnMax);
+    std::vector<ListBlock> blocks;
+    int64_t ent = 0;
+    h->list_own_cap = 0;
+    for (int b = 0; b < h->nbox; ++b) {
+        BoxParams &G = h->boxes[b];
+        const int nb = (G.n_part + own - 1) / own;
+        G.skin = list_skin(G.gd, h->prm.dt) * h->a_min;
+        G.blk_off = (int)blocks.size();
+        G.blk_n = nb;
+        for (int k = 0; k < nb; ++k) {
+            const int lo = (int)((int64_t)G.n_part * k / nb), hi = (int)((int64_t)G.n_part * (k + 1) / nb);
+            blocks.push_back({G.part_off + lo, hi - lo, b, (int)ent});
+            ent += (int64_t)kListPerOwn * (hi - lo) + kListSpare;
+            h->list_own_cap = std::max(h->list_own_cap, hi - lo);
+        }
+    }
+    if (ent > (int64_t)0x7fffffff) {
+        h->list_window = 0;  // lists of this size are not indexed
+        return DSS_OK;
+    }
+    h->list_blocks = (int)blocks.size();
+    HIPTRY(dalloc(&h->lblocks, blocks.size()));
+    HIPTRY(dalloc(&h->lent, ent));
+    HIPTRY(dalloc(&h->lxi, 3 * ent));
+    if (h->P.kr > 0.0) HIPTRY(dalloc(&h->lxr, 3 * ent));
+    HIPTRY(dalloc(&h->ln, blocks.size()));
+    HIPTRY(dalloc(&h->ldsum, h->N));
+    HIPTRY(dalloc(&h->lcross, h->N));
+    HIPTRY(dalloc(&h->lpartials, 12 * blocks.size()));
+    HIPTRY(dalloc(&h->lrec[0], h->N));
+    HIPTRY(hipMemcpyAsync(h->lblocks, blocks.data(), blocks.size() * sizeof(ListBlock), hipMemcpyHostToDevice,
+                          h->stream));
+    HIPTRY(hipMemcpyAsync(h->d_boxes, h->boxes.data(), h->boxes.size() * sizeof(BoxParams), hipMemcpyHostToDevice,
+                          h->stream));
+    HIPTRY(hipStreamSynchronize(h->stream));  // `blocks` goes out of scope
+    HIPTRY(dalloc(&h->lrec[1], h->N));
+    return DSS_OK;
+}
+
+template <typename Real, bool Roll>
+void launch_list(dss_handle *h, bool sum, bool last, const ListView &L, int n, const CommittedView &C,
+                 const HistView &H)
+{
+    TimedLaunch t(h, 3);
+    auto k = sum ? (last ? k_list<Real, Roll, true, true> : k_list<Real, Roll, true, false>)
+                 : (last ? k_list<Real, Roll, false, true> : k_list<Real, Roll, false, false>);
+    const size_t lds = (size_t)h->list_own_cap * (sizeof(ListRec) + 6 * sizeof(double) + sizeof(int));
+    hipExtLaunchKernelGGL(k, dim3(h->list_blocks), dim3(kListBlock), lds, h->stream, t.e0, t.e1, 0, h->P, h->d_boxes,
+                          h->boxes[0], L, h->lrec[(n - 1) & 1], h->lrec[n & 1], n, C, H, h->clk, h->lpartials, h->list_blocks);
+}
+
+// A window of n >= 2 time steps; bit k of `finish` sums the stress at step k.
+dss_status list_window(dss_handle *h, int n, uint64_t finish)
+{
+    ListView L;
+    L.blocks = h->lblocks;
+    L.ent = h->lent;
+    L.xi = h->lxi;
+    L.xr = h->lxr;
+    L.n = h->ln;
+    L.dsum = h->ldsum;
+    L.cross = h->lcross;
+    L.own_cap = h->list_own_cap;
+    CommittedView C;
+    C.pa = h->pa[h->cur];
+    C.vel = h->vel[h->cur];
+    C.omg = h->omg[h->cur];
+    C.B = h->fb();
+    C.img = h->img;
+    HistView H{};
+    H.key_old = h->hkey[h->hh];
+    H.xi_old = h->hxi[h->hh];
+    H.cnt_old = h->hcnt[h->hh];
+    H.xr_old = h->hxr[h->hh];
+    H.key_new = h->hkey[1 - h->hh];
+    H.xi_new = h->hxi[1 - h->hh];
+    H.cnt_new = h->hcnt[1 - h->hh];
+    H.own_new = h->hown[1 - h->hh];
+    H.xr_new = h->hxr[1 - h->hh];
+    const bool roll = h->P.kr > 0.0, mixed = h->prm.precision == DSS_MIXED;
+    {
+        TimedLaunch t(h, 8);
+        hipExtLaunchKernelGGL(roll ? k_list_begin<true> : k_list_begin<false>, dim3(h->list_blocks), dim3(kBeginBlock),
+                              (size_t)(kListPerOwn * h->list_own_cap + kListSpare) * sizeof(int2), h->stream, t.e0, t.e1, 0, h->P, h->d_boxes, h->cell_start, C, H, L,
+                              h->lrec[0], h->vel_is_half ? 1 : 0, h->clk);
+    }
+    for (int k = 1; k < n; ++k) {
+        const bool sum = (finish >> (k - 1)) & 1u, last = k == n - 1;
+        if (mixed)
+            roll ? launch_list<float, true>(h, sum, last, L, k, C, H) : launch_list<float, false>(h, sum, last, L, k, C, H);
+        else
+            roll ? launch_list<double, true>(h, sum, last, L, k, C, H) : launch_list<double, false>(h, sum, last, L, k, C, H);
+        if (sum) {
+            TimedLaunch t(h, 4);
+            hipExtLaunchKernelGGL(k_finish, dim3(12 * h->nbox), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->d_boxes,
+                                  h->lpartials, h->list_blocks, h->clk, h->run, 1, k);
+        }
+    }
+    HIPTRY(hipGetLastError());
+    h->hh = 1 - h->hh;  // the rows of the last list step
+    h->vel_is_half = true;
+    return evaluate(h, EVAL_STEP, (finish >> (n - 1)) & 1u, n);
+}
+
+// n consecutive time steps through one HIP graph, on pair lists (lists) or as n full steps
+// (n <= kRunSteps): bit k of `finish` sums the stress at step k.  One launch for the run, so the steps follow each other without the gap
 // that separates two graph launches on the device.  run_graph finds or captures the graph of
 // the run from the current buffers (capturing records the launches without running them, and
 // leaves the handle's state as it was); graph_run launches it and advances the state.
 constexpr int kRunSteps = 16;
 constexpr size_t kMaxRunGraphs = 64;  // graphs of runs kept per handle
-dss_status run_graph(dss_handle *h, int n, unsigned finish, hipGraphExec_t *out)
+dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraphExec_t *out)
 {
-    const uint64_t key = (uint64_t)h->cur | ((uint64_t)h->hh << 1) | ((uint64_t)(h->vel_is_half ? 1 : 0) << 2) |
-                         ((uint64_t)n << 3) | ((uint64_t)finish << 8);
+    const std::pair<uint64_t, uint64_t> key((uint64_t)h->cur | ((uint64_t)h->hh << 1) |
+                                                ((uint64_t)(h->vel_is_half ? 1 : 0) << 2) |
+                                                ((uint64_t)(lists ? 1 : 0) << 3) | ((uint64_t)n << 4),
+                                            finish);
     for (auto &g : h->run_graphs)
         if (g.first == key) {
             *out = g.second;
@@ -916,7 +1099,10 @@ dss_status run_graph(dss_handle *h, int n, unsigned finish, hipGraphExec_t *out)
     hipGraph_t g = nullptr;
     HIPTRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
     dss_status s = DSS_OK;
-    for (int k = 0; k < n && !s; ++k) s = evaluate(h, EVAL_STEP, (finish >> k) & 1u);
+    if (lists)
+        s = list_window(h, n, finish);
+    else
+        for (int k = 0; k < n && !s; ++k) s = evaluate(h, EVAL_STEP, (finish >> k) & 1u);
     hipError_t e = hipStreamEndCapture(h->stream, &g);
     h->cur = cur;
     h->hh = hh;
@@ -938,35 +1124,142 @@ dss_status run_graph(dss_handle *h, int n, unsigned finish, hipGraphExec_t *out)
     return DSS_OK;
 }
 
-dss_status graph_run(dss_handle *h, int n, unsigned finish)
+// The host's bookkeeping of a run of n steps: the particles are in the other buffers after every
+// full step, and so is the history; a window on pair lists ends with one full step, and its last
+// list step commits the history too.
+void commit_run(dss_handle *h, int n, bool lists)
+{
+    if (!lists) {
+        for (int k = 0; k < n; ++k) commit_eval(h, true);
+        return;
+    }
+    h->cur = 1 - h->cur;
+    h->vel_is_half = true;
+    h->step += n;
+}
+
+dss_status graph_run(dss_handle *h, int n, bool lists, uint64_t finish)
 {
     hipGraphExec_t ge = nullptr;
-    dss_status s = run_graph(h, n, finish, &ge);
+    dss_status s = run_graph(h, n, lists, finish, &ge);
     if (s) return s;
     HIPTRY(hipGraphLaunch(ge, h->stream));
-    for (int k = 0; k < n; ++k) commit_eval(h, true);
+    commit_run(h, n, lists);
     return DSS_OK;
 }
 
 // The runs of a dss_step call of n_steps steps sampling every stress_every: a run of steps
-// starting at index k of the call (its length, and which of its steps sum the stress), or a
-// single step when fewer than two remain.
+// starting at index k of the call (its length, whether it is a window on pair lists, and which of
+// its steps sum the stress), or a single step when fewer than two remain.  Full steps: runs as
+// long as the sampling period (2 .. 16) when there is one, else kRunSteps / 2.  Windows: the rest
+// of the call (or of a sampling period longer than a window) in the fewest equal parts, rounded up
+// to whole sampling periods where they fit, so that the graphs of a call repeat; what is too short
+// for a window (the search and the full step would cost more than they save) goes as full steps.
 struct StepRuns {
-    int64_t n_steps, stress_every, step0, run;
-    StepRuns(int64_t n, int64_t se, int64_t s0)
-        : n_steps(n), stress_every(se), step0(s0), run(se >= 2 && se <= kRunSteps ? se : kRunSteps / 2) {}
+    int64_t n_steps, stress_every, step0;
+    int full, longest;
+    StepRuns(int64_t n, int64_t se, int64_t s0, int longest_)
+        : n_steps(n), stress_every(se), step0(s0), full(se >= 2 && se <= kRunSteps ? (int)se : kRunSteps / 2),
+          longest(longest_)
+    {
+    }
     bool finish_at(int64_t k) const  // k: the step's index within the call
     {
         return k == n_steps - 1 || (stress_every > 0 && (step0 + k + 1) % stress_every == 0);
     }
-    int length_at(int64_t k) const { return n_steps - k >= 2 ? (int)std::min<int64_t>(run, n_steps - k) : 1; }
-    unsigned mask_at(int64_t k, int n) const
+    int length_at(int64_t k, bool &lists) const
     {
-        unsigned mask = 0;
-        for (int j = 0; j < n; ++j) mask |= (finish_at(k + j) ? 1u : 0u) << j;
+        const int64_t left = n_steps - k;
+        lists = longest >= kListWindowMin && left >= kListWindowMin;
+        if (!lists) return left >= 2 ? (int)std::min<int64_t>(full, left) : 1;
+        int64_t span = left;
+        if (stress_every > longest) {  // to the next sample, unless it is too near
+            const int64_t to = stress_every - (step0 + k) % stress_every;
+            if (to >= kListWindowMin) span = std::min(span, to);
+        }
+        const int64_t parts = (span + longest - 1) / longest;
+        int64_t n = (span + parts - 1) / parts;
+        if (stress_every >= 2 && stress_every <= longest) {
+            const int64_t whole = (n + stress_every - 1) / stress_every * stress_every;
+            n = whole <= longest ? whole : longest / stress_every * stress_every;
+        }
+        n = std::min(n, left);
+        return (int)(n < kListWindowMin ? std::min<int64_t>(longest, left) : n);
+    }
+    uint64_t mask_at(int64_t k, int n) const
+    {
+        uint64_t mask = 0;
+        for (int j = 0; j < n; ++j) mask |= (uint64_t)(finish_at(k + j) ? 1 : 0) << j;
         return mask;
     }
 };
+
+// Enqueue n_steps time steps from the current state (graphs, or direct launches).
+dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
+{
+    const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
+    dss_status s = DSS_OK;
+    if (lists_on(h) && n_steps >= kListWindowMin) s = setup_lists(h);
+    if (s) return s;
+    const StepRuns R(n_steps, stress_every, h->step, lists_on(h) ? h->list_window : 0);
+    for (int64_t k = 0; k < n_steps;) {
+        bool lists;
+        int n = R.length_at(k, lists);
+        if (lists && !h->listable) {  // a full step first
+            lists = false;
+            n = 1;
+        }
+        if (!graphs && !lists) n = 1;
+        if (lists || !h->runs.empty()) h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half});
+        if (graphs && n >= 2)
+            s = graph_run(h, n, lists, R.mask_at(k, n));
+        else if (lists)
+            s = list_window(h, n, R.mask_at(k, n));
+        else
+            s = graphs ? graph_step(h, R.finish_at(k)) : evaluate(h, EVAL_STEP, R.finish_at(k));
+        k += n;
+        if (s) return s;
+    }
+    return DSS_OK;
+}
+
+// Read the clock.  When a window stopped early (its lists no longer held every pair, or did not
+// fit), the state on the device is the committed one of that window's start and nothing later has
+// run: the host goes back to it and takes the remaining steps, with shorter windows (none when the
+// lists did not fit).
+dss_status settle(dss_handle *h, DevClock *out)
+{
+    for (;;) {
+        DevClock c;
+        HIPTRY(hipMemcpyAsync(&c, h->clk, sizeof(c), hipMemcpyDeviceToHost, h->stream));
+        HIPTRY(hipStreamSynchronize(h->stream));
+        if (!(c.err & kErrListMask)) {
+            if (!h->runs.empty() && h->list_window > 0 && h->list_window < kListWindow && ++h->list_good >= 4) {
+                h->list_window = std::min(2 * h->list_window, kListWindow);
+                h->list_good = 0;
+            }
+            h->runs.clear();
+            if (out) *out = c;
+            return DSS_OK;
+        }
+        auto at = h->runs.rbegin();
+        while (at != h->runs.rend() && at->step != c.step) ++at;
+        if (at == h->runs.rend()) return fail(h, DSS_ERR_HIP, "a window of time steps stopped at an unknown step");
+        const int64_t target = h->step;
+        h->step = at->step;
+        h->cur = at->cur;
+        h->hh = at->hh;
+        h->vel_is_half = at->vel_is_half;
+        h->runs.clear();
+        h->list_good = 0;
+        h->list_window = (c.err & kErrListFull) || h->list_window < 2 * kListWindowMin ? 0 : h->list_window / 2;
+        c.err &= ~kErrListMask;
+        HIPTRY(hipMemcpyAsync(h->clk, &c, sizeof(c), hipMemcpyHostToDevice, h->stream));
+        HIPTRY(hipStreamSynchronize(h->stream));
+        dss_status s = enqueue_steps(h, target - h->step, h->call_every);
+        if (s) return s;
+    }
+}
 
 }  // namespace
 
@@ -1112,6 +1405,9 @@ dss_status dss_set_particles_batch(dss_handle *h, const int64_t *n_per_box, cons
         for (int d = 0; d < 3; ++d) G.L[d] = q.L[d];
         G.gd = q.shear_rate;
         G.wk = 2.0 * kPi * q.wave_n / q.L[1];  // wave number of the wavy shear, eq. uinf
+        G.amax = box_amax[b];
+        G.skin = 0.0;
+        G.blk_off = G.blk_n = 0;
         G.part_off = (int)part;
         G.n_part = (int)n_per_box[b];
         part += n_per_box[b];
@@ -1295,6 +1591,7 @@ dss_status dss_set_step(dss_handle *h, int64_t n)
     HIPTRY(hipMemcpyAsync(h->clk, &c, sizeof(c), hipMemcpyHostToDevice, h->stream));
     HIPTRY(hipStreamSynchronize(h->stream));
     h->step = n;
+    h->listable = false;
     return DSS_OK;
 }
 
@@ -1324,9 +1621,15 @@ dss_status dss_compute_forces(dss_handle *h)
 
 dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sync)
 {
-    dss_status s = require_loaded(h);
+    dss_status s = require_loaded(h, false);
     if (s) return s;
     if (n_steps < 0 || stress_every < 0) return fail(h, DSS_ERR_ARG, "negative n_steps or stress_every");
+    // a new lattice, larger sample buffers and a long queue of runs wait for the steps under way
+    if (!h->runs.empty() && (h->tune_pending || h->runs.size() >= kMaxOpenRuns ||
+                             (stress_every > 0 && n_steps / stress_every + 1 > h->sample_cap_alloc))) {
+        s = settle(h);
+        if (s) return s;
+    }
     // stress sampling schedule of this call
     int64_t first = 0, cap = 0;
     if (stress_every > 0) {
@@ -1354,44 +1657,43 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
         if (s) return s;
         h->tune_pending = false;
     }
-    const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
-    // the stress and counters are summed only when a sample is due and after the last step;
-    // with graphs, runs of steps as one launch: as long as the sampling period (2 .. 16) when
-    // there is one, so that the runs of a call repeat, else kRunSteps / 2
-    const StepRuns R(n_steps, stress_every, h->step);
-    for (int64_t k = 0; k < n_steps;) {
-        const int n = graphs ? R.length_at(k) : 1;
-        if (n >= 2)
-            s = graph_run(h, n, R.mask_at(k, n));
-        else
-            s = graphs ? graph_step(h, R.finish_at(k)) : evaluate(h, EVAL_STEP, R.finish_at(k));
-        k += n;
-        if (s) return s;
-    }
+    // the stress and counters are summed only when a sample is due and after the last step
+    h->call_every = stress_every;
+    s = enqueue_steps(h, n_steps, stress_every);
+    if (s) return s;
     if (sync) return check_flags(h);
     return DSS_OK;
 }
 
 dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
 {
-    dss_status s = require_loaded(h);
+    dss_status s = require_loaded(h, false);
     if (s) return s;
     if (n_steps < 0 || stress_every < 0) return fail(h, DSS_ERR_ARG, "negative n_steps or stress_every");
     const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
     if (!graphs || h->tune_pending) return DSS_OK;  // direct launches, or a lattice change comes first
     // walk the call's runs as dss_step will, capturing the graphs it does not have yet; only
     // the handle's bookkeeping of the buffers advances, and it is put back
+    if (lists_on(h) && n_steps >= kListWindowMin) s = setup_lists(h);
+    if (s) return s;
     const int cur = h->cur, hh = h->hh;
     const bool vih = h->vel_is_half;
     const int64_t step = h->step;
-    const StepRuns R(n_steps, stress_every, h->step);
+    const StepRuns R(n_steps, stress_every, h->step, lists_on(h) ? h->list_window : 0);
+    bool listable = h->listable;
     for (int64_t k = 0; k < n_steps && !s;) {
-        const int n = R.length_at(k);
+        bool lists;
+        int n = R.length_at(k, lists);
+        if (lists && !listable) {
+            lists = false;
+            n = 1;
+        }
+        listable = true;
         if (n >= 2) {
             hipGraphExec_t ge = nullptr;
-            s = run_graph(h, n, R.mask_at(k, n), &ge);
+            s = run_graph(h, n, lists, R.mask_at(k, n), &ge);
         }
-        for (int j = 0; j < n; ++j) commit_eval(h, true);
+        commit_run(h, n, lists);
         k += n;
     }
     h->cur = cur;
@@ -1942,16 +2244,16 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     // reverse kernels does not stop them)
     const unsigned fwd_timed = h->timing & ~((1u << 5) | (1u << 6));
     const bool graphs = h->tune.graph && !h->graph_broken && fwd_timed == 0 && !h->P.record_pairs;
-    const StepRuns R(K, stress_every, h->step);
+    const StepRuns R(K, stress_every, h->step, 0);
     for (int64_t k = 0; k < K;) {
         if (k % C == 0) {
             s = snap_save(h, W.ck[k / C]);
             if (s) return s;
         }
         const int64_t seg_end = std::min<int64_t>(K, (k / C + 1) * C);  // the next checkpoint
-        const int n = graphs && seg_end - k >= 2 ? (int)std::min<int64_t>(R.run, seg_end - k) : 1;
+        const int n = graphs && seg_end - k >= 2 ? (int)std::min<int64_t>(R.full, seg_end - k) : 1;
         if (n >= 2)
-            s = graph_run(h, n, R.mask_at(k, n));
+            s = graph_run(h, n, false, R.mask_at(k, n));
         else
             s = evaluate(h, EVAL_STEP, R.finish_at(k));
         k += n;
@@ -2241,6 +2543,7 @@ dss_status dss_load_state(dss_handle *h, const void *blob, size_t bytes)
     h->hh = 0;
     h->step = hd.step;
     h->vel_is_half = hd.vel_is_half != 0;
+    h->listable = false;  // the snapshot does not say; the next full step settles it
     return DSS_OK;
 }
 

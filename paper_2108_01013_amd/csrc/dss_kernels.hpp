@@ -28,6 +28,12 @@ constexpr int kBlock = 256;
 constexpr unsigned kErrRowOverflow = 1u;
 constexpr unsigned kErrNonFinite = 2u;
 constexpr unsigned kErrPairBuffer = 4u;
+// a window of pair lists (dss_lists.hpp) stopped: its lists no longer hold every pair, or do not
+// fit.  Every kernel of a time step returns at once while one of them is set; the host resumes
+// from the committed state and clears them.
+constexpr unsigned kErrListStop = 0x100u;
+constexpr unsigned kErrListFull = 0x200u;
+constexpr unsigned kErrListMask = kErrListStop | kErrListFull;
 
 // A history entry's key is the partner id (below 2^29) with bit 30 set when the contact's
 // Coulomb cap was active at the step that wrote it and bit 29 when its rolling limit was (the
@@ -81,6 +87,9 @@ struct BoxParams {
     int n_part;        // particles of the box
     int nrec;          // stress partial records of the box (from row_off; its cell rows when tiled)
     double wk;         // wave number 2 pi n / L_y of the wavy shear
+    double amax;       // largest radius
+    double skin;       // margin of the pair lists beyond the cutoff
+    int blk_off, blk_n;  // blocks of the pair lists (dss_lists.hpp): first, number
 };
 
 // Device-side clock and error flags.  step = time index of the state.
@@ -178,6 +187,14 @@ __device__ __forceinline__ bool listed(const DevParams &P, double dx, double dy,
     return r2 < rc * rc;
 }
 
+// Cutoff of the pair set for a pair of radius sum s, as listed() tests it.
+__device__ __forceinline__ double pair_cutoff(const DevParams &P, double s)
+{
+#pragma clang fp contract(off)
+    const double rc = P.cf * s;
+    return P.ec && !P.ec_split ? fmax(rc, s + P.rext) : rc;
+}
+
 __device__ __forceinline__ double pmass(const DevParams &P, double a)
 {
 #pragma clang fp contract(off)
@@ -253,12 +270,15 @@ __device__ __forceinline__ void total_ft(const ForceBufs &B, int p, double f[6],
 {
     double a[6];
     load_ft(B.own + 6LL * p, f);
+    if (B.nnb) {
+        // the four records are requested together (one at a time, each load waited for the last)
+        double q[4][6];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        if (r >= B.nnb) break;
-        load_ft(B.nb + 6LL * (r * B.n + p), a);
+        for (int r = 0; r < 4; ++r) load_ft(B.nb + 6LL * (r * B.n + p), q[r]);
 #pragma unroll
-        for (int k = 0; k < 6; ++k) f[k] += a[k];
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) f[k] += q[r][k];
     }
     if (!with_x) return;
     load_ft(B.x + 6LL * p, a);
@@ -292,6 +312,7 @@ __global__ void __launch_bounds__(1024) k_scan(int *__restrict__ count, int *__r
     int4 v[C4];
 #pragma unroll
     for (int k = 0; k < C4; ++k) v[k] = cnt4[k * 1024 + t];
+    if (clk->err & kErrListMask) return;  // read beside the counts
     int s[C4], incl[C4];
 #pragma unroll
     for (int k = 0; k < C4; ++k) {
@@ -348,7 +369,7 @@ __global__ void __launch_bounds__(1024) k_scan(int *__restrict__ count, int *__r
         out4[k * 1024 + t] = o;
         cnt4[k * 1024 + t] = zero;
     }
-    if (t == 0 && advance && !tile_sum) clk->step += 1;
+    if (t == 0 && advance && !tile_sum) clk->step += advance;
 }
 
 // Second pass of the multi-workgroup scan: workgroup b adds the totals of workgroups
@@ -358,8 +379,9 @@ __global__ void __launch_bounds__(1024) k_scan_add(int *__restrict__ cell_start,
 {
     __shared__ int red[16];
     const int t = threadIdx.x, b = blockIdx.x;
+    if (clk->err & kErrListMask) return;
     if (b == 0) {
-        if (t == 0 && advance) clk->step += 1;
+        if (t == 0 && advance) clk->step += advance;
         return;
     }
     int part = 0;
@@ -380,9 +402,62 @@ __global__ void __launch_bounds__(1024) k_scan_add(int *__restrict__ cell_start,
     }
 }
 
+// Kick and drift of one particle with force f[0..2] and torque f[3..5] (velocity-Verlet of
+// Sec. 2.1): the finishing kick of the step that evaluated f when V, W hold its half-step
+// velocities (half), then the drift, the half kick and the Lees-Edwards wrap at time index `next`.
+// cross: y-face crossings (-1, 0, 1).  Returns the squared displacement beyond the ambient
+// gdot y dt (the pair lists' bound is on it).
+__device__ __forceinline__ double advance_particle(const DevParams &P, const BoxParams &G, double4 &X, double4 &V,
+                                                   double4 &W, const double f[6], bool half, long long next, int &cross)
+{
+#pragma clang fp contract(off)
+    const double dt = P.dt;
+    const double a = X.w;
+    const double m = pmass(P, a);
+    const double I = 0.4 * m * a * a;
+    const double ax = f[0] / m, ay = f[1] / m, az = f[2] / m;
+    const double bx = f[3] / I, by = f[4] / I, bz = f[5] / I;
+    if (half) {  // finish the previous step: u^n = u^{n-1/2} + dt/2 alpha^n
+        V.x = V.x + 0.5 * dt * ax;
+        V.y = V.y + 0.5 * dt * ay;
+        V.z = V.z + 0.5 * dt * az;
+        W.x = W.x + 0.5 * dt * bx;
+        W.y = W.y + 0.5 * dt * by;
+        W.z = W.z + 0.5 * dt * bz;
+    }
+    const double4 X0 = X;
+    X.x = X.x + dt * V.x + 0.5 * dt * dt * ax;
+    X.y = X.y + dt * V.y + 0.5 * dt * dt * ay;
+    X.z = X.z + dt * V.z + 0.5 * dt * dt * az;
+    V.x = V.x + 0.5 * dt * ax;
+    V.y = V.y + 0.5 * dt * ay;
+    V.z = V.z + 0.5 * dt * az;
+    W.x = W.x + 0.5 * dt * bx;
+    W.y = W.y + 0.5 * dt * by;
+    W.z = W.z + 0.5 * dt * bz;
+    const double dx = (X.x - X0.x) - G.gd * X0.y * dt, dy = X.y - X0.y, dz = X.z - X0.z;
+    // Lees-Edwards wrap at t_{n+1}
+    cross = 0;
+    if (X.y >= G.L[1]) {
+        X.y -= G.L[1];
+        X.x -= le_offset(P, G, next);
+        V.x -= G.gd * G.L[1];
+        cross = 1;
+    } else if (X.y < 0.0) {
+        X.y += G.L[1];
+        X.x += le_offset(P, G, next);
+        V.x += G.gd * G.L[1];
+        cross = -1;
+    }
+    X.x -= G.L[0] * floor(X.x / G.L[0]);
+    X.z -= G.L[2] * floor(X.z / G.L[2]);
+    return dx * dx + dy * dy + dz * dz;
+}
+
 // ----------------------------------------------------------------------------------
-// k_predict: velocity-Verlet drift + half kick (advance = 1) or velocity completion
-// only (advance = 0), Lees-Edwards wrap at t_{n+1}, cell id and histogram rank.
+// k_predict: velocity-Verlet drift + half kick to time index clk->step + advance (advance >= 1;
+// the steps since the clock's index were taken on pair lists) or velocity completion only
+// (advance = 0), Lees-Edwards wrap, cell id and histogram rank.
 //   vel_is_half = 1: vel holds the half-step velocity u^{n-1/2} of the forces, and
 //   u^n = u^{n-1/2} + dt/2 F^n / m completes the previous step.
 // The atomic force record is read, and cleared for the next evaluation, only when the last
@@ -401,14 +476,19 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
 {
 #pragma clang fp contract(off)
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const DevClock c0 = *clk;
+    const bool active = p < P.N;
+    double4 X = make_double4(0.0, 0.0, 0.0, 1.0), V = X, W = X;
+    if (active) {
+        X = pa[p];
+        V = vel[p];
+        W = omg[p];
+    }
+    if (c0.err & kErrListMask) return;
     if (p == 0 && pair_count) *pair_count = 0;  // the pairs this step's pair kernels record
     if (tz && p < P.N) tz[p] = 0;  // counts the adjoint's tape fills after this evaluation
-    const bool active = p < P.N;
     int c = -1;
     if (active) {
-    double4 X = pa[p];
-    double4 V = vel[p];
-    double4 W = omg[p];
     if (tx) {
         // the state as read, by id (the adjoint's tape of the previous evaluation)
         const long long id = (long long)W.w;
@@ -419,13 +499,9 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
     // the box of the particle: the table entry of a batch, else the kernel argument (no
     // load that waits for the particle record)
     auto body = [&](const BoxParams &G) {
-    const double dt = P.dt;
-    double a = X.w;
-    double m = pmass(P, a);
-    double I = 0.4 * m * a * a;
     double f[6];
     total_ft(B, p, f, false);
-    if (clk->deferred || P.ec_split) {
+    if (c0.deferred || P.ec_split) {
         double e[6];
         load_ft(B.x + 6LL * p, e);
 #pragma unroll
@@ -433,42 +509,21 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
         const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         store_ft(B.x + 6LL * p, z);
     }
-    double ax = f[0] / m, ay = f[1] / m, az = f[2] / m;
-    double bx = f[3] / I, by = f[4] / I, bz = f[5] / I;
-    if (vel_is_half) {  // finish the previous step: u^n = u^{n-1/2} + dt/2 alpha^n
-        V.x = V.x + 0.5 * dt * ax;
-        V.y = V.y + 0.5 * dt * ay;
-        V.z = V.z + 0.5 * dt * az;
-        W.x = W.x + 0.5 * dt * bx;
-        W.y = W.y + 0.5 * dt * by;
-        W.z = W.z + 0.5 * dt * bz;
-    }
     if (advance) {
-        X.x = X.x + dt * V.x + 0.5 * dt * dt * ax;
-        X.y = X.y + dt * V.y + 0.5 * dt * dt * ay;
-        X.z = X.z + dt * V.z + 0.5 * dt * dt * az;
-        V.x = V.x + 0.5 * dt * ax;
-        V.y = V.y + 0.5 * dt * ay;
-        V.z = V.z + 0.5 * dt * az;
-        W.x = W.x + 0.5 * dt * bx;
-        W.y = W.y + 0.5 * dt * by;
-        W.z = W.z + 0.5 * dt * bz;
-        // Lees-Edwards wrap at t_{n+1}
-        double delta = le_offset(P, G, clk->step + 1);
-        if (X.y >= G.L[1]) {
-            X.y -= G.L[1];
-            X.x -= delta;
-            V.x -= G.gd * G.L[1];
-            img[(int)W.w] += 1;  // y-face crossings, for the unwrapped shear-wise position
-        } else if (X.y < 0.0) {
-            X.y += G.L[1];
-            X.x += delta;
-            V.x += G.gd * G.L[1];
-            img[(int)W.w] -= 1;
-        }
-        X.x -= G.L[0] * floor(X.x / G.L[0]);
-        X.z -= G.L[2] * floor(X.z / G.L[2]);
+        int cross;
+        advance_particle(P, G, X, V, W, f, vel_is_half != 0, c0.step + advance, cross);
+        if (cross) img[(int)W.w] += cross;  // y-face crossings, for the unwrapped shear-wise position
         pa[p] = X;
+    } else if (vel_is_half) {
+        const double dt = P.dt;
+        const double m = pmass(P, X.w);
+        const double I = 0.4 * m * X.w * X.w;
+        V.x = V.x + 0.5 * dt * (f[0] / m);
+        V.y = V.y + 0.5 * dt * (f[1] / m);
+        V.z = V.z + 0.5 * dt * (f[2] / m);
+        W.x = W.x + 0.5 * dt * (f[3] / I);
+        W.y = W.y + 0.5 * dt * (f[4] / I);
+        W.z = W.z + 0.5 * dt * (f[5] / I);
     }
     vel[p] = V;
     omg[p] = W;
@@ -550,6 +605,9 @@ __global__ void __launch_bounds__(kBlock) k_scatter(int N, const int *__restrict
 {
     __shared__ int off[16];
     const int t = threadIdx.x;
+    const int p = blockIdx.x * blockDim.x + t;
+    const int pc = p < N ? cell[p] : 0, pr = p < N ? rank[p] : 0;
+    if (clk->err & kErrListMask) return;  // read beside the cell and rank
     if (blockIdx.x == 0 && t == 0) clk->deferred = 0;  // set again by the rows of this step's pair kernels
     if (ntile > 0) {
         if (t < 64) {
@@ -562,14 +620,12 @@ __global__ void __launch_bounds__(kBlock) k_scatter(int N, const int *__restrict
             if (t < 16) off[t] = incl - v;
         }
         __syncthreads();
-        if (blockIdx.x == 0 && t == 0 && advance) clk->step += 1;
+        if (blockIdx.x == 0 && t == 0 && advance) clk->step += advance;
         for (int q = blockIdx.x * blockDim.x + t; q < ncell1; q += gridDim.x * blockDim.x)
             cell_start[q] = cs_local[q] + off[q >> 12];
     }
-    int p = blockIdx.x * blockDim.x + t;
     if (p >= N) return;
-    const int c = cell[p];
-    int dst = (ntile > 0 ? cs_local[c] + off[c >> 12] : cs_local[c]) + rank[p];
+    const int dst = (ntile > 0 ? cs_local[pc] + off[pc >> 12] : cs_local[pc]) + pr;
     pa_out[dst] = pa_in[p];
     vel_out[dst] = vel_in[p];
     omg_out[dst] = omg_in[p];
@@ -1891,11 +1947,13 @@ __global__ void __launch_bounds__(kPairBlock, 3) k_pairs(DevParams P, const BoxP
     const int t = threadIdx.x;
     const int lane = t & 63, wid = t >> 6;
     const int grow = xcd_row(blockIdx.x, gridDim.x);
+    const DevClock c0 = *clk;
     const BoxParams G = boxes[P.nbox > 1 ? row_box[grow] : 0];
     const int nxc = G.nc[0], nzc = G.nc[2];
     const int row = grow - G.row_off;  // cell row within the box
     const int cz = row / G.nc[1];
-    const double delta = le_offset(P, G, clk->step);
+    if (c0.err & kErrListMask) return;
+    const double delta = le_offset(P, G, c0.step);
     PairTally tally;
 #pragma unroll
     for (int k = 0; k < 9; ++k) tally.S[k] = 0.0;
@@ -2368,14 +2426,17 @@ __global__ void __launch_bounds__(kBlock) k_pairs_ec(DevParams P, const BoxParam
 // ----------------------------------------------------------------------------------
 __global__ void __launch_bounds__(kBlock) k_finish(const BoxParams *__restrict__ boxes,
                                                     const double *__restrict__ partials, int pstride,
-                                                    DevClock *__restrict__ clk, DevRun *__restrict__ run, int sample)
-// partials: 12 components x pstride records
+                                                    DevClock *__restrict__ clk, DevRun *__restrict__ run, int sample,
+                                                    int list_step)
+// partials: 12 components x pstride records; list_step: 0, or the window's step on the pair lists
+// (the records are then those of the box's blocks, and the time index is the clock's plus it)
 {
     __shared__ double red[kBlock / 64];
+    if (clk->err & kErrListMask) return;
     const int t = threadIdx.x;
     const int b = blockIdx.x / 12, k = blockIdx.x - (blockIdx.x / 12) * 12;
     const BoxParams &G = boxes[b];
-    const int r0 = G.row_off, nrow = G.nrec;
+    const int r0 = list_step ? G.blk_off : G.row_off, nrow = list_step ? G.blk_n : G.nrec;
     const double *src = partials + (long long)k * pstride + r0;
     double acc = 0.0;
     if (k == 11) {
@@ -2392,7 +2453,7 @@ __global__ void __launch_bounds__(kBlock) k_finish(const BoxParams *__restrict__
     for (int w = 0; w < kBlock / 64; ++w) x = (k == 11) ? fmax(x, red[w]) : x + red[w];
     if (k < 9) {
         run->sigma_last[9 * b + k] = x;
-        const long long n = clk->step;
+        const long long n = clk->step + list_step;
         if (sample && run->sample_every > 0 && n % run->sample_every == 0 && n >= run->sample_first) {
             const long long slot = (n - run->sample_first) / run->sample_every;
             if (slot < run->sample_cap) run->samples[(slot * (gridDim.x / 12) + b) * 9 + k] = x;

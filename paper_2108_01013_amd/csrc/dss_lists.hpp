@@ -1,0 +1,515 @@
+// dss_lists.hpp -- windows of time steps on pair lists.
+//
+// Most pairs of one time step are the pairs of the next: the particles move by about 1e-3 of a
+// radius per step.  dss_step therefore takes runs of steps as windows.  A window of n steps from
+// a committed state is
+//   k_list_begin          the pairs inside the cutoff plus a margin (skin) at the window's first
+//                         state, with their stored stretches, and the first kick and drift;
+//   k_list x (n - 1)      one launch per step: the pair physics over the lists, the Stokes terms,
+//                         the finishing kick and the next kick, drift and wrap;
+//   a full step           the counting sort, search and pair kernels of dss_kernels.hpp, which leave
+//                         the sorted order, cells, history rows and force records of an ordinary step.
+// The listed-pair test of every step is the FP64 one at the step's own positions: the list only
+// holds more candidates than the test accepts, so the pair set, forces and history are those of a
+// search at every step (up to the order of sums).
+//
+// Validity.  With A = 1 + gdot dt e_x e_y the separation of two particles (or of a particle and
+// an image across the sheared faces) advances as r' = A r + d_j - d_i, d the displacement of a
+// particle in the step beyond the ambient gdot y dt.  So after n steps, with g = gdot n dt and
+// s+- = sqrt(1 + g^2 / 4) +- g / 2 the singular values of A^n,
+//   |r_n| >= s- |r_0| - s+ (D_i + D_j),  D_i = sum_k |d_i,k|,
+// and no pair outside the list is inside its cutoff while s- (rc + skin) - 2 s+ D >= rc for the
+// largest cutoff rc of the box and every D.  Each particle's sum is kept beside its record (a
+// maximum over the box instead, by an atomic of every workgroup on one word, took 50 of the 76 us
+// of a step of 100k particles); a particle that finds the next step beyond the bound (or a list, a
+// history row or a force out of range) sets a flag in
+// the clock's error word, every later kernel of the stream's queue then returns at once, and the
+// committed state at the window's start, which a window writes only in its last list step, is
+// where the host resumes (dss_api.hip, settle).
+//
+// Work split.  One workgroup per block of consecutive sorted slots (about one x-row of cells; the
+// blocks of one box never span another).  It evaluates the pairs inside its block once and
+// every pair that crosses its border on its own side, so a particle's force is complete in its
+// workgroup's LDS and the integration follows in the same launch: no partner records (192 B per
+// particle written and read back each step by the row tiles), no second launch.  A pair that
+// crosses blocks is evaluated by both workgroups from the same inputs in the same orientation, so
+// both hold the same stretch to the bit.
+// Measured (FP64, a sheared box): N = 100k, 24 us per list step against 64 us for a full step
+// (k_pairs 40, k_predict 9, k_scatter 6, k_scan 4, and their launches); N = 500k, 103 against
+// 360 us; N = 1000, 6.4 against 27 us.
+#pragma once
+
+#include "dss_kernels.hpp"
+
+namespace dss {
+
+constexpr int kListBlock = 192;       // lanes of k_list: four workgroups per CU at 168 VGPRs
+constexpr int kBeginBlock = 256;      // lanes of k_list_begin
+constexpr int kBeginLanes = 8;        // lanes that take a run of candidates together
+constexpr int kBeginRuns = 2;         // runs of a lane in flight
+constexpr int kBeginRows = 1024;      // (particle, cell row) pairs of a batch of its search
+constexpr int kListOwnMax = 128;      // particles of a block
+constexpr int kListPerOwn = 24;       // list entries allotted per particle of a block
+constexpr int kListSpare = 64;        // and per block
+
+// One particle in a window: (x, y, z, a), (u, box), (w, id); a neighbour gather is one 96-byte record.
+struct ListRec {
+    double4 p, v, w;
+};
+
+// A block of consecutive slots of one box; its list starts at entry e0.
+struct ListBlock {
+    int start, n, box, e0;
+};
+
+// A list entry.  x: partner slot, kEntSwap when the partner is the pair's first member (the pair is
+// evaluated in that orientation), kEntHas when a stretch is stored.  y: the own particle's index in
+// the block, and for a pair inside the block the partner's (from bit 8) and kEntIn.
+constexpr int kEntSlot = 0x1fffffff;
+constexpr int kEntSwap = 0x20000000;
+constexpr int kEntHas = 0x40000000;
+constexpr int kEntIn = 0x40000000;
+constexpr int kEntIdx = 0xff;
+constexpr int kEntIdxBits = 8;
+constexpr int kClasses = 5;  // contacts inside the block and across, listed pairs across and inside, margin
+
+struct ListView {
+    const ListBlock *blocks;
+    int2 *ent;
+    double *xi, *xr;      // 3 per entry; xr only with rolling resistance
+    int *n;               // entries of each block
+    double *dsum;         // displacement sum D of the bound above, by slot
+    int *cross;           // y-face crossings of the window by slot
+    int own_cap;          // largest block
+};
+
+// The committed state of a handle: read by k_list_begin, written by the last list step.
+struct CommittedView {
+    double4 *pa, *vel, *omg;
+    ForceBufs B;
+    int *img;
+};
+
+// Largest displacement sum of a particle with which the lists hold every pair after n steps.
+__device__ __forceinline__ double list_budget(const DevParams &P, const BoxParams &G, double skin, int n)
+{
+    const double g = fabs(G.gd) * P.dt * (double)n;
+    const double q = sqrt(1.0 + 0.25 * g * g);
+    const double rc = pair_cutoff(P, 2.0 * G.amax);
+    return ((q - 0.5 * g) * (rc + skin) - rc * (1.0 + 1e-12)) / (2.0 * (q + 0.5 * g));
+}
+
+// Periodic difference b - a of two cell coordinates in (-n/2, n/2], 0 for the ambiguous half.
+__device__ __forceinline__ int cell_diff(int a, int b, int n)
+{
+    int d = b - a;
+    if (2 * d > n) d -= n;
+    if (2 * d < -n) d += n;
+    return 2 * d == n || 2 * d == -n ? 0 : d;
+}
+
+// Whether j is in the forward half shell of i (then i is the pair's first member): by the cell
+// offsets along z, y, x, then by slot.  Antisymmetric, so both blocks of a pair agree.
+__device__ __forceinline__ bool list_forward(const BoxParams &G, const double icw[3], const double4 &Xi,
+                                             const double4 &Xj, int i, int j)
+{
+    const int dz = cell_diff((int)(Xi.z * icw[2]), (int)(Xj.z * icw[2]), G.nc[2]);
+    if (dz) return dz > 0;
+    const int dy = cell_diff((int)(Xi.y * icw[1]), (int)(Xj.y * icw[1]), G.nc[1]);
+    if (dy) return dy > 0;
+    const int dx = cell_diff((int)(Xi.x * icw[0]), (int)(Xj.x * icw[0]), G.nc[0]);
+    return dx ? dx > 0 : j > i;
+}
+
+// The cell rows around a particle: rows (cz + z0 .. , cy + y0 ..), ny x nz of them.  Where the reach
+// spans more rows than the box has (small boxes), every row is taken once and along its whole
+// length (whole).
+struct ListRows {
+    int ny, nz, y0, z0;
+    bool whole;
+};
+
+__device__ __forceinline__ ListRows list_rows(const BoxParams &G, double reach)
+{
+    const int Ry = (int)ceil(reach / G.cw[1]), Rz = (int)ceil(reach / G.cw[2]);
+    ListRows R;
+    R.whole = 2 * Ry + 1 > G.nc[1] || 2 * Rz + 1 > G.nc[2] || 2.0 * reach + 2.0 * G.cw[0] > G.L[0];
+    R.ny = R.whole ? G.nc[1] : 2 * Ry + 1;
+    R.nz = R.whole ? G.nc[2] : 2 * Rz + 1;
+    R.y0 = -Ry;
+    R.z0 = -Rz;
+    return R;
+}
+
+// A run of candidates of one particle of the block: slots jb .. jb + n, all with the same image
+// (cross: y-face crossing, w: box lengths along x, z: box lengths along z; without `whole`).
+struct ListTask {
+    int jb, code;
+};
+__device__ __forceinline__ ListTask list_task(int jb, int n, int il, int cross, int w, int z)
+{
+    return {jb, n | (il << 16) | ((cross + 1) << 24) | ((z + 1) << 26) | ((w + 4) << 28)};
+}
+
+// Candidates of row (qy, qz) of the rows R around particle il at Xi: at most two runs.  A row
+// farther than reach in y-z has none; a row reached across a y face is searched around the x
+// shifted by the Lees-Edwards offset.  icw: 1 / cell widths.
+template <typename Push>
+__device__ __forceinline__ void list_row(const BoxParams &G, const double icw[3], double delta,
+                                         const int *__restrict__ cell_start, const ListRows &R, int il,
+                                         const double4 &Xi, double reach, int qy, int qz, Push &&push)
+{
+    const int nxc = G.nc[0], nyc = G.nc[1], nzc = G.nc[2];
+    if (R.whole) {
+        const int base = G.cell_off + (qz * nyc + qy) * nxc;
+        const int jb = cell_start[base], n = cell_start[base + nxc] - jb;
+        if (n > 0) push(list_task(jb, n, il, 0, 0, 0));
+        return;
+    }
+    // the margin of the window covers the rounding of these cell numbers too
+    const int zu = (int)(Xi.z * icw[2]) + qz + R.z0, yu = (int)(Xi.y * icw[1]) + qy + R.y0;
+    const double zlo = (double)zu * G.cw[2], ylo = (double)yu * G.cw[1];
+    const double ez = fmax(0.0, fmax(zlo - Xi.z, Xi.z - (zlo + G.cw[2])));
+    const double ey = fmax(0.0, fmax(ylo - Xi.y, Xi.y - (ylo + G.cw[1])));
+    const double h2 = reach * reach - (ey * ey + ez * ez);
+    if (h2 <= 0.0) return;
+    const int cross = yu >= nyc ? 1 : (yu < 0 ? -1 : 0), cz = zu >= nzc ? 1 : (zu < 0 ? -1 : 0);
+    // the window in x, wider by what FP32 rounds off the root
+    const double xs = Xi.x - (cross > 0 ? delta : (cross < 0 ? -delta : 0.0));
+    const double hw = (double)__builtin_sqrtf((float)h2) * (1.0 + 1e-6) + 1e-9 * G.L[0];
+    int xl = (int)floor((xs - hw) * icw[0]);
+    int span = (int)floor((xs + hw) * icw[0]) - xl + 1, w = 0;
+    for (; xl < 0; xl += nxc) --w;
+    for (; xl >= nxc; xl -= nxc) ++w;
+    const int base = G.cell_off + ((zu - cz * nzc) * nyc + yu - cross * nyc) * nxc;
+    const int len = min(span, nxc - xl);
+    const int jb = cell_start[base + xl], n = cell_start[base + xl + len] - jb;
+    if (n > 0) push(list_task(jb, n, il, cross, w, cz));
+    if (span > len) {
+        const int j2 = cell_start[base], n2 = cell_start[base + span - len] - j2;
+        if (n2 > 0) push(list_task(j2, n2, il, cross, w + 1, cz));
+    }
+}
+
+// ----------------------------------------------------------------------------------
+// k_list_begin: the lists of one block at the committed state, and the first kick and drift of
+// the block's particles into the window's records.  In batches of kBeginRows (particle, cell row)
+// pairs the lanes write the candidate runs of their rows into LDS, then take the runs (so every
+// lane has one, although most rows are out of reach) and push the candidates that pass into a
+// queue; then all lanes take the queued ones: the pair's orientation and class (contacts, listed
+// pairs, candidates of the margin, stored in this order, so that a wavefront of k_list holds one
+// kind), a pair inside the block from its first member only, and the stored stretch from the
+// committed history rows.  (One particle per eight lanes, each walking its share of the rows:
+// 73 us at N = 100k, 53 us so.)
+// ----------------------------------------------------------------------------------
+template <bool Roll>
+__global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const BoxParams *__restrict__ boxes,
+                                                             const int *__restrict__ cell_start, CommittedView C,
+                                                             HistView H, ListView L, ListRec *__restrict__ out,
+                                                             int vel_is_half, DevClock *__restrict__ clk)
+{
+    extern __shared__ int2 q_lds[];
+    __shared__ ListTask tasks[2 * kBeginRows];
+    __shared__ int qn, tn, cnt[kClasses + 1], pos[kClasses];
+    const int t = threadIdx.x;
+    const int blk = xcd_row(blockIdx.x, gridDim.x);
+    const ListBlock K = L.blocks[blk];
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const BoxParams G = boxes[K.box];
+    const int cap = kListPerOwn * K.n + kListSpare;
+    const double skin = G.skin;
+    if (t <= kClasses) cnt[t] = 0;
+    if (t == 0) qn = tn = 0;
+    const double delta = le_offset(P, G, c0.step);
+    const ListRows R = list_rows(G, pair_cutoff(P, 2.0 * G.amax) + skin);
+    const double icw[3] = {1.0 / G.cw[0], 1.0 / G.cw[1], 1.0 / G.cw[2]};
+    // (particle, row) pairs numbered with a power of two of rows per particle
+    int sh = 0;
+    while ((1 << sh) < R.ny * R.nz) ++sh;
+    const int all = K.n << sh;
+    __syncthreads();
+    for (int k0 = 0; k0 < all; k0 += kBeginRows) {
+        for (int k = k0 + t; k < min(k0 + kBeginRows, all); k += kBeginBlock) {
+            const int il = k >> sh, q = k & ((1 << sh) - 1), qz = q / R.ny, qy = q - qz * R.ny;
+            if (qz >= R.nz) continue;
+            const double4 Xi = C.pa[K.start + il];
+            list_row(G, icw, delta, cell_start, R, il, Xi, pair_cutoff(P, Xi.w + G.amax) + skin, qy, qz,
+                     [&](const ListTask &a) { tasks[atomicAdd(&tn, 1)] = a; });
+        }
+        __syncthreads();
+        const int nt = tn;
+        // kBeginLanes lanes take one run together (their loads are contiguous), kBeginRuns runs at a
+        // time (their loads are in flight together)
+        const int sub = t & (kBeginLanes - 1);
+        for (int k = t / kBeginLanes; k < nt; k += kBeginRuns * kBeginBlock / kBeginLanes) {
+            int jb[kBeginRuns], n[kBeginRuns], il[kBeginRuns], most = 0;
+            double sx[kBeginRuns], sy[kBeginRuns], sz[kBeginRuns], ai[kBeginRuns];
+            double4 Y[kBeginRuns];
+#pragma unroll
+            for (int r = 0; r < kBeginRuns; ++r) {
+                const int m = k + r * (kBeginBlock / kBeginLanes);
+                const ListTask a = tasks[min(m, nt - 1)];
+                const int cross = ((a.code >> 24) & 3) - 1, z = ((a.code >> 26) & 3) - 1, w = ((a.code >> 28) & 7) - 4;
+                jb[r] = a.jb;
+                n[r] = m < nt ? a.code & 0xffff : 0;
+                il[r] = (a.code >> 16) & 0xff;
+                const double4 X = C.pa[K.start + il[r]];
+                sx[r] = X.x - ((double)cross * delta + (double)w * G.L[0]);
+                sy[r] = X.y - (double)cross * G.L[1];
+                sz[r] = X.z - (double)z * G.L[2];
+                ai[r] = X.w;
+                most = max(most, n[r]);
+            }
+            for (int j0 = sub; j0 < most; j0 += kBeginLanes) {
+#pragma unroll
+                for (int r = 0; r < kBeginRuns; ++r) Y[r] = C.pa[jb[r] + (j0 < n[r] ? j0 : 0)];
+#pragma unroll
+                for (int r = 0; r < kBeginRuns; ++r) {
+                    double dx = Y[r].x - sx[r], dy = Y[r].y - sy[r], dz = Y[r].z - sz[r];
+                    if (R.whole) min_image(G, delta, sx[r], sy[r], sz[r], Y[r].x, Y[r].y, Y[r].z, dx, dy, dz);
+                    const double rl = pair_cutoff(P, ai[r] + Y[r].w) + skin;
+                    if (j0 < n[r] && jb[r] + j0 != K.start + il[r] && dx * dx + dy * dy + dz * dz < rl * rl) {
+                        const int e = atomicAdd(&qn, 1);
+                        if (e < cap) q_lds[e] = make_int2(jb[r] + j0, il[r]);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (t == 0) tn = 0;
+        __syncthreads();
+    }
+    if (t < K.n) {
+        const int i = K.start + t;
+        double4 X = C.pa[i], V = C.vel[i], W = C.omg[i];
+        double f[6];
+        total_ft(C.B, i, f, clk->deferred != 0);
+        int cross = 0;
+        const double d = sqrt(advance_particle(P, G, X, V, W, f, vel_is_half != 0, clk->step + 1, cross));
+        out[i].p = X;
+        out[i].v = V;
+        out[i].w = W;
+        L.cross[i] = cross;
+        L.dsum[i] = d;
+        if (!(d <= list_budget(P, G, skin, 1))) atomicOr(&clk->err, kErrListStop);
+    }
+    __syncthreads();
+    const int total = qn;
+    if (total > cap) {
+        if (t == 0) atomicOr(&clk->err, kErrListFull);
+        return;
+    }
+    for (int k = t; k < total; k += kBeginBlock) {
+        int2 e = q_lds[k];
+        const int i = K.start + e.y, j = e.x, jl = j - K.start;
+        const double4 Xi = C.pa[i], Xj = C.pa[j];
+        double dx, dy, dz;
+        min_image(G, delta, Xi.x, Xi.y, Xi.z, Xj.x, Xj.y, Xj.z, dx, dy, dz);
+        const double r2 = dx * dx + dy * dy + dz * dz, s = Xi.w + Xj.w, rc = pair_cutoff(P, s);
+        const bool fwd = list_forward(G, icw, Xi, Xj, i, j), in = jl >= 0 && jl < K.n;
+        const int cls = in && !fwd ? kClasses : (r2 < s * s * (1.0 + 1e-9) ? (in ? 0 : 1) : (r2 < rc * rc ? (in ? 3 : 2) : 4));
+        atomicAdd(&cnt[cls], 1);
+        q_lds[k] = make_int2(j | (fwd ? 0 : kEntSwap),
+                             e.y | (in ? (jl << kEntIdxBits) | kEntIn : 0) | (cls << (2 * kEntIdxBits)));
+    }
+    __syncthreads();
+    if (t == 0) {
+        int n = 0;
+        for (int c = 0; c < kClasses; ++c) {
+            pos[c] = n;
+            n += cnt[c];
+        }
+        L.n[blk] = n;
+    }
+    __syncthreads();
+    for (int k = t; k < total; k += kBeginBlock) {
+        int2 e = q_lds[k];
+        const int cls = (e.y >> (2 * kEntIdxBits)) & 7;
+        if (cls == kClasses) continue;
+        const int slot = K.e0 + atomicAdd(&pos[cls], 1);
+        e.y &= ~(7 << (2 * kEntIdxBits));
+        const int i = K.start + (e.y & kEntIdx), j = e.x & kEntSlot;
+        const int a = (e.x & kEntSwap) ? j : i, b = (e.x & kEntSwap) ? i : j;
+        const int ida = (int)C.omg[a].w, idb = (int)C.omg[b].w;
+        double x[3], y[3] = {0.0, 0.0, 0.0};
+        // only a pair in contact at the committed state has a stored stretch (the host does not begin
+        // a window when the offset was changed after that step); the class is by r^2, the rows
+        // hold those with sqrt(r^2) - a_i - a_j < 0
+        if (cls < 2 && (row_find(H.key_old, H.xi_old, H.cnt_old, P.M, a, idb, x, Roll ? H.xr_old : nullptr, y) ||
+            row_find(H.key_old, H.xi_old, H.cnt_old, P.M, b, ida, x, Roll ? H.xr_old : nullptr, y))) {
+            const double sg = ida > idb ? -1.0 : 1.0;  // stored from the smaller id to the larger
+            e.x |= kEntHas;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                L.xi[3LL * slot + c] = sg * x[c];
+                if constexpr (Roll) L.xr[3LL * slot + c] = y[c];
+            }
+        }
+        L.ent[slot] = e;
+    }
+}
+
+// ----------------------------------------------------------------------------------
+// k_list: time step n of the window (1 .. length - 1) of one block: the listed pairs at the records
+// `in` (the physics and history of the pair kernels), the Stokes terms, then the finishing kick
+// and the next step's kick, drift and wrap into `out`; with Last, instead, the state, the force
+// record and the sorted history rows of the step are committed.  Sum: the block's stress and
+// counters go to its partial record.
+// Bound by FP64 issue and by the latency of the partner gathers: three wavefronts per workgroup
+// and four workgroups per CU keep twelve wavefronts per CU in flight (the register file's limit
+// at the physics' 168 VGPRs).
+// ----------------------------------------------------------------------------------
+template <typename Real, bool Roll, bool Sum, bool Last>
+__global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxParams *__restrict__ boxes,
+                                                         BoxParams G0, ListView L, const ListRec *__restrict__ in,
+                                                         ListRec *__restrict__ out, int n, CommittedView C, HistView H,
+                                                         DevClock *__restrict__ clk, double *__restrict__ partials,
+                                                         int pstride)
+{
+    extern __shared__ double4 list_lds[];
+    // the block's records, 6 accumulators per particle, contact counts
+    ListRec *const rec = reinterpret_cast<ListRec *>(list_lds);
+    double *const acc = reinterpret_cast<double *>(rec + L.own_cap);
+    int *const cnt = reinterpret_cast<int *>(acc + 6 * L.own_cap);
+    __shared__ double red[kListBlock / 64][12];
+    const int t = threadIdx.x;
+    const int blk = xcd_row(blockIdx.x, gridDim.x);
+    // everything the block's number leads to is requested before the first use
+    const ListBlock K = L.blocks[blk];
+    const int ne = L.n[blk];
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const BoxParams G = P.nbox > 1 ? boxes[K.box] : G0;
+    {
+        const double2 *const src = reinterpret_cast<const double2 *>(in + K.start);
+        double2 *const dst = reinterpret_cast<double2 *>(rec);
+        for (int k = t; k < 6 * K.n; k += kListBlock) {
+            dst[k] = src[k];
+            acc[k] = 0.0;
+        }
+        for (int k = t; k < K.n; k += kListBlock) cnt[k] = 0;
+    }
+    const double delta = le_offset(P, G, c0.step + n);
+    PairTally tally;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) tally.S[k] = 0.0;
+    tally.npair = tally.ncont = 0;
+    tally.fill = 0;
+    bool bad = false;
+    __syncthreads();
+    // the entry of the lane's next round is requested a round ahead, and the stretch with the
+    // records: one memory latency per round instead of three
+    int2 next = t < ne ? L.ent[K.e0 + t] : make_int2(0, 0);
+    for (int k = t; k < ne; k += kListBlock) {
+        const int2 e = next;
+        if (k + kListBlock < ne) next = L.ent[K.e0 + k + kListBlock];
+        const int il = e.y & kEntIdx, jl = (e.y >> kEntIdxBits) & kEntIdx;
+        const bool swap = (e.x & kEntSwap) != 0, has = (e.x & kEntHas) != 0, inside = (e.y & kEntIn) != 0;
+        const int own = K.start + il;
+        ListRec A, B = rec[il];
+        if (inside)
+            A = rec[jl];
+        else
+            A = in[e.x & kEntSlot];
+        const double4 Xi = swap ? A.p : B.p, Xj = swap ? B.p : A.p;
+        const double4 Vi = swap ? A.v : B.v, Vj = swap ? B.v : A.v;
+        const double4 Wi = swap ? A.w : B.w, Wj = swap ? B.w : A.w;
+        double xo[3] = {0.0, 0.0, 0.0}, xro[3] = {0.0, 0.0, 0.0};
+        double *const xs = L.xi + 3LL * (K.e0 + k);
+        if (has) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                xo[c] = xs[c];
+                if constexpr (Roll) xro[c] = L.xr[3LL * (K.e0 + k) + c];
+            }
+        }
+        double dx, dy, dz, r2;
+        min_image(G, delta, Xi.x, Xi.y, Xi.z, Xj.x, Xj.y, Xj.z, dx, dy, dz);
+        const bool on = listed(P, dx, dy, dz, Xi.w, Xj.w, r2);
+        const double dist = sqrt(r2);
+        const bool touch = on && dist - Xi.w - Xj.w < 0.0;
+        if (has != touch) L.ent[K.e0 + k].x = e.x ^ kEntHas;  // the stretch is dropped, or begins at zero
+        if (!on) continue;
+        PairOut o;
+        double S[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        pair_physics<Real, Roll, false>(P, G.gd, G.wk, dx, dy, dz, dist, Xi.w, Xj.w, Xi.y, Xj.y, Vi, Vj, Wi, Wj, xo,
+                                        xro, S, o);
+        double *const a = acc + 6 * il;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            atomicAdd(a + c, swap ? -o.Fi[c] : o.Fi[c]);
+            atomicAdd(a + 3 + c, swap ? o.Tj[c] : o.Ti[c]);
+        }
+        if (inside) {
+            double *const b = acc + 6 * jl;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                atomicAdd(b + c, -o.Fi[c]);
+                atomicAdd(b + 3 + c, o.Tj[c]);
+            }
+        }
+        if (!swap) {
+            // the pair's first member counts it, holds its history row entry and its stress
+            ++tally.npair;
+            if constexpr (Sum) {
+#pragma unroll
+                for (int c = 0; c < 9; ++c) tally.S[c] += S[c];
+            }
+        }
+        if (o.contact) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                xs[c] = o.xi[c];
+                if constexpr (Roll) L.xr[3LL * (K.e0 + k) + c] = o.xr[c];
+            }
+            if (!swap) {
+                ++tally.ncont;
+                const int slot = atomicAdd(&cnt[il], 1);
+                if constexpr (Last)
+                    store_history<Roll>(H, P.M, own, slot, (int)Wi.w, (int)Wj.w, o, clk);
+                else
+                    bad = bad || slot >= P.M;  // the row would overflow: the full step reports it
+            }
+        }
+    }
+    if constexpr (Sum) reduce_sums(tally, red, partials, pstride, blk);
+    __syncthreads();
+    for (int il = t; il < K.n; il += kListBlock) {
+        const int i = K.start + il;
+        double4 X = rec[il].p, V = rec[il].v, W = rec[il].w;
+        double f[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) f[c] = acc[6 * il + c];
+        stokes_terms<false>(P, G, X, V, W, f, nullptr);
+        tally.fill = max(tally.fill, cnt[il]);
+        if constexpr (Last) {
+            C.pa[i] = X;
+            C.vel[i] = V;
+            C.omg[i] = W;
+            store_ft(C.B.own + 6LL * i, f);
+            if (c0.deferred) {
+                const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+                store_ft(C.B.x + 6LL * i, z);  // of the evaluation before the window
+            }
+            if (L.cross[i]) C.img[(int)W.w] += L.cross[i];
+            if (!finite6(f)) atomicOr(&clk->err, kErrNonFinite);
+            finish_row<Roll>(H, P.M, i, cnt[il], (int)W.w);
+        } else {
+            int cross = 0;
+            const double d = L.dsum[i] + sqrt(advance_particle(P, G, X, V, W, f, true, c0.step + n + 1, cross));
+            bad = bad || !finite6(f) || !(d <= list_budget(P, G, G.skin, n + 1));
+            L.dsum[i] = d;
+            if (cross) L.cross[i] += cross;
+            out[i].p = X;
+            out[i].v = V;
+            out[i].w = W;
+        }
+    }
+    if constexpr (Sum) reduce_fill(tally.fill, red, partials, pstride, blk);
+    if constexpr (!Last) {
+        if (bad) atomicOr(&clk->err, kErrListStop);
+    }
+}
+
+}  // namespace dss

@@ -1,0 +1,226 @@
+"""Windows of time steps on pair lists against the same steps taken one call at a time (a call of
+one step is an ordinary full step, checked in lockstep with the oracle by the other tests): the
+state, the stress samples, the committed history and the counters.
+
+Tolerance: the two differ by the order of sums only, about 1e-16 relative per step; the
+contact stiffness (kn dt^2 / m ~ 1e-2) amplifies a difference of positions by at most a few
+per cent per step, so 1e-10 of the largest value holds over the 20 to 70 steps taken here; in
+mixed precision a pair may be rounded to 32 bits in its other orientation, 1e-7 of a pair force
+with the same growth: 1e-5."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2108_01013_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def rel(a, b):
+    return float(np.max(np.abs(np.asarray(a) - np.asarray(b))) / max(np.max(np.abs(b)), 1e-300))
+
+
+def near_x(a, b, L):
+    d = a - b
+    d -= np.asarray(L) * np.round(d / np.asarray(L))
+    return float(np.max(np.abs(d)))
+
+
+def run_both(make, steps, every, tol, L, calls=1):
+    """One call (or `calls` calls) of many steps against calls of one step."""
+    a, b = make(), make()
+    for c in range(calls):
+        a.step(steps, stress_every=every, sync=(c == calls - 1))
+    last, mean, ns = a.read_stress()
+    samples = []
+    for k in range(steps * calls):
+        b.step(1)
+        if every and b.info()["step"] % every == 0 and k >= steps * (calls - 1):
+            samples.append(b.read_stress()[0])
+    assert ns == len(samples)
+    assert rel(last, b.read_stress()[0]) < tol
+    if samples:
+        assert rel(mean, np.mean(samples, axis=0)) < tol
+    sa, sb = a.state(), b.state()
+    for k in ("u", "w", "F", "T"):
+        assert rel(sa[k], sb[k]) < tol, k
+    assert near_x(sa["x"], sb["x"], L) < tol
+    ia, ib = a.info(), b.info()
+    # (the largest row depends on which of two particles of one cell was sorted first)
+    for k in ("n_pairs", "n_contacts", "step", "error_flags", "cells"):
+        assert ia[k] == ib[k], k
+    pa, xa = a.history()
+    pb, xb = b.history()
+    assert np.array_equal(pa, pb)
+    if len(xb):
+        assert rel(xa, xb) < max(tol, 1e-9)
+    assert np.array_equal(a.cells()[1], b.cells()[1])
+    a.close()
+    b.close()
+    return len(pb)
+
+
+@pytest.fixture(scope="module")
+def box():
+    w = synth.bidisperse_box(2500, 0.55, 31)
+    rng = np.random.default_rng(5)
+    u = 0.05 * rng.standard_normal(w.x.shape)
+    u[:, 0] += w.x[:, 1]
+    return w, w.rad * 1.0005, u, 0.05 * rng.standard_normal(w.x.shape)
+
+
+@pytest.mark.parametrize("steps,every", [(5, 0), (33, 1), (64, 10), (70, 48)])
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("rolling", [False, True])
+def test_window_lengths(box, steps, every, precision, rolling):
+    from paper_2108_01013_amd.dss import Simulation
+    w, rad, u, om = box
+    p = dict(w.params, **(dict(kr=0.05 * w.params["kn"], mu_r=0.1) if rolling else {}))
+
+    def make():
+        s = Simulation(p, precision=precision)
+        s.set_particles(w.x, rad, u, om)
+        return s
+
+    assert run_both(make, steps, every, 1e-5 if precision else 1e-10, p["L"]) > 200
+
+
+@pytest.mark.parametrize("n,side", [(1, 14.0), (2, 14.0), (17, 9.5), (300, 16.0)])
+def test_small_boxes(n, side):
+    """From one particle, and lattices whose search spans every cell row (4 x 3 x 3 cells)."""
+    from paper_2108_01013_amd.dss import Simulation
+    rng = np.random.default_rng(n)
+    rad = synth.bidisperse_radii(n, seed=n) if n > 2 else np.ones(n)
+    L = [max(side, 13.0), side, side]
+    x = rng.uniform(0.0, 1.0, (n, 3)) * L if n < 300 else synth.relax_positions(rad, side, seed=4)
+    p = synth.default_params(L, shear_rate=3.0)
+
+    def make():
+        s = Simulation(p)
+        s.set_particles(x, rad)
+        s.set_step(4321)
+        s.compute_forces()
+        return s
+
+    # 17 random centres overlap deeply at first: 20 steps of a violent start
+    run_both(make, 40 if n != 17 else 20, 7, 1e-10 if n != 17 else 1e-7, L)
+
+
+def test_several_calls_without_a_wait(box):
+    from paper_2108_01013_amd.dss import Simulation
+    w, rad, u, om = box
+
+    def make():
+        s = Simulation(w.params)
+        s.set_particles(w.x, rad, u, om)
+        return s
+
+    run_both(make, 20, 5, 1e-10, w.params["L"], calls=3)
+
+
+def test_lattice_change_before_a_window(box):
+    """The first step on a new lattice is a full one: only its counting sort fills the cell starts
+    that the lists are searched with."""
+    from paper_2108_01013_amd.dss import Simulation
+    w, rad, u, om = box
+
+    def make():
+        s = Simulation(w.params)
+        s.set_particles(w.x, rad, u, om)
+        s.step(8)
+        s.set_tuning(cell_scale=1.25)
+        return s
+
+    run_both(make, 24, 6, 1e-10, w.params["L"])
+
+
+@pytest.mark.parametrize("calls", [1, 3])
+def test_window_that_stops(calls):
+    """Particles fast enough to use up the lists' margin within a window: the steps after it are
+    taken again from the window's start, also when the caller waits only after several calls."""
+    from paper_2108_01013_amd.dss import Simulation
+    rng = np.random.default_rng(8)
+    n, L = 1500, 45.0
+    rad = synth.bidisperse_radii(n, seed=8)
+    x = synth.relax_positions(rad, L, seed=8)
+    p = synth.default_params([L] * 3, dt=5e-4)
+    u = rng.standard_normal((n, 3))
+    u[:, 0] += x[:, 1]
+    u[::40] += 40.0 * rng.standard_normal((len(u[::40]), 3))
+
+    def make():
+        s = Simulation(p)
+        s.set_particles(x, rad, u)
+        return s
+
+    run_both(make, 40, 8, 1e-8, [L] * 3, calls=calls)
+
+
+def test_lists_that_do_not_fit():
+    """More neighbours than a list holds (small particles in one corner of the box, overlapping
+    many times over): every step is a full one."""
+    from paper_2108_01013_amd.dss import Simulation
+    rng = np.random.default_rng(3)
+    n = 800
+    x = rng.uniform(0.0, 1.0, (n, 3)) * [6.0, 6.0, 6.0]
+    p = synth.default_params([24.0] * 3, kn=1.0, kt=0.3, gamma_n=0.0, capacity=0)
+
+    def make():
+        s = Simulation(p, capacity=400)
+        s.set_particles(x, np.ones(n))
+        return s
+
+    run_both(make, 12, 4, 1e-10, p["L"])
+
+
+def test_batch_windows():
+    from paper_2108_01013_amd.dss import Batch
+    ws = [synth.bidisperse_box(int(n), phi, 50 + k) for k, (n, phi) in enumerate([(600, 0.4), (2100, 0.55), (900, 0.5)])]
+    ps = [dict(w.params, shear_rate=g) for w, g in zip(ws, (0.01, 1.0, 10.0))]
+    sims = []
+    for one in (False, True):
+        s = Batch(ps)
+        s.set_particles([w.x for w in ws], [w.rad * 1.0005 for w in ws])
+        if one:
+            for _ in range(45):
+                s.step(1)
+        else:
+            s.step(45, stress_every=9)
+        sims.append(s)
+    a, b = sims
+    assert rel(a.read_stress()[0], b.read_stress()[0]) < 1e-10
+    sa, sb = a.state(), b.state()
+    for k in ("u", "w", "F", "T"):
+        assert rel(sa[k], sb[k]) < 1e-10, k
+    for k in range(3):
+        q = a.box_slice(k)
+        assert near_x(sa["x"][q], sb["x"][q], ps[k]["L"]) < 1e-10
+        assert a.box_info(k)["n_pairs"] == b.box_info(k)["n_pairs"]
+    pa, xa = a.history()
+    pb, xb = b.history()
+    assert np.array_equal(pa, pb) and len(pb) > 200 and rel(xa, xb) < 1e-9
+
+
+def test_oracle_run(box):
+    """40 free steps against the oracle, from a large time index (an arbitrary offset)."""
+    from paper_2108_01013_amd.dss import Simulation
+    w, rad, u, om = box
+    n0 = 123457
+    s = Simulation(w.params)
+    s.set_particles(w.x, rad, u, om)
+    s.set_step(n0)
+    s.compute_forces()
+    st0 = s.state()
+    acc, accw = oracle.accelerations(w.params, rad, st0["F"], st0["T"])
+    st = oracle.State(st0["x"], st0["u"], st0["w"], acc, accw, rad.copy(), n0, oracle.History())
+    s.step(40, stress_every=10)
+    for _ in range(40):
+        st, F, T, S, npairs, _ = oracle.step(w.params, st, use_cells=True)
+    got = s.state()
+    assert rel(got["F"], F) < 1e-10 and rel(got["T"], T) < 1e-10
+    assert near_x(got["x"], st.x, w.params["L"]) < 1e-10
+    assert s.info()["n_pairs"] == npairs
+    assert rel(s.read_stress()[0], S) < 1e-10
+    hp, hx = s.history()
+    assert np.array_equal(hp, st.history.pairs)
+    s.close()
