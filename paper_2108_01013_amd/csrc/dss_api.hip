@@ -111,9 +111,11 @@ constexpr int kListWindow = 64;
 constexpr int kListWindowMin = 5;
 // Margin of the lists of a box beyond its cutoff, in smallest radii: what particles moving at a
 // few shear rates use up over a window of kListWindow steps, with a floor.
-inline double list_skin(double shear_rate, double dt)
+// `reach`: the box's cutoff radius in the same units, which the shear shortens by up to
+// reach x strain.
+inline double list_skin(double shear_rate, double dt, double reach)
 {
-    return std::min(0.1 + 10.0 * std::fabs(shear_rate) * dt * kListWindow, 0.6);
+    return std::min(0.1 + (10.0 + reach) * std::fabs(shear_rate) * dt * kListWindow, 0.6);
 }
 constexpr size_t kMaxOpenRuns = 4096;  // runs enqueued without a read of the clock
 }  // namespace
@@ -148,7 +150,7 @@ struct dss_handle {
     // HIP graphs of one time step, keyed by (current buffers, committed history buffers,
     // half-step velocities, stress summation), and of runs of steps (the same key for the
     // first step, the run length and which of its steps sum the stress)
-    hipGraphExec_t graph[16] = {};
+    hipGraphExec_t graph[32] = {};
     std::vector<std::pair<std::pair<uint64_t, uint64_t>, hipGraphExec_t>> run_graphs;
     bool graph_broken = false;
     hipStream_t stream = nullptr;
@@ -160,6 +162,7 @@ struct dss_handle {
     int64_t N = 0;
     bool loaded = false;
     bool vel_is_half = false;  // vel holds the half-step velocity of the last forces
+    bool own_total = false;    // the own records hold the whole force (after a window on pair lists)
     int cur = 0;               // particle buffers holding the current state
     int hh = 0;                // history buffers holding the committed history
     int64_t step = 0;          // host mirror of the time index
@@ -194,7 +197,7 @@ struct dss_handle {
         b.nb = ft_nb;
         b.x = ft_x;
         b.n = N;
-        b.nnb = P.sized ? 0 : 4;
+        b.nnb = P.sized || own_total ? 0 : 4;
         return b;
     }
     DevRun run_host{};
@@ -220,9 +223,10 @@ struct dss_handle {
     ListBlock *lblocks = nullptr;
     int2 *lent = nullptr;
     double *lxi = nullptr, *lxr = nullptr, *ldsum = nullptr, *lpartials = nullptr;
-    int *ln = nullptr, *lcross = nullptr;
+    int *ln = nullptr, *lcross = nullptr, *lof = nullptr;
+    double *lown = nullptr;
     ListRec *lrec[2] = {nullptr, nullptr};
-    int list_blocks = 0, list_own_cap = 0;
+    int list_blocks = 0, list_own_cap = 0, list_cap = 0;
     int list_window = kListWindow;   // longest window (0: off); halved when one stopped early
     int list_good = 0;               // calls since then without a stop
     // the runs of steps enqueued since the host last read the clock: the state each began from,
@@ -230,7 +234,7 @@ struct dss_handle {
     struct Run {
         int64_t step;
         int cur, hh;
-        bool vel_is_half;
+        bool vel_is_half, own_total;
     };
     std::vector<Run> runs;
     int64_t call_every = 0;
@@ -279,12 +283,13 @@ void free_lattice(dss_handle *h)
         if (p) (void)hipFree(p);
     };
     destroy_graphs(h);
-    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross);
+    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross); F(h->lof); F(h->lown);
     F(h->lrec[0]); F(h->lrec[1]);
     h->lblocks = nullptr;
     h->lent = nullptr;
     h->lxi = h->lxr = h->ldsum = h->lpartials = nullptr;
-    h->ln = h->lcross = nullptr;
+    h->ln = h->lcross = h->lof = nullptr;
+    h->lown = nullptr;
     h->lrec[0] = h->lrec[1] = nullptr;
     F(h->count); F(h->cell_start); F(h->tile_sum); F(h->cs_local); F(h->partials); F(h->d_boxes); F(h->d_row_box);
     h->cs_local = nullptr;
@@ -835,22 +840,56 @@ void commit_eval(dss_handle *h, bool advance)
 {
     h->cur = 1 - h->cur;
     h->vel_is_half = advance;
+    h->own_total = false;
     if (advance) {
         h->hh = 1 - h->hh;
         h->step += 1;
     }
 }
 
-// steps: time steps the clock advances by (EVAL_STEP; more than one when the steps before were
-// taken on pair lists, which leave the whole force in the own records).
-dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true, int steps = 1)
+// The counting sort of the current buffers into the others: kick and drift (advance = 1) or velocity
+// completion (half) of k_predict with the cell ids and ranks, the scan, the scatter (own: force
+// records that move with their particles into ft_own).  clock: time steps the clock advances by.
+void launch_sort(dss_handle *h, bool half, int advance, int clock, const double *own)
 {
     const int N = (int)h->N;
     const int grid = (N + kBlock - 1) / kBlock;
     const int c = h->cur, o = 1 - h->cur;
-    const int advance = mode == EVAL_STEP ? steps : 0;
-    ForceBufs B = h->fb();
-    if (advance > 1) B.nnb = 0;
+    {
+        TimedLaunch t(h, 0);
+        hipExtLaunchKernelGGL(k_predict, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->P, h->d_boxes,
+                              h->pa[c], h->vel[c], h->omg[c], h->fb(), half ? 1 : 0, advance, h->clk, h->cell, h->rank,
+                              h->count, h->img, h->boxes[0],
+                              h->P.record_pairs ? h->pair_count : (unsigned long long *)nullptr, h->tape_x,
+                              h->tape_u, h->tape_w, h->tape_zero);
+    }
+    if (h->scan_tiles > 0) {
+        TimedLaunch t(h, 1);
+        hipExtLaunchKernelGGL(k_scan<4>, dim3(h->scan_tiles), dim3(1024), 0, h->stream, t.e0, (hipEvent_t) nullptr,
+                              0, h->count, h->cell_start, h->clk, clock, h->tile_sum);
+        hipExtLaunchKernelGGL(k_scan_add, dim3(h->scan_tiles), dim3(1024), 0, h->stream, (hipEvent_t) nullptr, t.e1,
+                              0, h->cell_start, h->tile_sum, 4 * 1024, h->clk, clock);
+    } else {
+        // one workgroup per tile of 4096 cells, in parallel; k_scatter adds the tile offsets
+        // (scan_c4 is 1 .. 16, see setup_lattice)
+        TimedLaunch t(h, 1);
+        hipExtLaunchKernelGGL(k_scan<1>, dim3(h->scan_c4), dim3(1024), 0, h->stream, t.e0, t.e1, 0, h->count,
+                              h->cs_local, h->clk, clock, h->tile_sum);
+    }
+    TimedLaunch t(h, 2);
+    const bool tiles = h->scan_tiles == 0;
+    hipExtLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, N, h->cell, h->rank,
+                          tiles ? h->cs_local : h->cell_start, h->tile_sum, tiles ? h->scan_c4 : 0,
+                          h->ncell_total + 1, h->cell_start, h->clk, clock, h->pa[c], h->vel[c], h->omg[c],
+                          h->pa[o], h->vel[o], h->omg[o], h->prev, own, h->ft_own);
+}
+
+dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
+{
+    const int N = (int)h->N;
+    const int grid = (N + kBlock - 1) / kBlock;
+    const int c = h->cur, o = 1 - h->cur;
+    const int advance = mode == EVAL_STEP ? 1 : 0;
     if (mode == EVAL_INPLACE) {
         if (h->vel_is_half) {
             TimedLaunch t(h, 0);
@@ -863,43 +902,18 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true, int steps 
         if (s) return s;
         HIPTRY(hipGetLastError());
         h->vel_is_half = false;
+        h->own_total = false;
+        h->own_total = false;
         return DSS_OK;
     }
-    {
-        TimedLaunch t(h, 0);
-        hipExtLaunchKernelGGL(k_predict, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->P, h->d_boxes,
-                              h->pa[c], h->vel[c], h->omg[c], B, h->vel_is_half ? 1 : 0, advance, h->clk, h->cell, h->rank, h->count, h->img, h->boxes[0],
-                              h->P.record_pairs ? h->pair_count : (unsigned long long *)nullptr, h->tape_x,
-                              h->tape_u, h->tape_w, h->tape_zero);
-    }
-    if (h->scan_tiles > 0) {
-        TimedLaunch t(h, 1);
-        hipExtLaunchKernelGGL(k_scan<4>, dim3(h->scan_tiles), dim3(1024), 0, h->stream, t.e0, (hipEvent_t) nullptr,
-                              0, h->count, h->cell_start, h->clk, advance, h->tile_sum);
-        hipExtLaunchKernelGGL(k_scan_add, dim3(h->scan_tiles), dim3(1024), 0, h->stream, (hipEvent_t) nullptr, t.e1,
-                              0, h->cell_start, h->tile_sum, 4 * 1024, h->clk, advance);
-    } else {
-        // one workgroup per tile of 4096 cells, in parallel; k_scatter adds the tile offsets
-        TimedLaunch t(h, 1);
-        if (h->scan_c4 < 1 || h->scan_c4 > 16) return fail(h, DSS_ERR_BOX, "cell lattice too large for the scan");
-        hipExtLaunchKernelGGL(k_scan<1>, dim3(h->scan_c4), dim3(1024), 0, h->stream, t.e0, t.e1, 0, h->count,
-                              h->cs_local, h->clk, advance, h->tile_sum);
-    }
-    {
-        TimedLaunch t(h, 2);
-        const bool tiles = h->scan_tiles == 0;
-        hipExtLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, N, h->cell, h->rank,
-                              tiles ? h->cs_local : h->cell_start, h->tile_sum, tiles ? h->scan_c4 : 0,
-                              h->ncell_total + 1, h->cell_start, h->clk, advance, h->pa[c], h->vel[c], h->omg[c],
-                              h->pa[o], h->vel[o], h->omg[o], h->prev);
-        if (mode != EVAL_RESORT) h->listable = true;
-    }
+    launch_sort(h, h->vel_is_half, advance, advance, nullptr);
+    if (mode != EVAL_RESORT) h->listable = true;
     if (mode == EVAL_RESORT) {
         // the committed rows follow their particles; the pair kernels then find them in place
         const int hn = 1 - h->hh;
         hipLaunchKernelGGL(k_history_move, dim3(grid), dim3(kBlock), 0, h->stream, N, h->P.M, h->prev,
                            h->hkey[h->hh], h->hxi[h->hh], h->hxr[h->hh], h->hcnt[h->hh], h->hown[h->hh], h->hkey[hn],
-                           h->hxi[hn], h->hxr[hn], h->hcnt[hn], h->hown[hn]);
+                           h->hxi[hn], h->hxr[hn], h->hcnt[hn], h->hown[hn], h->clk);
         HIPTRY(hipGetLastError());
         h->hh = hn;
     }
@@ -907,7 +921,6 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true, int steps 
     if (s) return s;
     HIPTRY(hipGetLastError());
     commit_eval(h, advance != 0);
-    if (advance > 1) h->step += advance - 1;
     return DSS_OK;
 }
 
@@ -916,11 +929,12 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true, int steps 
 // a memset, which is not recorded into graphs).
 dss_status graph_step(dss_handle *h, bool finish)
 {
-    const int key = h->cur | (h->hh << 1) | ((h->vel_is_half ? 1 : 0) << 2) | ((finish ? 1 : 0) << 3);
+    const int key = h->cur | (h->hh << 1) | ((h->vel_is_half ? 1 : 0) << 2) | ((finish ? 1 : 0) << 3) |
+                    ((h->own_total ? 1 : 0) << 4);
     if (!h->graph[key]) {
         hipGraph_t g = nullptr;
         const int cur = h->cur, hh = h->hh;
-        const bool vih = h->vel_is_half;
+        const bool vih = h->vel_is_half, total = h->own_total;
         const int64_t step = h->step;
         HIPTRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
         dss_status s = evaluate(h, EVAL_STEP, finish);
@@ -929,6 +943,7 @@ dss_status graph_step(dss_handle *h, bool finish)
         h->cur = cur;
         h->hh = hh;
         h->vel_is_half = vih;
+        h->own_total = total;
         h->step = step;
         if (s) {
             if (g) (void)hipGraphDestroy(g);
@@ -947,18 +962,35 @@ dss_status graph_step(dss_handle *h, bool finish)
     return DSS_OK;
 }
 
-// Whether the time steps of the handle can go as windows on pair lists: the plain row-tile search
-// (not the size-class stencils, whose pairs are few against their searches' kernels, nor the pass
-// of the electro-chemical far pairs), no recording of pairs, no wavy shear.
+// The host's bookkeeping of a run of n steps: the particles are in the other buffers after every
+// full step, and so is the history; a window on pair lists sorts once, and its rows return to
+// where they were.
+void commit_run(dss_handle *h, int n, bool lists)
+{
+    if (!lists) {
+        for (int k = 0; k < n; ++k) commit_eval(h, true);
+        return;
+    }
+    h->cur = 1 - h->cur;
+    h->vel_is_half = true;
+    h->own_total = true;
+    h->step += n;
+}
+
+// Whether the time steps of the handle can go as windows on pair lists: the row tiles or the
+// size-class stencils without the electro-chemical ranges, no recording of pairs, no wavy shear.
 bool lists_on(const dss_handle *h)
 {
-    return h->list_window >= kListWindowMin && h->tune.tiled && !h->P.sized && !h->P.ec && !h->P.record_pairs &&
+    return h->list_window >= kListWindowMin && (h->tune.tiled || h->P.sized) && !h->P.ec && !h->P.record_pairs &&
            h->P.wave_amp == 0.0;
 }
 
 // Blocks of the pair lists and the memory of a window, on the handle's first window.  A block
 // holds about as many particles as fill the workgroup slots once (1 / 64 of them kept free, as
 // for the cell rows), at least 16 and at most kListOwnMax; the blocks of a box are of one size.
+// With size-class stencils the slots of a class are one range: its blocks hold fewer particles the
+// larger these are, by the list entries allotted to one (a quarter of the paper's estimate of the
+// particles around it beyond kListPerOwn).
 dss_status setup_lists(dss_handle *h)
 {
     if (h->lrec[1]) return DSS_OK;  // allocated last
@@ -968,18 +1000,45 @@ dss_status setup_lists(dss_handle *h)
     std::vector<ListBlock> blocks;
     int64_t ent = 0;
     h->list_own_cap = 0;
+    h->list_cap = 0;
+    auto add = [&](int start, int n, int box, int cls, int most, int per_own) {
+        const int nb = (n + most - 1) / most;
+        for (int k = 0; k < nb; ++k) {
+            const int lo = (int)((int64_t)n * k / nb), hi = (int)((int64_t)n * (k + 1) / nb);
+            const int cap = per_own * (hi - lo) + kListSpare;
+            blocks.push_back({start + lo, hi - lo, box, cls, (int)std::min<int64_t>(ent, 0x7fffffff), cap});
+            ent += cap;
+            h->list_own_cap = std::max(h->list_own_cap, hi - lo);
+            h->list_cap = std::max(h->list_cap, cap);
+        }
+    };
     for (int b = 0; b < h->nbox; ++b) {
         BoxParams &G = h->boxes[b];
-        const int nb = (G.n_part + own - 1) / own;
-        G.skin = list_skin(G.gd, h->prm.dt) * h->a_min;
+        G.skin = list_skin(G.gd, h->prm.dt, h->prm.cutoff_factor * G.amax / h->a_min) * h->a_min;
         G.blk_off = (int)blocks.size();
-        G.blk_n = nb;
-        for (int k = 0; k < nb; ++k) {
-            const int lo = (int)((int64_t)G.n_part * k / nb), hi = (int)((int64_t)G.n_part * (k + 1) / nb);
-            blocks.push_back({G.part_off + lo, hi - lo, b, (int)ent});
-            ent += (int64_t)kListPerOwn * (hi - lo) + kListSpare;
-            h->list_own_cap = std::max(h->list_own_cap, hi - lo);
+        if (h->P.sized) {
+            std::vector<int> count(h->P.ncls, 0);
+            std::vector<double> top(h->P.ncls, 0.0);
+            for (double a : h->rad_host) {
+                const int k = std::max(0, std::min((int)std::floor(a * h->P.cls_mul + h->P.cls_add), h->P.ncls - 1));
+                ++count[k];
+                top[k] = std::max(top[k], a);
+            }
+            int start = 0;
+            for (int k = 0; k < h->P.ncls; ++k) {
+                const int per_own = kListPerOwn + paper_capacity(top[k], h->a_min) / 4;
+                const int most = std::max(1, std::min(own, (kListCapMax - kListSpare) / per_own));
+                if (per_own + kListSpare > kListCapMax) {
+                    h->list_window = 0;  // one particle's list would not fit a workgroup
+                    return DSS_OK;
+                }
+                if (count[k]) add(start, count[k], b, k, most, per_own);
+                start += count[k];
+            }
+        } else {
+            add(G.part_off, G.n_part, b, 0, own, kListPerOwn);
         }
+        G.blk_n = (int)blocks.size() - G.blk_off;
     }
     if (ent > (int64_t)0x7fffffff) {
         h->list_window = 0;  // lists of this size are not indexed
@@ -993,13 +1052,23 @@ dss_status setup_lists(dss_handle *h)
     HIPTRY(dalloc(&h->ln, blocks.size()));
     HIPTRY(dalloc(&h->ldsum, h->N));
     HIPTRY(dalloc(&h->lcross, h->N));
+    HIPTRY(dalloc(&h->lown, 6 * h->N));
     HIPTRY(dalloc(&h->lpartials, 12 * blocks.size()));
     HIPTRY(dalloc(&h->lrec[0], h->N));
     HIPTRY(hipMemcpyAsync(h->lblocks, blocks.data(), blocks.size() * sizeof(ListBlock), hipMemcpyHostToDevice,
                           h->stream));
     HIPTRY(hipMemcpyAsync(h->d_boxes, h->boxes.data(), h->boxes.size() * sizeof(BoxParams), hipMemcpyHostToDevice,
                           h->stream));
-    HIPTRY(hipStreamSynchronize(h->stream));  // `blocks` goes out of scope
+    HIPTRY(hipMemsetAsync(h->ln, 0, blocks.size() * sizeof(int), h->stream));
+    std::vector<int> of;
+    if (h->P.sized) {
+        of.resize(h->N);
+        for (size_t k = 0; k < blocks.size(); ++k)
+            std::fill_n(of.begin() + blocks[k].start, blocks[k].n, (int)k);
+        HIPTRY(dalloc(&h->lof, h->N));
+        HIPTRY(hipMemcpyAsync(h->lof, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice, h->stream));
+    }
+    HIPTRY(hipStreamSynchronize(h->stream));  // the host tables go out of scope
     HIPTRY(dalloc(&h->lrec[1], h->N));
     return DSS_OK;
 }
@@ -1025,6 +1094,7 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
     L.xi = h->lxi;
     L.xr = h->lxr;
     L.n = h->ln;
+    L.of = h->lof;
     L.dsum = h->ldsum;
     L.cross = h->lcross;
     L.own_cap = h->list_own_cap;
@@ -1033,6 +1103,7 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
     C.vel = h->vel[h->cur];
     C.omg = h->omg[h->cur];
     C.B = h->fb();
+    C.own = h->lown;
     C.img = h->img;
     HistView H{};
     H.key_old = h->hkey[h->hh];
@@ -1047,12 +1118,16 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
     const bool roll = h->P.kr > 0.0, mixed = h->prm.precision == DSS_MIXED;
     {
         TimedLaunch t(h, 8);
+        if (h->P.sized)
+            hipExtLaunchKernelGGL(k_list_search, dim3(h->list_blocks), dim3(kBeginBlock), 0, h->stream, t.e0,
+                                  (hipEvent_t) nullptr, 0, h->P, h->d_boxes, h->cell_start, h->pa[h->cur], L, h->clk);
         hipExtLaunchKernelGGL(roll ? k_list_begin<true> : k_list_begin<false>, dim3(h->list_blocks), dim3(kBeginBlock),
-                              (size_t)(kListPerOwn * h->list_own_cap + kListSpare) * sizeof(int2), h->stream, t.e0, t.e1, 0, h->P, h->d_boxes, h->cell_start, C, H, L,
-                              h->lrec[0], h->vel_is_half ? 1 : 0, h->clk);
+                              (size_t)h->list_cap * sizeof(int2), h->stream, h->P.sized ? (hipEvent_t) nullptr : t.e0,
+                              t.e1, 0, h->P, h->d_boxes, h->cell_start, C, H, L, h->lrec[0], h->vel_is_half ? 1 : 0,
+                              h->clk);
     }
-    for (int k = 1; k < n; ++k) {
-        const bool sum = (finish >> (k - 1)) & 1u, last = k == n - 1;
+    for (int k = 1; k <= n; ++k) {
+        const bool sum = (finish >> (k - 1)) & 1u, last = k == n;
         if (mixed)
             roll ? launch_list<float, true>(h, sum, last, L, k, C, H) : launch_list<float, false>(h, sum, last, L, k, C, H);
         else
@@ -1063,10 +1138,14 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
                                   h->lpartials, h->list_blocks, h->clk, h->run, 1, k);
         }
     }
+    // sort the last state; its rows, committed to the other history buffers, move back with it
+    launch_sort(h, false, 0, n, h->lown);
+    hipLaunchKernelGGL(k_history_move, dim3((unsigned)((h->N + kBlock - 1) / kBlock)), dim3(kBlock), 0, h->stream,
+                       (int)h->N, h->P.M, h->prev, H.key_new, H.xi_new, H.xr_new, H.cnt_new, H.own_new,
+                       h->hkey[h->hh], h->hxi[h->hh], h->hxr[h->hh], h->hcnt[h->hh], h->hown[h->hh], h->clk);
     HIPTRY(hipGetLastError());
-    h->hh = 1 - h->hh;  // the rows of the last list step
-    h->vel_is_half = true;
-    return evaluate(h, EVAL_STEP, (finish >> (n - 1)) & 1u, n);
+    commit_run(h, n, true);
+    return DSS_OK;
 }
 
 // n consecutive time steps through one HIP graph, on pair lists (lists) or as n full steps
@@ -1080,7 +1159,8 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
 {
     const std::pair<uint64_t, uint64_t> key((uint64_t)h->cur | ((uint64_t)h->hh << 1) |
                                                 ((uint64_t)(h->vel_is_half ? 1 : 0) << 2) |
-                                                ((uint64_t)(lists ? 1 : 0) << 3) | ((uint64_t)n << 4),
+                                                ((uint64_t)(lists ? 1 : 0) << 3) |
+                                                ((uint64_t)(h->own_total ? 1 : 0) << 4) | ((uint64_t)n << 5),
                                             finish);
     for (auto &g : h->run_graphs)
         if (g.first == key) {
@@ -1094,7 +1174,7 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
         h->run_graphs.clear();
     }
     const int cur = h->cur, hh = h->hh;
-    const bool vih = h->vel_is_half;
+    const bool vih = h->vel_is_half, total = h->own_total;
     const int64_t step = h->step;
     hipGraph_t g = nullptr;
     HIPTRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
@@ -1107,6 +1187,7 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
     h->cur = cur;
     h->hh = hh;
     h->vel_is_half = vih;
+    h->own_total = total;
     h->step = step;
     if (s) {
         if (g) (void)hipGraphDestroy(g);
@@ -1122,20 +1203,6 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
     HIPTRY(hipGraphUpload(ge, h->stream));
     *out = ge;
     return DSS_OK;
-}
-
-// The host's bookkeeping of a run of n steps: the particles are in the other buffers after every
-// full step, and so is the history; a window on pair lists ends with one full step, and its last
-// list step commits the history too.
-void commit_run(dss_handle *h, int n, bool lists)
-{
-    if (!lists) {
-        for (int k = 0; k < n; ++k) commit_eval(h, true);
-        return;
-    }
-    h->cur = 1 - h->cur;
-    h->vel_is_half = true;
-    h->step += n;
 }
 
 dss_status graph_run(dss_handle *h, int n, bool lists, uint64_t finish)
@@ -1210,7 +1277,7 @@ dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
             n = 1;
         }
         if (!graphs && !lists) n = 1;
-        if (lists || !h->runs.empty()) h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half});
+        if (lists || !h->runs.empty()) h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half, h->own_total});
         if (graphs && n >= 2)
             s = graph_run(h, n, lists, R.mask_at(k, n));
         else if (lists)
@@ -1250,11 +1317,13 @@ dss_status settle(dss_handle *h, DevClock *out)
         h->cur = at->cur;
         h->hh = at->hh;
         h->vel_is_half = at->vel_is_half;
+        h->own_total = at->own_total;
         h->runs.clear();
         h->list_good = 0;
         h->list_window = (c.err & kErrListFull) || h->list_window < 2 * kListWindowMin ? 0 : h->list_window / 2;
         c.err &= ~kErrListMask;
         HIPTRY(hipMemcpyAsync(h->clk, &c, sizeof(c), hipMemcpyHostToDevice, h->stream));
+        HIPTRY(hipMemsetAsync(h->ln, 0, h->list_blocks * sizeof(int), h->stream));
         HIPTRY(hipStreamSynchronize(h->stream));
         dss_status s = enqueue_steps(h, target - h->step, h->call_every);
         if (s) return s;
@@ -1518,6 +1587,7 @@ dss_status dss_set_particles_batch(dss_handle *h, const int64_t *n_per_box, cons
     h->hh = 0;
     h->step = 0;
     h->vel_is_half = false;
+    h->own_total = false;
     h->tune_pending = false;
     const int grid = (int)((N + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_load, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, dx, dr, du, dw, dpb, h->d_boxes,
@@ -1677,7 +1747,7 @@ dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_ever
     if (lists_on(h) && n_steps >= kListWindowMin) s = setup_lists(h);
     if (s) return s;
     const int cur = h->cur, hh = h->hh;
-    const bool vih = h->vel_is_half;
+    const bool vih = h->vel_is_half, total = h->own_total;
     const int64_t step = h->step;
     const StepRuns R(n_steps, stress_every, h->step, lists_on(h) ? h->list_window : 0);
     bool listable = h->listable;
@@ -1699,6 +1769,7 @@ dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_ever
     h->cur = cur;
     h->hh = hh;
     h->vel_is_half = vih;
+    h->own_total = total;
     h->step = step;
     return s;
 }
@@ -1974,8 +2045,19 @@ struct Snapshot {
     }
 };
 
+// The partner records as zeros after a window on pair lists (the own records hold the whole force):
+// for snapshots, which carry every record.
+dss_status whole_records(dss_handle *h)
+{
+    if (h->own_total) HIPTRY(hipMemsetAsync(h->ft_nb, 0, 24 * h->N * sizeof(double), h->stream));
+    h->own_total = false;
+    return DSS_OK;
+}
+
 dss_status snap_save(dss_handle *h, Snapshot &s)
 {
+    dss_status st0 = whole_records(h);
+    if (st0) return st0;
     const int64_t N = h->N, M = h->P.M;
     if (!s.img) {  // allocated last: a snapshot without it is released and allocated whole
         s.release();
@@ -2043,6 +2125,7 @@ dss_status snap_restore(dss_handle *h, const Snapshot &s)
     h->hh = s.hh;
     h->step = s.step;
     h->vel_is_half = s.vel_is_half;
+    h->own_total = false;
     return DSS_OK;
 }
 
@@ -2493,6 +2576,8 @@ dss_status dss_save_state(dss_handle *h, void *blob, size_t *bytes)
         *bytes = need;
         return fail(h, DSS_ERR_CAPACITY, "state buffer too small");
     }
+    s = whole_records(h);
+    if (s) return s;
     StateHeader hd{};
     std::memcpy(hd.magic, "DSSSTATE", 8);
     hd.version = kStateVersion;
@@ -2543,6 +2628,7 @@ dss_status dss_load_state(dss_handle *h, const void *blob, size_t bytes)
     h->hh = 0;
     h->step = hd.step;
     h->vel_is_half = hd.vel_is_half != 0;
+    h->own_total = false;
     h->listable = false;  // the snapshot does not say; the next full step settles it
     return DSS_OK;
 }

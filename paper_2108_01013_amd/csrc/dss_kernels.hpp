@@ -246,7 +246,8 @@ struct ForceBufs {
     double *nb;      // 4 x N x 6
     double *x;       // N x 6, atomic accumulation, cleared by k_predict after use
     long long n;     // N (stride of nb)
-    int nnb;         // partner records in use (4 on the row tiles, 0 with size-class stencils)
+    int nnb;         // partner records in use (4 on the row tiles, 0 with size-class stencils and after
+                     //   a window on pair lists)
 };
 
 __device__ __forceinline__ void load_ft(const double *__restrict__ rec, double f[6])
@@ -457,7 +458,8 @@ __device__ __forceinline__ double advance_particle(const DevParams &P, const Box
 // ----------------------------------------------------------------------------------
 // k_predict: velocity-Verlet drift + half kick to time index clk->step + advance (advance >= 1;
 // the steps since the clock's index were taken on pair lists) or velocity completion only
-// (advance = 0), Lees-Edwards wrap, cell id and histogram rank.
+// (advance = 0), Lees-Edwards wrap, cell id and histogram rank.  advance = 0 with vel_is_half = 0 is
+// the cell id and rank alone (the sort at the end of a window: velocities as they are).
 //   vel_is_half = 1: vel holds the half-step velocity u^{n-1/2} of the forces, and
 //   u^n = u^{n-1/2} + dt/2 F^n / m completes the previous step.
 // The atomic force record is read, and cleared for the next evaluation, only when the last
@@ -499,7 +501,8 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
     // the box of the particle: the table entry of a batch, else the kernel argument (no
     // load that waits for the particle record)
     auto body = [&](const BoxParams &G) {
-    double f[6];
+    double f[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (advance || vel_is_half) {
     total_ft(B, p, f, false);
     if (c0.deferred || P.ec_split) {
         double e[6];
@@ -508,6 +511,7 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
         for (int k = 0; k < 6; ++k) f[k] += e[k];
         const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         store_ft(B.x + 6LL * p, z);
+    }
     }
     if (advance) {
         int cross;
@@ -525,8 +529,10 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
         W.y = W.y + 0.5 * dt * (f[4] / I);
         W.z = W.z + 0.5 * dt * (f[5] / I);
     }
-    vel[p] = V;
-    omg[p] = W;
+    if (advance || vel_is_half) {
+        vel[p] = V;
+        omg[p] = W;
+    }
     int cx = cell_coord(X.x, G.cw[0], G.nc[0]);
     int cy = cell_coord(X.y, G.cw[1], G.nc[1]);
     int cz = cell_coord(X.z, G.cw[2], G.nc[2]);
@@ -601,7 +607,8 @@ __global__ void __launch_bounds__(kBlock) k_scatter(int N, const int *__restrict
                                                      const double4 *__restrict__ vel_in,
                                                      const double4 *__restrict__ omg_in, double4 *__restrict__ pa_out,
                                                      double4 *__restrict__ vel_out, double4 *__restrict__ omg_out,
-                                                     int *__restrict__ prev)
+                                                     int *__restrict__ prev, const double *__restrict__ own_in,
+                                                     double *__restrict__ own_out)
 {
     __shared__ int off[16];
     const int t = threadIdx.x;
@@ -630,6 +637,11 @@ __global__ void __launch_bounds__(kBlock) k_scatter(int N, const int *__restrict
     vel_out[dst] = vel_in[p];
     omg_out[dst] = omg_in[p];
     prev[dst] = p;
+    if (own_in) {  // the force record of the sorted state moves with its particle
+        double f[6];
+        load_ft(own_in + 6LL * p, f);
+        store_ft(own_out + 6LL * dst, f);
+    }
 }
 
 // ----------------------------------------------------------------------------------
@@ -668,12 +680,19 @@ __device__ __forceinline__ float sqrt_r(float x) { return __builtin_sqrtf(x); }
 // differences (which cancel the large ambient-flow values) are formed in FP64 and rounded
 // once; the unit vector, coefficients, log/exp, contact model and stresslet are FP32; the
 // results are accumulated in FP64 by the caller.
-template <typename Real, bool Roll = false, bool Wave = false>
+// List: the pair lists' instantiation.  In mixed precision it names the fused operations that the
+// compiler takes in the kernels of a full step (and would take otherwise here), so that a pair has
+// the same force to the bit on lists and in a full step: v.n and t.n begin with the rounded product
+// of the x components; 2 a_i^2 + a_i a_j rounds a_i a_j first on the row tiles and the lane path of
+// the size-class stencils, and the sum only (`kept`) on their wavefront path, which keeps 2 a_i^2
+// outside its loop.
+template <typename Real, bool Roll = false, bool Wave = false, bool List = false>
 __device__ __forceinline__ void pair_physics(const DevParams &P, double gd_d, double wk, double dx_d, double dy_d,
                                              double dz_d, double dist,
                                              double ai_d, double aj_d, double yi, double yj, const double4 &Vi,
                                              const double4 &Vj, const double4 &Wi, const double4 &Wj,
-                                             const double xo[3], const double xro[3], double *S, PairOut &o)
+                                             const double xo[3], const double xro[3], double *S, PairOut &o,
+                                             bool kept = false)
 {
     // ---------------- FP64 in both modes: gap, lubrication argument, velocity differences
     const double h_d = dist - ai_d - aj_d;
@@ -731,7 +750,12 @@ __device__ __forceinline__ void pair_physics(const DevParams &P, double gd_d, do
     const Real is = rcp_r(s);
     const Real is2 = is * is, is3 = is2 * is;
     const Real XA = K * (Real)2.0 * ai2 * aj2 * is3 * invg;
-    const Real YA = K * (Real)(4.0 / 15.0) * ai * aj * ((Real)2.0 * ai2 + ai * aj + (Real)2.0 * aj2) * is3 * lg;
+    Real sq;
+    if constexpr (List && std::is_same<Real, float>::value)
+        sq = fmaf(2.0f, aj2, kept ? fmaf(ai, aj, 2.0f * ai2) : fmaf(2.0f, ai2, ai * aj));
+    else
+        sq = (Real)2.0 * ai2 + ai * aj + (Real)2.0 * aj2;
+    const Real YA = K * (Real)(4.0 / 15.0) * ai * aj * sq * is3 * lg;
     const Real YBi = -K * (Real)(2.0 / 15.0) * ai2 * aj * ((Real)4.0 * ai + aj) * is2 * lg;
     const Real YBj = K * (Real)(2.0 / 15.0) * ai * aj2 * (ai + (Real)4.0 * aj) * is2 * lg;
     const Real YCii = K * (Real)(8.0 / 15.0) * ai2 * ai * aj * is * lg;
@@ -741,7 +765,13 @@ __device__ __forceinline__ void pair_physics(const DevParams &P, double gd_d, do
     const Real vx = dux + s * (Real)0.5 * gbar * ny;
     const Real vy = duy + s * (Real)0.5 * gbar * nx;
     const Real vz = duz;
-    const Real vn = vx * nx + vy * ny + vz * nz;
+    Real vn;
+    if constexpr (List && std::is_same<Real, float>::value) {
+#pragma clang fp contract(off)
+        vn = vz * nz + fmaf(vy, ny, vx * nx);
+    } else {
+        vn = vx * nx + vy * ny + vz * nz;
+    }
     // n x w'
     const Real cix = ny * wiz - nz * wiy, ciy = nz * wix - nx * wiz, ciz = nx * wiy - ny * wix;
     const Real cjx = ny * wjz - nz * wjy, cjy = nz * wjx - nx * wjz, cjz = nx * wjy - ny * wjx;
@@ -822,7 +852,13 @@ __device__ __forceinline__ void pair_physics(const DevParams &P, double gd_d, do
         // (a_i w_i + a_j w_j) x n
         const Real qx = sy * nz - sz * ny, qy = sz * nx - sx * nz, qz = sx * ny - sy * nx;
         const Real tx = Dx - qx, ty = Dy - qy, tz = Dz - qz;
-        const Real tn = tx * nx + ty * ny + tz * nz;
+        Real tn;
+        if constexpr (List && std::is_same<Real, float>::value) {
+#pragma clang fp contract(off)
+            tn = fmaf(tz, nz, fmaf(ty, ny, tx * nx));
+        } else {
+            tn = tx * nx + ty * ny + tz * nz;
+        }
         const Real dtR = (Real)P.dt;
         Real xx = (Real)xo[0] + (tx - tn * nx) * dtR;
         Real xy = (Real)xo[1] + (ty - tn * ny) * dtR;
@@ -2475,8 +2511,10 @@ __global__ void __launch_bounds__(kBlock) k_history_move(int N, int M, const int
                                                           const int *__restrict__ cnt_old,
                                                           const int *__restrict__ own_old, int *__restrict__ key_new,
                                                           double *__restrict__ xi_new, double *__restrict__ xr_new,
-                                                          int *__restrict__ cnt_new, int *__restrict__ own_new)
+                                                          int *__restrict__ cnt_new, int *__restrict__ own_new,
+                                                          const DevClock *__restrict__ clk)
 {
+    if (clk->err & kErrListMask) return;
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N) return;
     const int p = prev[q];

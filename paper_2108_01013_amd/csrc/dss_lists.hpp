@@ -4,11 +4,15 @@
 // radius per step.  dss_step therefore takes runs of steps as windows.  A window of n steps from
 // a committed state is
 //   k_list_begin          the pairs inside the cutoff plus a margin (skin) at the window's first
-//                         state, with their stored stretches, and the first kick and drift;
-//   k_list x (n - 1)      one launch per step: the pair physics over the lists, the Stokes terms,
-//                         the finishing kick and the next kick, drift and wrap;
-//   a full step           the counting sort, search and pair kernels of dss_kernels.hpp, which leave
-//                         the sorted order, cells, history rows and force records of an ordinary step.
+//                         state, with their stored stretches, and the first kick and drift (with
+//                         size-class stencils k_list_search finds the pairs first);
+//   k_list x n            one launch per step: the pair physics over the lists, the Stokes terms,
+//                         the finishing kick and the next kick, drift and wrap; the last one commits
+//                         the state, the force records and the sorted history rows instead;
+//   a counting sort       at the last state (k_predict's cell ids alone, k_scan, k_scatter, and
+//                         k_history_move for the rows), which leaves the order, cells, rows and
+//                         records of an ordinary step.  (A full step at the end instead cost 61 us
+//                         against 47 at N = 100k, and 2.3 ms against 0.3 at N = 500k, size ratio 10.)
 // The listed-pair test of every step is the FP64 one at the step's own positions: the list only
 // holds more candidates than the test accepts, so the pair set, forces and history are those of a
 // search at every step (up to the order of sums).
@@ -49,17 +53,19 @@ constexpr int kBeginLanes = 8;        // lanes that take a run of candidates tog
 constexpr int kBeginRuns = 2;         // runs of a lane in flight
 constexpr int kBeginRows = 1024;      // (particle, cell row) pairs of a batch of its search
 constexpr int kListOwnMax = 128;      // particles of a block
-constexpr int kListPerOwn = 24;       // list entries allotted per particle of a block
+constexpr int kListPerOwn = 24;       // list entries allotted per particle (more for a large one)
 constexpr int kListSpare = 64;        // and per block
+constexpr int kListCapMax = kListPerOwn * kListOwnMax + kListSpare;
 
 // One particle in a window: (x, y, z, a), (u, box), (w, id); a neighbour gather is one 96-byte record.
 struct ListRec {
     double4 p, v, w;
 };
 
-// A block of consecutive slots of one box; its list starts at entry e0.
+// A block of consecutive slots of one box (and of one size class); its list has room for cap
+// entries from e0.
 struct ListBlock {
-    int start, n, box, e0;
+    int start, n, box, cls, e0, cap;
 };
 
 // A list entry.  x: partner slot, kEntSwap when the partner is the pair's first member (the pair is
@@ -78,6 +84,7 @@ struct ListView {
     int2 *ent;
     double *xi, *xr;      // 3 per entry; xr only with rolling resistance
     int *n;               // entries of each block
+    const int *of;        // block of a slot (with size-class stencils)
     double *dsum;         // displacement sum D of the bound above, by slot
     int *cross;           // y-face crossings of the window by slot
     int own_cap;          // largest block
@@ -86,7 +93,8 @@ struct ListView {
 // The committed state of a handle: read by k_list_begin, written by the last list step.
 struct CommittedView {
     double4 *pa, *vel, *omg;
-    ForceBufs B;
+    ForceBufs B;    // of the evaluation before the window
+    double *own;    // the force records of the last list step (before the sort)
     int *img;
 };
 
@@ -108,11 +116,13 @@ __device__ __forceinline__ int cell_diff(int a, int b, int n)
     return 2 * d == n || 2 * d == -n ? 0 : d;
 }
 
-// Whether j is in the forward half shell of i (then i is the pair's first member): by the cell
-// offsets along z, y, x, then by slot.  Antisymmetric, so both blocks of a pair agree.
-__device__ __forceinline__ bool list_forward(const BoxParams &G, const double icw[3], const double4 &Xi,
-                                             const double4 &Xj, int i, int j)
+// Whether i is the pair's first member, as in the pair kernels: with size-class stencils the larger
+// one (of equal radii the later slot), else the one with j in its forward half shell (by the cell
+// offsets along z, y, x, then by slot).  Antisymmetric, so both blocks of a pair agree.
+__device__ __forceinline__ bool list_forward(const DevParams &P, const BoxParams &G, const double icw[3],
+                                             const double4 &Xi, const double4 &Xj, int i, int j)
 {
+    if (P.sized) return Xj.w < Xi.w || (Xj.w == Xi.w && j < i);
     const int dz = cell_diff((int)(Xi.z * icw[2]), (int)(Xj.z * icw[2]), G.nc[2]);
     if (dz) return dz > 0;
     const int dy = cell_diff((int)(Xi.y * icw[1]), (int)(Xj.y * icw[1]), G.nc[1]);
@@ -143,25 +153,28 @@ __device__ __forceinline__ ListRows list_rows(const BoxParams &G, double reach)
 
 // A run of candidates of one particle of the block: slots jb .. jb + n, all with the same image
 // (cross: y-face crossing, w: box lengths along x, z: box lengths along z; without `whole`).
+// A run of kTaskMax slots or more is not searched: the lists are given up.
 struct ListTask {
     int jb, code;
 };
+constexpr int kTaskMax = 0xffff;
 __device__ __forceinline__ ListTask list_task(int jb, int n, int il, int cross, int w, int z)
 {
-    return {jb, n | (il << 16) | ((cross + 1) << 24) | ((z + 1) << 26) | ((w + 4) << 28)};
+    return {jb, min(n, kTaskMax) | (il << 16) | ((cross + 1) << 24) | ((z + 1) << 26) | ((w + 4) << 28)};
 }
 
 // Candidates of row (qy, qz) of the rows R around particle il at Xi: at most two runs.  A row
 // farther than reach in y-z has none; a row reached across a y face is searched around the x
-// shifted by the Lees-Edwards offset.  icw: 1 / cell widths.
+// shifted by the Lees-Edwards offset.  icw: 1 / cell widths; cell0: first cell of the lattice (of a
+// size class).
 template <typename Push>
 __device__ __forceinline__ void list_row(const BoxParams &G, const double icw[3], double delta,
-                                         const int *__restrict__ cell_start, const ListRows &R, int il,
-                                         const double4 &Xi, double reach, int qy, int qz, Push &&push)
+                                         const int *__restrict__ cell_start, const ListRows &R, int cell0,
+                                         int il, const double4 &Xi, double reach, int qy, int qz, Push &&push)
 {
     const int nxc = G.nc[0], nyc = G.nc[1], nzc = G.nc[2];
     if (R.whole) {
-        const int base = G.cell_off + (qz * nyc + qy) * nxc;
+        const int base = cell0 + (qz * nyc + qy) * nxc;
         const int jb = cell_start[base], n = cell_start[base + nxc] - jb;
         if (n > 0) push(list_task(jb, n, il, 0, 0, 0));
         return;
@@ -181,7 +194,7 @@ __device__ __forceinline__ void list_row(const BoxParams &G, const double icw[3]
     int span = (int)floor((xs + hw) * icw[0]) - xl + 1, w = 0;
     for (; xl < 0; xl += nxc) --w;
     for (; xl >= nxc; xl -= nxc) ++w;
-    const int base = G.cell_off + ((zu - cz * nzc) * nyc + yu - cross * nyc) * nxc;
+    const int base = cell0 + ((zu - cz * nzc) * nyc + yu - cross * nyc) * nxc;
     const int len = min(span, nxc - xl);
     const int jb = cell_start[base + xl], n = cell_start[base + xl + len] - jb;
     if (n > 0) push(list_task(jb, n, il, cross, w, cz));
@@ -191,56 +204,44 @@ __device__ __forceinline__ void list_row(const BoxParams &G, const double icw[3]
     }
 }
 
-// ----------------------------------------------------------------------------------
-// k_list_begin: the lists of one block at the committed state, and the first kick and drift of
-// the block's particles into the window's records.  In batches of kBeginRows (particle, cell row)
-// pairs the lanes write the candidate runs of their rows into LDS, then take the runs (so every
-// lane has one, although most rows are out of reach) and push the candidates that pass into a
-// queue; then all lanes take the queued ones: the pair's orientation and class (contacts, listed
-// pairs, candidates of the margin, stored in this order, so that a wavefront of k_list holds one
-// kind), a pair inside the block from its first member only, and the stored stretch from the
-// committed history rows.  (One particle per eight lanes, each walking its share of the rows:
-// 73 us at N = 100k, 53 us so.)
-// ----------------------------------------------------------------------------------
-template <bool Roll>
-__global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const BoxParams *__restrict__ boxes,
-                                                             const int *__restrict__ cell_start, CommittedView C,
-                                                             HistView H, ListView L, ListRec *__restrict__ out,
-                                                             int vel_is_half, DevClock *__restrict__ clk)
+// The candidates of a block's particles among the cells from cell0 on (the box's, or a size
+// class's), partners of radius up to amax: push(il, j, Xi, Xj) for every one inside its cutoff plus
+// the margin.  In batches of kBeginRows (particle, cell row) pairs the lanes write the candidate
+// runs of their rows into LDS, then take the runs (so every lane has one, although most rows are
+// out of reach): kBeginLanes lanes one run together (their loads are contiguous), kBeginRuns at a
+// time (their loads are in flight together).  (One particle per eight lanes, each walking its
+// share of the rows, took 73 us at N = 100k, k_list_begin takes 53 so.)
+struct ListTasks {
+    ListTask task[2 * kBeginRows];
+    int n;
+};
+
+template <typename Push>
+__device__ __forceinline__ void list_collect(const DevParams &P, const BoxParams &G, double delta,
+                                             const int *__restrict__ cell_start, const double4 *__restrict__ pa,
+                                             const ListBlock &K, double own_amax, double amax, int cell0, ListTasks &T,
+                                             DevClock *__restrict__ clk, Push &&push)
 {
-    extern __shared__ int2 q_lds[];
-    __shared__ ListTask tasks[2 * kBeginRows];
-    __shared__ int qn, tn, cnt[kClasses + 1], pos[kClasses];
     const int t = threadIdx.x;
-    const int blk = xcd_row(blockIdx.x, gridDim.x);
-    const ListBlock K = L.blocks[blk];
-    const DevClock c0 = *clk;
-    if (c0.err & kErrListMask) return;
-    const BoxParams G = boxes[K.box];
-    const int cap = kListPerOwn * K.n + kListSpare;
     const double skin = G.skin;
-    if (t <= kClasses) cnt[t] = 0;
-    if (t == 0) qn = tn = 0;
-    const double delta = le_offset(P, G, c0.step);
-    const ListRows R = list_rows(G, pair_cutoff(P, 2.0 * G.amax) + skin);
+    const ListRows R = list_rows(G, pair_cutoff(P, own_amax + amax) + skin);
     const double icw[3] = {1.0 / G.cw[0], 1.0 / G.cw[1], 1.0 / G.cw[2]};
     // (particle, row) pairs numbered with a power of two of rows per particle
     int sh = 0;
     while ((1 << sh) < R.ny * R.nz) ++sh;
     const int all = K.n << sh;
-    __syncthreads();
     for (int k0 = 0; k0 < all; k0 += kBeginRows) {
+        if (t == 0) T.n = 0;
+        __syncthreads();
         for (int k = k0 + t; k < min(k0 + kBeginRows, all); k += kBeginBlock) {
             const int il = k >> sh, q = k & ((1 << sh) - 1), qz = q / R.ny, qy = q - qz * R.ny;
             if (qz >= R.nz) continue;
-            const double4 Xi = C.pa[K.start + il];
-            list_row(G, icw, delta, cell_start, R, il, Xi, pair_cutoff(P, Xi.w + G.amax) + skin, qy, qz,
-                     [&](const ListTask &a) { tasks[atomicAdd(&tn, 1)] = a; });
+            const double4 Xi = pa[K.start + il];
+            list_row(G, icw, delta, cell_start, R, cell0, il, Xi, pair_cutoff(P, Xi.w + amax) + skin, qy, qz,
+                     [&](const ListTask &a) { T.task[atomicAdd(&T.n, 1)] = a; });
         }
         __syncthreads();
-        const int nt = tn;
-        // kBeginLanes lanes take one run together (their loads are contiguous), kBeginRuns runs at a
-        // time (their loads are in flight together)
+        const int nt = T.n;
         const int sub = t & (kBeginLanes - 1);
         for (int k = t / kBeginLanes; k < nt; k += kBeginRuns * kBeginBlock / kBeginLanes) {
             int jb[kBeginRuns], n[kBeginRuns], il[kBeginRuns], most = 0;
@@ -249,12 +250,16 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
 #pragma unroll
             for (int r = 0; r < kBeginRuns; ++r) {
                 const int m = k + r * (kBeginBlock / kBeginLanes);
-                const ListTask a = tasks[min(m, nt - 1)];
+                const ListTask a = T.task[min(m, nt - 1)];
                 const int cross = ((a.code >> 24) & 3) - 1, z = ((a.code >> 26) & 3) - 1, w = ((a.code >> 28) & 7) - 4;
                 jb[r] = a.jb;
-                n[r] = m < nt ? a.code & 0xffff : 0;
+                n[r] = m < nt ? a.code & kTaskMax : 0;
+                if (n[r] == kTaskMax) {
+                    atomicOr(&clk->err, kErrListFull);
+                    n[r] = 0;
+                }
                 il[r] = (a.code >> 16) & 0xff;
-                const double4 X = C.pa[K.start + il[r]];
+                const double4 X = pa[K.start + il[r]];
                 sx[r] = X.x - ((double)cross * delta + (double)w * G.L[0]);
                 sy[r] = X.y - (double)cross * G.L[1];
                 sz[r] = X.z - (double)z * G.L[2];
@@ -263,22 +268,93 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
             }
             for (int j0 = sub; j0 < most; j0 += kBeginLanes) {
 #pragma unroll
-                for (int r = 0; r < kBeginRuns; ++r) Y[r] = C.pa[jb[r] + (j0 < n[r] ? j0 : 0)];
+                for (int r = 0; r < kBeginRuns; ++r) Y[r] = pa[jb[r] + (j0 < n[r] ? j0 : 0)];
 #pragma unroll
                 for (int r = 0; r < kBeginRuns; ++r) {
                     double dx = Y[r].x - sx[r], dy = Y[r].y - sy[r], dz = Y[r].z - sz[r];
                     if (R.whole) min_image(G, delta, sx[r], sy[r], sz[r], Y[r].x, Y[r].y, Y[r].z, dx, dy, dz);
                     const double rl = pair_cutoff(P, ai[r] + Y[r].w) + skin;
-                    if (j0 < n[r] && jb[r] + j0 != K.start + il[r] && dx * dx + dy * dy + dz * dz < rl * rl) {
-                        const int e = atomicAdd(&qn, 1);
-                        if (e < cap) q_lds[e] = make_int2(jb[r] + j0, il[r]);
-                    }
+                    if (j0 < n[r] && jb[r] + j0 != K.start + il[r] && dx * dx + dy * dy + dz * dz < rl * rl)
+                        push(il[r], jb[r] + j0, ai[r], Y[r].w);
                 }
             }
         }
         __syncthreads();
-        if (t == 0) tn = 0;
-        __syncthreads();
+    }
+}
+
+// ----------------------------------------------------------------------------------
+// k_list_search (size-class stencils): the candidate pairs of one block, found by the pair's first
+// member (the larger one, which scans the classes up to its own), appended as (partner, own index)
+// to the lists of both members' blocks.  L.n counts them (zero at the window's start).
+// ----------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kBeginBlock) k_list_search(DevParams P, const BoxParams *__restrict__ boxes,
+                                                              const int *__restrict__ cell_start,
+                                                              const double4 *__restrict__ pa, ListView L,
+                                                              DevClock *__restrict__ clk)
+{
+    __shared__ ListTasks T;
+    // the blocks of the largest particles, which scan most, first
+    const ListBlock K = L.blocks[gridDim.x - 1 - blockIdx.x];
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const BoxParams G = boxes[K.box];
+    const double delta = le_offset(P, G, c0.step);
+    // largest radius of a class (with a margin for the rounding of its number)
+    auto top = [&](int k) { return k == P.ncls - 1 ? G.amax : fmin(G.amax, (k + 1 - P.cls_add) / P.cls_mul * (1.0 + 1e-12)); };
+    for (int k = 0; k <= K.cls; ++k)
+        list_collect(P, G, delta, cell_start, pa, K, top(K.cls), top(k), k * (G.nc[0] * G.nc[1] * G.nc[2]), T, clk,
+                     [&](int il, int j, double ai, double aj) {
+                         const int i = K.start + il;
+                         if (!(aj < ai || (aj == ai && j < i))) return;
+                         const int bi = L.of[i], bj = L.of[j];
+                         const int e = atomicAdd(&L.n[bi], 1);
+                         if (e < K.cap) L.ent[K.e0 + e] = make_int2(j, il);
+                         if (bj == bi) return;
+                         const ListBlock Kj = L.blocks[bj];
+                         const int f = atomicAdd(&L.n[bj], 1);
+                         if (f < Kj.cap) L.ent[Kj.e0 + f] = make_int2(i, j - Kj.start);
+                     });
+}
+
+// ----------------------------------------------------------------------------------
+// k_list_begin: the lists of one block at the committed state, and the first kick and drift of
+// the block's particles into the window's records.  The candidates (searched here, or with
+// size-class stencils found by k_list_search) are queued in LDS; then all lanes take the queued
+// ones: the pair's orientation and class (contacts, listed pairs, candidates of the margin, stored
+// in this order, so that a wavefront of k_list holds one kind), a pair inside the block from its
+// first member only, and the stored stretch from the committed history rows.
+// ----------------------------------------------------------------------------------
+template <bool Roll>
+__global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const BoxParams *__restrict__ boxes,
+                                                             const int *__restrict__ cell_start, CommittedView C,
+                                                             HistView H, ListView L, ListRec *__restrict__ out,
+                                                             int vel_is_half, DevClock *__restrict__ clk)
+{
+    extern __shared__ int2 q_lds[];
+    __shared__ ListTasks T;
+    __shared__ int qn, cnt[kClasses + 1], pos[kClasses];
+    const int t = threadIdx.x;
+    const int blk = xcd_row(blockIdx.x, gridDim.x);
+    const ListBlock K = L.blocks[blk];
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const BoxParams G = boxes[K.box];
+    const int cap = K.cap;
+    const double skin = G.skin;
+    if (t <= kClasses) cnt[t] = 0;
+    if (t == 0) qn = P.sized ? L.n[blk] : 0;
+    const double delta = le_offset(P, G, c0.step);
+    const double icw[3] = {1.0 / G.cw[0], 1.0 / G.cw[1], 1.0 / G.cw[2]};
+    __syncthreads();
+    if (P.sized) {
+        for (int k = t; k < min(qn, cap); k += kBeginBlock) q_lds[k] = L.ent[K.e0 + k];
+    } else {
+        list_collect(P, G, delta, cell_start, C.pa, K, G.amax, G.amax, G.cell_off, T, clk,
+                     [&](int il, int j, double, double) {
+                         const int e = atomicAdd(&qn, 1);
+                         if (e < cap) q_lds[e] = make_int2(j, il);
+                     });
     }
     if (t < K.n) {
         const int i = K.start + t;
@@ -307,7 +383,7 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
         double dx, dy, dz;
         min_image(G, delta, Xi.x, Xi.y, Xi.z, Xj.x, Xj.y, Xj.z, dx, dy, dz);
         const double r2 = dx * dx + dy * dy + dz * dz, s = Xi.w + Xj.w, rc = pair_cutoff(P, s);
-        const bool fwd = list_forward(G, icw, Xi, Xj, i, j), in = jl >= 0 && jl < K.n;
+        const bool fwd = list_forward(P, G, icw, Xi, Xj, i, j), in = jl >= 0 && jl < K.n;
         const int cls = in && !fwd ? kClasses : (r2 < s * s * (1.0 + 1e-9) ? (in ? 0 : 1) : (r2 < rc * rc ? (in ? 3 : 2) : 4));
         atomicAdd(&cnt[cls], 1);
         q_lds[k] = make_int2(j | (fwd ? 0 : kEntSwap),
@@ -351,7 +427,7 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
 }
 
 // ----------------------------------------------------------------------------------
-// k_list: time step n of the window (1 .. length - 1) of one block: the listed pairs at the records
+// k_list: time step n of the window (1 .. length) of one block: the listed pairs at the records
 // `in` (the physics and history of the pair kernels), the Stokes terms, then the finishing kick
 // and the next step's kick, drift and wrap into `out`; with Last, instead, the state, the force
 // record and the sorted history rows of the step are committed.  Sum: the block's stress and
@@ -433,8 +509,8 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
         if (!on) continue;
         PairOut o;
         double S[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        pair_physics<Real, Roll, false>(P, G.gd, G.wk, dx, dy, dz, dist, Xi.w, Xj.w, Xi.y, Xj.y, Vi, Vj, Wi, Wj, xo,
-                                        xro, S, o);
+        pair_physics<Real, Roll, false, true>(P, G.gd, G.wk, dx, dy, dz, dist, Xi.w, Xj.w, Xi.y, Xj.y, Vi, Vj, Wi, Wj,
+                                              xo, xro, S, o, P.sized && size_class(P, Xi.w) >= P.wave_cls);
         double *const a = acc + 6 * il;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -487,7 +563,7 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
             C.pa[i] = X;
             C.vel[i] = V;
             C.omg[i] = W;
-            store_ft(C.B.own + 6LL * i, f);
+            store_ft(C.own + 6LL * i, f);
             if (c0.deferred) {
                 const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
                 store_ft(C.B.x + 6LL * i, z);  // of the evaluation before the window
@@ -507,7 +583,9 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
         }
     }
     if constexpr (Sum) reduce_fill(tally.fill, red, partials, pstride, blk);
-    if constexpr (!Last) {
+    if constexpr (Last) {
+        if (t == 0) L.n[blk] = 0;  // of the next window's search (every lane has read its count)
+    } else {
         if (bad) atomicOr(&clk->err, kErrListStop);
     }
 }

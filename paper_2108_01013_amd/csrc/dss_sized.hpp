@@ -466,7 +466,9 @@ __global__ void __launch_bounds__(kBlock, 2) k_pairs_sized(DevParams P, const Bo
     const BoxParams G = boxes[0];
     const int ncb = G.nc[0] * G.nc[1] * G.nc[2];
     const int n_lane = P.wave_cls < P.ncls ? cell_start[P.wave_cls * ncb] : P.N;
-    const double delta = le_offset(P, G, clk->step);
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const double delta = le_offset(P, G, c0.step);
     if (blockIdx.x == 0 && threadIdx.x == 0) clk->deferred = 1;  // the atomic record is in use
     PairTally tally;
 #pragma unroll

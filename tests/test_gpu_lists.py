@@ -173,6 +173,47 @@ def test_lists_that_do_not_fit():
     run_both(make, 12, 4, 1e-10, p["L"])
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("cell_scale,rolling", [(1.0, False), (1.5, True), (3.0, False)])
+def test_size_classes(precision, cell_scale, rolling):
+    """Size-class stencils: several classes, and at cell_scale 3 a lattice whose rows are all taken."""
+    from paper_2108_01013_amd.dss import Simulation
+    n = 2500
+    rad = synth.lognormal_radii(n, seed=12)
+    L = synth.box_for_fraction(rad, 0.5)
+    x = synth.relax_positions(rad, L, seed=12)
+    p = synth.default_params([L] * 3, **(dict(kr=2e4, mu_r=0.1) if rolling else {}))
+    rng = np.random.default_rng(2)
+    u = 0.05 * rng.standard_normal(x.shape)
+    u[:, 0] += x[:, 1]
+
+    def make():
+        s = Simulation(p, precision=precision)
+        s.set_tuning(sized=True, cell_scale=cell_scale)
+        s.set_particles(x, rad * 1.002, u)
+        return s
+
+    assert run_both(make, 30, 8, 1e-5 if precision else 1e-10, p["L"], calls=2) > 100
+
+
+def test_snapshot_after_a_window(box):
+    """A snapshot carries the whole state: a second handle continues from it."""
+    from paper_2108_01013_amd.dss import Simulation
+    w, rad, u, om = box
+    a, b = Simulation(w.params), Simulation(w.params)
+    a.set_particles(w.x, rad, u, om)
+    b.set_particles(w.x, rad, u, om)
+    a.step(20)
+    b.load_state(a.save_state())
+    for s in (a, b):
+        s.step(1)
+        s.step(12, stress_every=4)
+    sa, sb = a.state(), b.state()
+    for k in ("x", "u", "w", "F", "T"):
+        assert rel(sa[k], sb[k]) < 1e-10, k
+    assert rel(a.read_stress()[1], b.read_stress()[1]) < 1e-10
+
+
 def test_batch_windows():
     from paper_2108_01013_amd.dss import Batch
     ws = [synth.bidisperse_box(int(n), phi, 50 + k) for k, (n, phi) in enumerate([(600, 0.4), (2100, 0.55), (900, 0.5)])]
