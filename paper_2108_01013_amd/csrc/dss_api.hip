@@ -225,6 +225,9 @@ struct dss_handle {
     double *lxi = nullptr, *lxr = nullptr, *ldsum = nullptr, *lpartials = nullptr;
     int *ln = nullptr, *lcross = nullptr, *lof = nullptr;
     double *lown = nullptr;
+    int *lfar = nullptr, *lfar_n = nullptr;  // electro-chemical far pairs by slot
+    double *lfar_f = nullptr;
+    int far_cap = 0;
     ListRec *lrec[2] = {nullptr, nullptr};
     int list_blocks = 0, list_own_cap = 0, list_cap = 0;
     int list_window = kListWindow;   // longest window (0: off); halved when one stopped early
@@ -283,13 +286,15 @@ void free_lattice(dss_handle *h)
         if (p) (void)hipFree(p);
     };
     destroy_graphs(h);
-    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross); F(h->lof); F(h->lown);
+    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross); F(h->lof); F(h->lown); F(h->lfar); F(h->lfar_n); F(h->lfar_f);
     F(h->lrec[0]); F(h->lrec[1]);
     h->lblocks = nullptr;
     h->lent = nullptr;
     h->lxi = h->lxr = h->ldsum = h->lpartials = nullptr;
     h->ln = h->lcross = h->lof = nullptr;
     h->lown = nullptr;
+    h->lfar = h->lfar_n = nullptr;
+    h->lfar_f = nullptr;
     h->lrec[0] = h->lrec[1] = nullptr;
     F(h->count); F(h->cell_start); F(h->tile_sum); F(h->cs_local); F(h->partials); F(h->d_boxes); F(h->d_row_box);
     h->cs_local = nullptr;
@@ -978,10 +983,12 @@ void commit_run(dss_handle *h, int n, bool lists)
 }
 
 // Whether the time steps of the handle can go as windows on pair lists: the row tiles or the
-// size-class stencils without the electro-chemical ranges, no recording of pairs, no wavy shear.
+// size-class stencils, with the electro-chemical ranges where the far pairs have a pass of their own
+// (else the whole pair set, more than a list holds, is on the lattice), no recording of pairs, no
+// wavy shear.
 bool lists_on(const dss_handle *h)
 {
-    return h->list_window >= kListWindowMin && (h->tune.tiled || h->P.sized) && !h->P.ec && !h->P.record_pairs &&
+    return h->list_window >= kListWindowMin && (h->tune.tiled || h->P.sized) && (!h->P.ec || h->P.ec_split) && !h->P.record_pairs &&
            h->P.wave_amp == 0.0;
 }
 
@@ -1045,6 +1052,22 @@ dss_status setup_lists(dss_handle *h)
         return DSS_OK;
     }
     h->list_blocks = (int)blocks.size();
+    if (h->P.ec_split) {
+        // far lists: 1.6 times the partners of a uniform gas within the longest range and the margin;
+        // the records of their pass follow the blocks' ones
+        BoxParams &G = h->boxes[0];
+        const double r = 2.0 * G.amax + h->P.rext + G.skin;
+        const double mean = (double)h->N / (G.L[0] * G.L[1] * G.L[2]) * (4.0 / 3.0) * kPi * r * r * r;
+        h->far_cap = ((int)std::min(1.6 * mean + 32.0, 1.0e6) + 7) / 8 * 8;
+        if ((double)h->N * h->far_cap > 4.0e9) {
+            h->list_window = 0;  // 16 GB of far lists
+            return DSS_OK;
+        }
+        G.blk_n += h->ec_grid;
+        HIPTRY(dalloc(&h->lfar, (size_t)h->N * h->far_cap));
+        HIPTRY(dalloc(&h->lfar_n, h->N));
+        HIPTRY(dalloc(&h->lfar_f, 3 * h->N));
+    }
     HIPTRY(dalloc(&h->lblocks, blocks.size()));
     HIPTRY(dalloc(&h->lent, ent));
     HIPTRY(dalloc(&h->lxi, 3 * ent));
@@ -1053,7 +1076,7 @@ dss_status setup_lists(dss_handle *h)
     HIPTRY(dalloc(&h->ldsum, h->N));
     HIPTRY(dalloc(&h->lcross, h->N));
     HIPTRY(dalloc(&h->lown, 6 * h->N));
-    HIPTRY(dalloc(&h->lpartials, 12 * blocks.size()));
+    HIPTRY(dalloc(&h->lpartials, 12 * (blocks.size() + h->ec_grid)));
     HIPTRY(dalloc(&h->lrec[0], h->N));
     HIPTRY(hipMemcpyAsync(h->lblocks, blocks.data(), blocks.size() * sizeof(ListBlock), hipMemcpyHostToDevice,
                           h->stream));
@@ -1073,6 +1096,9 @@ dss_status setup_lists(dss_handle *h)
     return DSS_OK;
 }
 
+// Stress partial records of a list step: one per block, then those of the far pairs' pass.
+int list_records(const dss_handle *h) { return h->list_blocks + h->ec_grid; }
+
 template <typename Real, bool Roll>
 void launch_list(dss_handle *h, bool sum, bool last, const ListView &L, int n, const CommittedView &C,
                  const HistView &H)
@@ -1082,7 +1108,8 @@ void launch_list(dss_handle *h, bool sum, bool last, const ListView &L, int n, c
                  : (last ? k_list<Real, Roll, false, true> : k_list<Real, Roll, false, false>);
     const size_t lds = (size_t)h->list_own_cap * (sizeof(ListRec) + 6 * sizeof(double) + sizeof(int));
     hipExtLaunchKernelGGL(k, dim3(h->list_blocks), dim3(kListBlock), lds, h->stream, t.e0, t.e1, 0, h->P, h->d_boxes,
-                          h->boxes[0], L, h->lrec[(n - 1) & 1], h->lrec[n & 1], n, C, H, h->clk, h->lpartials, h->list_blocks);
+                          h->boxes[0], L, h->lrec[(n - 1) & 1], h->lrec[n & 1], n, C, H, h->clk, h->lpartials,
+                          list_records(h));
 }
 
 // A window of n >= 2 time steps; bit k of `finish` sums the stress at step k.
@@ -1095,6 +1122,10 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
     L.xr = h->lxr;
     L.n = h->ln;
     L.of = h->lof;
+    L.far = h->lfar;
+    L.far_n = h->lfar_n;
+    L.far_f = h->lfar_f;
+    L.far_cap = h->far_cap;
     L.dsum = h->ldsum;
     L.cross = h->lcross;
     L.own_cap = h->list_own_cap;
@@ -1126,8 +1157,19 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
                               t.e1, 0, h->P, h->d_boxes, h->cell_start, C, H, L, h->lrec[0], h->vel_is_half ? 1 : 0,
                               h->clk);
     }
+    if (h->P.ec_split) {
+        TimedLaunch t(h, 8);
+        hipExtLaunchKernelGGL(k_list_far_begin, dim3(h->list_blocks), dim3(kBeginBlock), 0, h->stream, t.e0, t.e1, 0,
+                              h->P, h->d_boxes, h->cell_start, h->pa[h->cur], L, h->clk);
+    }
     for (int k = 1; k <= n; ++k) {
         const bool sum = (finish >> (k - 1)) & 1u, last = k == n;
+        if (h->P.ec_split) {
+            TimedLaunch t(h, 7);
+            hipExtLaunchKernelGGL(sum ? k_list_far<true> : k_list_far<false>, dim3(h->ec_grid), dim3(kBlock), 0,
+                                  h->stream, t.e0, t.e1, 0, h->P, h->boxes[0], L, h->lrec[(k - 1) & 1], k, h->clk,
+                                  h->lpartials, list_records(h), h->list_blocks);
+        }
         if (mixed)
             roll ? launch_list<float, true>(h, sum, last, L, k, C, H) : launch_list<float, false>(h, sum, last, L, k, C, H);
         else
@@ -1135,7 +1177,7 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
         if (sum) {
             TimedLaunch t(h, 4);
             hipExtLaunchKernelGGL(k_finish, dim3(12 * h->nbox), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->d_boxes,
-                                  h->lpartials, h->list_blocks, h->clk, h->run, 1, k);
+                                  h->lpartials, list_records(h), h->clk, h->run, 1, k);
         }
     }
     // sort the last state; its rows, committed to the other history buffers, move back with it

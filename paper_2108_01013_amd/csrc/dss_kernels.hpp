@@ -2329,7 +2329,9 @@ __global__ void __launch_bounds__(kBlock) k_pairs_ec(DevParams P, const BoxParam
     double f[3] = {0.0, 0.0, 0.0};
     const bool on = i < P.N;
     const double4 Xi = on ? pa[i] : make_double4(0.0, 0.0, 0.0, 1.0);
-    const double delta = le_offset(P, G, clk->step);
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const double delta = le_offset(P, G, c0.step);
     const int idi = (on && P.record_pairs) ? (int)omg[i].w : 0;
     int nb = 0;
     // forces of the buffered far partners (every lane of the wavefront at once)

@@ -86,6 +86,11 @@ struct ListView {
     int *n;               // entries of each block
     const int *of;        // block of a slot (with size-class stencils)
     double *dsum;         // displacement sum D of the bound above, by slot
+    // electro-chemical pairs beyond the lubrication list (ec_split): the partners of each slot
+    // within their ranges plus the margin, far_cap per slot, and their force on it (3 per slot)
+    int *far, *far_n;
+    double *far_f;
+    int far_cap;
     int *cross;           // y-face crossings of the window by slot
     int own_cap;          // largest block
 };
@@ -103,7 +108,8 @@ __device__ __forceinline__ double list_budget(const DevParams &P, const BoxParam
 {
     const double g = fabs(G.gd) * P.dt * (double)n;
     const double q = sqrt(1.0 + 0.25 * g * g);
-    const double rc = pair_cutoff(P, 2.0 * G.amax);
+    // largest cutoff; with ec_split that of the far pairs, whose lists have the same margin
+    const double rc = P.ec_split ? 2.0 * G.amax + P.rext : pair_cutoff(P, 2.0 * G.amax);
     return ((q - 0.5 * g) * (rc + skin) - rc * (1.0 + 1e-12)) / (2.0 * (q + 0.5 * g));
 }
 
@@ -205,8 +211,8 @@ __device__ __forceinline__ void list_row(const BoxParams &G, const double icw[3]
 }
 
 // The candidates of a block's particles among the cells from cell0 on (the box's, or a size
-// class's), partners of radius up to amax: push(il, j, Xi, Xj) for every one inside its cutoff plus
-// the margin.  In batches of kBeginRows (particle, cell row) pairs the lanes write the candidate
+// class's), partners of radius up to amax: push(il, j, a_i, a_j) for every one inside its cutoff (Far:
+// the electro-chemical ranges) plus the margin.  In batches of kBeginRows (particle, cell row) pairs the lanes write the candidate
 // runs of their rows into LDS, then take the runs (so every lane has one, although most rows are
 // out of reach): kBeginLanes lanes one run together (their loads are contiguous), kBeginRuns at a
 // time (their loads are in flight together).  (One particle per eight lanes, each walking its
@@ -216,15 +222,16 @@ struct ListTasks {
     int n;
 };
 
-template <typename Push>
+template <bool Far = false, typename Push>
 __device__ __forceinline__ void list_collect(const DevParams &P, const BoxParams &G, double delta,
                                              const int *__restrict__ cell_start, const double4 *__restrict__ pa,
                                              const ListBlock &K, double own_amax, double amax, int cell0, ListTasks &T,
                                              DevClock *__restrict__ clk, Push &&push)
 {
     const int t = threadIdx.x;
-    const double skin = G.skin;
-    const ListRows R = list_rows(G, pair_cutoff(P, own_amax + amax) + skin);
+    // radius of the search for a pair of radius sum s
+    auto reach = [&](double s) { return (Far ? s + P.rext : pair_cutoff(P, s)) + G.skin; };
+    const ListRows R = list_rows(G, reach(own_amax + amax));
     const double icw[3] = {1.0 / G.cw[0], 1.0 / G.cw[1], 1.0 / G.cw[2]};
     // (particle, row) pairs numbered with a power of two of rows per particle
     int sh = 0;
@@ -237,7 +244,7 @@ __device__ __forceinline__ void list_collect(const DevParams &P, const BoxParams
             const int il = k >> sh, q = k & ((1 << sh) - 1), qz = q / R.ny, qy = q - qz * R.ny;
             if (qz >= R.nz) continue;
             const double4 Xi = pa[K.start + il];
-            list_row(G, icw, delta, cell_start, R, cell0, il, Xi, pair_cutoff(P, Xi.w + amax) + skin, qy, qz,
+            list_row(G, icw, delta, cell_start, R, cell0, il, Xi, reach(Xi.w + amax), qy, qz,
                      [&](const ListTask &a) { T.task[atomicAdd(&T.n, 1)] = a; });
         }
         __syncthreads();
@@ -273,7 +280,7 @@ __device__ __forceinline__ void list_collect(const DevParams &P, const BoxParams
                 for (int r = 0; r < kBeginRuns; ++r) {
                     double dx = Y[r].x - sx[r], dy = Y[r].y - sy[r], dz = Y[r].z - sz[r];
                     if (R.whole) min_image(G, delta, sx[r], sy[r], sz[r], Y[r].x, Y[r].y, Y[r].z, dx, dy, dz);
-                    const double rl = pair_cutoff(P, ai[r] + Y[r].w) + skin;
+                    const double rl = reach(ai[r] + Y[r].w);
                     if (j0 < n[r] && jb[r] + j0 != K.start + il[r] && dx * dx + dy * dy + dz * dz < rl * rl)
                         push(il[r], jb[r] + j0, ai[r], Y[r].w);
                 }
@@ -360,7 +367,7 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
         const int i = K.start + t;
         double4 X = C.pa[i], V = C.vel[i], W = C.omg[i];
         double f[6];
-        total_ft(C.B, i, f, clk->deferred != 0);
+        total_ft(C.B, i, f, c0.deferred || P.ec_split);
         int cross = 0;
         const double d = sqrt(advance_particle(P, G, X, V, W, f, vel_is_half != 0, clk->step + 1, cross));
         out[i].p = X;
@@ -424,6 +431,108 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
         }
         L.ent[slot] = e;
     }
+}
+
+// ----------------------------------------------------------------------------------
+// k_list_far_begin: with the electro-chemical far pairs on a pass of their own (ec_split), the
+// partners of each particle of a block within their ranges plus the margin (the lubrication list's
+// among them: the step's test tells).
+// ----------------------------------------------------------------------------------
+__global__ void __launch_bounds__(kBeginBlock) k_list_far_begin(DevParams P, const BoxParams *__restrict__ boxes,
+                                                                 const int *__restrict__ cell_start,
+                                                                 const double4 *__restrict__ pa, ListView L,
+                                                                 DevClock *__restrict__ clk)
+{
+    __shared__ ListTasks T;
+    __shared__ int cnt[kListOwnMax];
+    const int t = threadIdx.x;
+    const ListBlock K = L.blocks[xcd_row(blockIdx.x, gridDim.x)];
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const BoxParams G = boxes[K.box];
+    if (t < kListOwnMax) cnt[t] = 0;
+    __syncthreads();
+    list_collect<true>(P, G, le_offset(P, G, c0.step), cell_start, pa, K, G.amax, G.amax, G.cell_off, T, clk,
+                       [&](int il, int j, double, double) {
+                           const int e = atomicAdd(&cnt[il], 1);
+                           if (e < L.far_cap) L.far[(long long)(K.start + il) * L.far_cap + e] = j;
+                       });
+    if (t < K.n) {
+        L.far_n[K.start + t] = min(cnt[t], L.far_cap);
+        if (cnt[t] > L.far_cap) atomicOr(&clk->err, kErrListFull);
+    }
+}
+
+// ----------------------------------------------------------------------------------
+// k_list_far: the force of the electro-chemical far pairs on every particle at step n of a window,
+// as k_pairs_ec takes it (the same FP64 distance and ranges, gathered from both sides, no atomics)
+// over the far lists: kEcLanes lanes share a particle, kEcChunk partners of a lane in flight.
+// The search of k_pairs_ec tests about 500 candidates per particle, a list holds about 100: 315 us
+// per step at N = 100k with attraction, 68 us so, plus 145 us per window for the lists.
+// ----------------------------------------------------------------------------------
+template <bool Sum>
+__global__ void __launch_bounds__(kBlock) k_list_far(DevParams P, BoxParams G, ListView L,
+                                                      const ListRec *__restrict__ in, int n,
+                                                      const DevClock *__restrict__ clk, double *__restrict__ partials,
+                                                      int pstride, int rec0)
+{
+    __shared__ double red[kBlock / 64][12];
+    const int t = threadIdx.x;
+    const int sub = t & (kEcLanes - 1);
+    const int i = (xcd_row(blockIdx.x, gridDim.x) * kBlock + t) / kEcLanes;
+    const DevClock c0 = *clk;
+    if (c0.err & kErrListMask) return;
+    const bool on = i < P.N;
+    const int nf = on ? L.far_n[i] : 0;
+    const double4 Xi = in[on ? i : 0].p;
+    const double delta = le_offset(P, G, c0.step + n);
+    PairTally tally;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) tally.S[k] = 0.0;
+    tally.npair = tally.ncont = 0;
+    tally.fill = 0;
+    double f[3] = {0.0, 0.0, 0.0};
+    const int *const list = L.far + (long long)(on ? i : 0) * L.far_cap;
+    for (int e0 = sub; e0 < nf; e0 += kEcLanes * kEcChunk) {
+        int j[kEcChunk];
+        double4 X[kEcChunk];
+#pragma unroll
+        for (int u = 0; u < kEcChunk; ++u) j[u] = list[e0 + u * kEcLanes < nf ? e0 + u * kEcLanes : sub];
+#pragma unroll
+        for (int u = 0; u < kEcChunk; ++u) X[u] = in[j[u]].p;
+#pragma unroll
+        for (int u = 0; u < kEcChunk; ++u) {
+            double dx, dy, dz, r2, rl, re;
+            min_image(G, delta, Xi.x, Xi.y, Xi.z, X[u].x, X[u].y, X[u].z, dx, dy, dz);
+            const double s = Xi.w + X[u].w;
+            {
+#pragma clang fp contract(off)
+                r2 = (dx * dx + dy * dy) + dz * dz;
+                rl = P.cf * s;
+                re = s + P.rext;
+            }
+            if (!(e0 + u * kEcLanes < nf) || r2 < rl * rl || !(r2 < re * re)) continue;
+            const double dist = sqrt(r2);
+            const double g = ec_far_force(P, dist, Xi.w, X[u].w) * rcp_nr(dist);
+            const double F[3] = {g * dx, g * dy, g * dz};
+#pragma unroll
+            for (int c = 0; c < 3; ++c) f[c] += F[c];
+            if constexpr (Sum) {
+                const double r[3] = {dx, dy, dz};
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) tally.S[3 * a + c] += 0.5 * r[a] * F[c];
+                if (i < j[u]) ++tally.npair;
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < kEcLanes; o <<= 1)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) f[c] += __shfl_xor(f[c], o, 64);
+    if (on && sub < 3) L.far_f[3LL * i + sub] = sub == 0 ? f[0] : (sub == 1 ? f[1] : f[2]);
+    if constexpr (Sum) reduce_tally(tally, red, partials, pstride, rec0 + blockIdx.x);
 }
 
 // ----------------------------------------------------------------------------------
@@ -558,13 +667,17 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
 #pragma unroll
         for (int c = 0; c < 6; ++c) f[c] = acc[6 * il + c];
         stokes_terms<false>(P, G, X, V, W, f, nullptr);
+        if (P.ec_split) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) f[c] += L.far_f[3LL * i + c];
+        }
         tally.fill = max(tally.fill, cnt[il]);
         if constexpr (Last) {
             C.pa[i] = X;
             C.vel[i] = V;
             C.omg[i] = W;
             store_ft(C.own + 6LL * i, f);
-            if (c0.deferred) {
+            if (c0.deferred || P.ec_split) {
                 const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
                 store_ft(C.B.x + 6LL * i, z);  // of the evaluation before the window
             }

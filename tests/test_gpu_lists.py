@@ -196,6 +196,21 @@ def test_size_classes(precision, cell_scale, rolling):
     assert run_both(make, 30, 8, 1e-5 if precision else 1e-10, p["L"], calls=2) > 100
 
 
+@pytest.mark.parametrize("precision,ham,lam", [(0, 1e-3, 0.05), (1, 1e-3, 0.05), (0, 0.0, 0.08)])
+def test_electro_chemical_ranges(precision, ham, lam):
+    """The far pairs of the electro-chemical ranges on lists of their own."""
+    from paper_2108_01013_amd.dss import Simulation
+    w = synth.bidisperse_box(4500, 0.45, 23, ec_ranges=True, hamaker=ham, lambda_D=lam)
+
+    def make():
+        s = Simulation(w.params, precision=precision)
+        s.set_particles(w.x, w.rad * 1.001)
+        assert s.box_info(0)["ec_far_rows"][0] > 0
+        return s
+
+    assert run_both(make, 24, 6, 1e-5 if precision else 1e-10, w.params["L"], calls=2) > 100
+
+
 def test_snapshot_after_a_window(box):
     """A snapshot carries the whole state: a second handle continues from it."""
     from paper_2108_01013_amd.dss import Simulation
