@@ -2768,21 +2768,21 @@ dss_status dss_phi_profile(dss_handle *h, int32_t nbins, double a_split, double 
     if (nbins < 1 || nbins > 2048 || !phi) return fail(h, DSS_ERR_ARG, "nbins in [1, 2048] and phi non-null");
     const int64_t N = h->N;
     const int grid = (int)((N + kBlock - 1) / kBlock);
-    double *part = nullptr;
+    const int m = 2 * nbins;
+    double *part = nullptr, *sum = nullptr;
     h->obs_ws.rewind();
-    HIPTRY(h->obs_ws.get(&part, 2 * (size_t)nbins * grid));
+    HIPTRY(h->obs_ws.get(&part, (size_t)m * grid));
+    HIPTRY(h->obs_ws.get(&sum, m));
     const BoxParams &G = h->boxes[0];
-    hipLaunchKernelGGL(k_phi_profile, dim3(grid), dim3(kBlock), 2 * (size_t)nbins * sizeof(double), h->stream, (int)N,
+    hipLaunchKernelGGL(k_phi_profile, dim3(grid), dim3(kBlock), (size_t)m * sizeof(double), h->stream, (int)N,
                        G.L[1], (int)nbins, a_split, h->pa[h->cur], part);
+    hipLaunchKernelGGL(k_phi_reduce, dim3((64 * m + kBlock - 1) / kBlock), dim3(kBlock), 0, h->stream, part, grid, m,
+                       sum);
     HIPTRY(hipGetLastError());
-    std::vector<double> hp(2 * (size_t)nbins * grid);
-    HIPTRY(hipMemcpy(hp.data(), part, hp.size() * sizeof(double), hipMemcpyDeviceToHost));
+    HIPTRY(hipMemcpyAsync(phi, sum, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPTRY(hipStreamSynchronize(h->stream));
     const double slab = G.L[0] * G.L[2] * (G.L[1] / (double)nbins);
-    for (int k = 0; k < 2 * nbins; ++k) {
-        double t = 0.0;
-        for (int b = 0; b < grid; ++b) t += hp[(size_t)b * 2 * nbins + k];
-        phi[k] = t / slab;
-    }
+    for (int k = 0; k < m; ++k) phi[k] = phi[k] / slab;
     return DSS_OK;
 }
 
@@ -2803,7 +2803,8 @@ dss_status dss_phi_profile_noalloc(dss_handle *h, int32_t nbins, double a_split,
     const BoxParams &G = h->boxes[0];
     hipLaunchKernelGGL(k_phi_profile, dim3(grid), dim3(kBlock), (size_t)m * sizeof(double), h->stream, (int)h->N,
                        G.L[1], (int)nbins, a_split, h->pa[h->cur], part);
-    hipLaunchKernelGGL(k_phi_reduce, dim3((m + kBlock - 1) / kBlock), dim3(kBlock), 0, h->stream, part, grid, m, sum);
+    hipLaunchKernelGGL(k_phi_reduce, dim3((64 * m + kBlock - 1) / kBlock), dim3(kBlock), 0, h->stream, part, grid, m,
+                       sum);
     HIPTRY(hipGetLastError());
     HIPTRY(hipMemcpyAsync(phi, sum, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIPTRY(hipStreamSynchronize(h->stream));
@@ -2827,6 +2828,11 @@ dss_status dss_contact_clusters(dss_handle *h, int64_t cap, int64_t *hist, int64
     HIPTRY(h->obs_ws.get(&dh, cap));
     HIPTRY(hipMemsetAsync(dh, 0, cap * sizeof(unsigned long long), h->stream));
     hipLaunchKernelGGL(k_cc_init, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, parent, size);
+    for (int pass = 0; pass < kLowerPasses; ++pass) {
+        hipLaunchKernelGGL(k_cc_lower, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, h->P.M, h->hown[h->hh],
+                           h->hkey[h->hh], h->hcnt[h->hh], parent);
+        hipLaunchKernelGGL(k_cc_flatten, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, parent);
+    }
     hipLaunchKernelGGL(k_cc_hook, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, h->P.M, h->hown[h->hh],
                        h->hkey[h->hh], h->hcnt[h->hh], parent);
     hipLaunchKernelGGL(k_cc_count, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, parent, size);

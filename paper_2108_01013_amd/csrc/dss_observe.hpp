@@ -92,16 +92,18 @@ __global__ void __launch_bounds__(kBlock) k_phi_profile(int N, double Ly, int nb
     for (int k = threadIdx.x; k < 2 * nb; k += kBlock) part[(long long)blockIdx.x * 2 * nb + k] = hist[k];
 }
 
-// Sum of the nw partial profiles of k_phi_profile in workgroup order (the order the host sums
-// them in for dss_phi_profile): out[k] = sum_b part[b][k], k < m = 2 nb.
+// Sum of the nw partial profiles of k_phi_profile: out[k] = sum_b part[b][k], k < m = 2 nb, one
+// wavefront per k, its lanes over the workgroups, in a fixed order (one lane per k, adding 391
+// partials one after the other, took 94 us at N = 100k; 4.6 us so).
 __global__ void __launch_bounds__(kBlock) k_phi_reduce(const double *__restrict__ part, int nw, int m,
                                                         double *__restrict__ out)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int k = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
     if (k >= m) return;
     double t = 0.0;
-    for (int b = 0; b < nw; ++b) t += part[(long long)b * m + k];
-    out[k] = t;
+    for (int b = lane; b < nw; b += 64) t += part[(long long)b * m + k];
+    t = warp_sum(t);
+    if (lane == 0) out[k] = t;
 }
 
 // Connected components of the contact graph by lock-free union-find over particle ids.
@@ -110,17 +112,37 @@ __global__ void __launch_bounds__(kBlock) k_phi_reduce(const double *__restrict_
 // visited node is pointed at its grandparent, which is still an ancestor no larger than it,
 // and only non-roots are written (hooks change roots only, by compare-and-swap), so the
 // invariant holds under concurrent finds and hooks while chains stay short.
+// The loads and stores of a find are of workgroup scope, from the XCD's own L2 (at system scope
+// each went to memory: k_cc_hook alone 632 us at N = 100k, 270 us so): a parent read late is an
+// older ancestor, which serves as well, and a root read late fails the compare-and-swap, whose
+// answer is where the next find begins.
 __device__ __forceinline__ int cc_find(int *parent, int v)
 {
-    int cur = __atomic_load_n(&parent[v], __ATOMIC_RELAXED);
+    int cur = __hip_atomic_load(&parent[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (cur == v) return v;
     int prev = v;
     for (;;) {
-        const int next = __atomic_load_n(&parent[cur], __ATOMIC_RELAXED);
+        const int next = __hip_atomic_load(&parent[cur], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (next == cur) return cur;
-        __atomic_store_n(&parent[prev], next, __ATOMIC_RELAXED);
+        __hip_atomic_store(&parent[prev], next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         prev = cur;
         cur = next;
+    }
+}
+
+// base[idx] += the number of active lanes of the wavefront with that idx, one atomic per
+// distinct idx.
+template <typename T>
+__device__ __forceinline__ void cc_add_grouped(T *base, long long idx, bool active)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned long long todo = __ballot(active);
+    while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const long long v = __shfl(idx, leader, 64);
+        const unsigned long long same = __ballot(active && idx == v);
+        if (lane == leader) atomicAdd(&base[v], (T)__popcll(same));
+        todo &= ~same;
     }
 }
 
@@ -130,6 +152,43 @@ __global__ void __launch_bounds__(kBlock) k_cc_init(int N, int *__restrict__ par
     if (v >= N) return;
     parent[v] = v;
     size[v] = 0;
+}
+
+// The larger of the parents of every contact's particles goes under the smaller, by a plain store:
+// of several stores to one parent any may stay, since each is a smaller member of the same
+// cluster, and the links that were lost are made by the next pass or by k_cc_hook, which joins
+// the particles of every contact.  With k_cc_flatten after each, kLowerPasses passes leave
+// k_cc_hook little to join (random spheres of mean coordination 4.5: 82 000, 33 000, 16 000, 7 500
+// and 0 of 225 000 contacts are left between trees after 1 .. 5 passes), and so none of its
+// compare-and-swaps of many lanes on the root of the largest cluster: 53 us of passes and 8 us of
+// k_cc_hook at N = 100k, where k_cc_hook alone took 270 us (the passes by atomicMin: 118 us).
+constexpr int kLowerPasses = 5;
+
+__global__ void __launch_bounds__(kBlock) k_cc_lower(int N, int M, const int *__restrict__ own,
+                                                      const int *__restrict__ key, const int *__restrict__ cnt,
+                                                      int *parent)
+{
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= N) return;
+    const int a = own[p];
+    const int n = cnt[p];
+    const int ra = __hip_atomic_load(&parent[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int k = 0; k < n; ++k) {
+        const int b = key[(long long)p * M + k] & kKeyMask;
+        const int rb = __hip_atomic_load(&parent[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const int lo = ra < rb ? ra : rb, hi = ra < rb ? rb : ra;
+        if (lo != hi && __hip_atomic_load(&parent[hi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > lo)
+            __hip_atomic_store(&parent[hi], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+// Every particle under its root.
+__global__ void __launch_bounds__(kBlock) k_cc_flatten(int N, int *parent)
+{
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= N) return;
+    const int root = cc_find(parent, v);
+    __hip_atomic_store(&parent[v], root, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Every committed contact (row owner own[p], partner key) joins its two particles.
@@ -146,19 +205,30 @@ __global__ void __launch_bounds__(kBlock) k_cc_hook(int N, int M, const int *__r
         int ra = cc_find(parent, a), rb = cc_find(parent, b);
         while (ra != rb) {
             const int lo = ra < rb ? ra : rb, hi = ra < rb ? rb : ra;
-            if (atomicCAS(&parent[hi], hi, lo) == hi) break;
+            const int was = atomicCAS(&parent[hi], hi, lo);
+            if (was == hi) break;
             ra = cc_find(parent, lo);
-            rb = cc_find(parent, hi);
+            rb = cc_find(parent, was);  // was < hi
         }
     }
 }
 
-// Cluster sizes: size[root] = particles under root.
+// Cluster sizes: size[root] = particles under root.  A cluster that spans the box holds most
+// lanes of every workgroup: the lanes under the first lane's root are counted by the workgroup (one
+// atomic for all), the others by their wavefront (one atomic per lane on one word: 1023 us at
+// N = 100k with a cluster of 95 000, 7 us so).
 __global__ void __launch_bounds__(kBlock) k_cc_count(int N, int *parent, int *__restrict__ size)
 {
+    __shared__ int first;
     const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= N) return;
-    atomicAdd(&size[cc_find(parent, v)], 1);
+    const bool on = v < N;
+    const int root = on ? cc_find(parent, v) : -1;
+    if (threadIdx.x == 0) first = root;
+    __syncthreads();
+    const int f = first;
+    const int n = __syncthreads_count(root == f);
+    if (threadIdx.x == 0) atomicAdd(&size[f], n);
+    cc_add_grouped(size, root, on && root != f);
 }
 
 // Histogram of cluster sizes: hist[s - 1] += 1 for every root of size s (s > cap counts in
@@ -167,10 +237,11 @@ __global__ void __launch_bounds__(kBlock) k_cc_hist(int N, const int *parent, co
                                                      long long cap, unsigned long long *__restrict__ hist)
 {
     const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= N) return;
-    if (parent[v] != v) return;
-    const long long s = size[v];
-    atomicAdd(&hist[(s < cap ? s : cap) - 1], 1ull);
+    const bool root = v < N && parent[v] == v;
+    const long long s = root ? size[v] : 1;
+    const int ones = __syncthreads_count(root && s == 1);  // one atomic of the workgroup for these
+    if (threadIdx.x == 0 && ones) atomicAdd(&hist[0], (unsigned long long)ones);
+    cc_add_grouped(hist, (s < cap ? s : cap) - 1, root && s != 1);
 }
 
 }  // namespace dss
