@@ -9,7 +9,7 @@
 // of x, uh, wh (by particle id) and of the contact stretches (in canonical history rows)
 // backwards one step at a time.  Everything here works on the recorded run ("tape") by
 // particle id: positions, half-step velocities, the listed pairs (id_min, id_max) and the
-// contact history in canonical rows (row of the smaller id, sorted by partner id).
+// contact history in canonical rows (row of the smaller id, in no particular order).
 #pragma once
 
 #include "dss_kernels.hpp"
@@ -17,23 +17,29 @@
 
 namespace dss {
 
-// Position of contact (a < b) in canonical rows, or -1 (keys carry the cap flag in bit 30).
+// Position of contact (a < b) in canonical rows, or -1 (keys carry the cap flag in bit 30; the
+// rows are not sorted, and four keys are read at a time).
 __device__ __forceinline__ long long canon_find(const int *__restrict__ key, const int *__restrict__ cnt, int M, int a,
                                                 int b)
 {
-    const int n = cnt[a];
+    const int n = cnt[a] < M ? cnt[a] : M;
     const int *kr = key + (long long)a * M;
-    for (int k = 0; k < n; ++k) {
-        const int kk = kr[k] & kKeyMask;
-        if (kk == b) return (long long)a * M + k;
-        if (kk > b) break;
+    for (int k0 = 0; k0 < n; k0 += 4) {
+        int kk[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) kk[e] = k0 + e < n ? kr[k0 + e] & kKeyMask : -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (kk[e] == b) return (long long)a * M + k0 + e;
     }
     return -1;
 }
 
 // Committed history rows (slot rows with owner ids and partner keys, stretch oriented from
-// the smaller to the larger id) -> canonical rows by id.  Pass 1 appends each contact to the
-// row of its smaller id; pass 2 sorts every row by partner id.  ccnt must be zero on entry.
+// the smaller to the larger id) -> canonical rows by id: each contact is appended to the row of its
+// smaller id (the rows were sorted by partner id after it; nothing reads the order, and the
+// second kernel took 10 us at N = 2000 and 16 us at N = 50k a step).  ccnt must be zero on entry, and
+// may count past M (kErrRowOverflow): its readers take at most M.
 template <int sw>
 __global__ void __launch_bounds__(kBlock) k_canon_fill(int N, int M, const int *__restrict__ own,
                                                        const int *__restrict__ key, const double *__restrict__ xi,
@@ -41,11 +47,12 @@ __global__ void __launch_bounds__(kBlock) k_canon_fill(int N, int M, const int *
                                                        int *__restrict__ ckey, double *__restrict__ cxi,
                                                        int *__restrict__ ccnt, DevClock *__restrict__ clk)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    // four lanes to a row: its contacts' atomics overlap
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, p = t >> 2;
     if (p >= N) return;
     const int id = own[p];
     const int n = cnt[p];
-    for (int k = 0; k < n; ++k) {
+    for (int k = t & 3; k < n; k += 4) {
         const int kw = key[(long long)p * M + k];
         const int partner = kw & kKeyMask;
         const int a = id < partner ? id : partner, b = id < partner ? partner : id;
@@ -70,32 +77,6 @@ __global__ void __launch_bounds__(kBlock) k_canon_fill(int N, int M, const int *
     }
 }
 
-template <int sw>
-__global__ void __launch_bounds__(kBlock) k_canon_sort(int N, int M, int *__restrict__ ckey, double *__restrict__ cxi,
-                                                       int *__restrict__ ccnt)
-{
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= N) return;
-    int n = ccnt[a];
-    n = n < M ? n : M;
-    ccnt[a] = n;
-    int *kr = ckey + (long long)a * M;
-    double *xr = cxi + (long long)a * M * sw;
-    for (int i = 1; i < n; ++i) {
-        const int k = kr[i];
-        double v[6];
-        for (int c = 0; c < sw; ++c) v[c] = xr[sw * i + c];
-        int j = i - 1;
-        while (j >= 0 && (kr[j] & kKeyMask) > (k & kKeyMask)) {
-            kr[j + 1] = kr[j];
-            for (int c = 0; c < sw; ++c) xr[sw * (j + 1) + c] = xr[sw * j + c];
-            --j;
-        }
-        kr[j + 1] = k;
-        for (int c = 0; c < sw; ++c) xr[sw * (j + 1) + c] = v[c];
-    }
-}
-
 // Stretch adjoints from canonical rows A to canonical rows B (the same contacts, possibly
 // laid out differently): every contact of B takes the adjoint of its match in A, or 0.
 template <int sw>
@@ -106,7 +87,7 @@ __global__ void __launch_bounds__(kBlock) k_canon_rekey(int N, int M, const int 
 {
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
     if (a >= N) return;
-    const int n = cntB[a];
+    const int n = cntB[a] < M ? cntB[a] : M;
     for (int k = 0; k < n; ++k) {
         const long long q = (long long)a * M + k;
         const long long s = canon_find(keyA, cntA, M, a, keyB[q] & kKeyMask);
@@ -121,7 +102,7 @@ __global__ void __launch_bounds__(kBlock) k_canon_zero(int N, int M, const int *
 {
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
     if (a >= N) return;
-    const int n = cnt[a];
+    const int n = cnt[a] < M ? cnt[a] : M;
     double *r = g + (long long)a * M * sw;
     for (int k = 0; k < sw * n; ++k) r[k] = 0.0;
 }
@@ -139,7 +120,8 @@ __global__ void __launch_bounds__(kBlock) k_canon_zero(int N, int M, const int *
 // full list go to an overflow list whose entries k_pairs_vjp_sum adds with FP64 atomics, so
 // there are none on the common path); the old-stretch adjoint is stored at the
 // contact's position in the previous rows, and the parameter gradients (mu, F_ER) are summed
-// per workgroup, then added once.
+// per workgroup (theta_part, 2 per workgroup; k_pairs_vjp_sum adds them up: an atomic of every
+// workgroup on one word waited for the others, about 10 ns each).
 // ----------------------------------------------------------------------------------
 struct VjpTape {
     const int *pairs;       // 2 x npairs (id_min, id_max)
@@ -147,11 +129,11 @@ struct VjpTape {
     const int *key_old, *cnt_old;    // canonical rows before the step (null: empty)
     const double *xi_old;
     const int *key_new, *cnt_new;    // canonical rows after the step (null: not committed)
-    int sw;                          // stretch entries per contact: 3, or 6 with the rolling stretch
 };
 
 // The reverse pass of recorded pair k of a tape entry: its ids (a < b), the position of its
 // stretch in the previous canonical rows (or -1), and its PairGrad.
+template <bool Roll, bool Stress>
 __device__ __forceinline__ void vjp_of_pair(const DevParams &P, const BoxParams &G, long long step, int k,
                                             const VjpTape &tp, const double *__restrict__ xib_new,
                                             const double *__restrict__ Fb, const double *__restrict__ Tb,
@@ -164,7 +146,7 @@ __device__ __forceinline__ void vjp_of_pair(const DevParams &P, const BoxParams 
     const double *xa = tp.x + 3LL * a, *xb = tp.x + 3LL * b;
     double r[3];
     min_image(G, delta, xa[0], xa[1], xa[2], xb[0], xb[1], xb[2], r[0], r[1], r[2]);
-    const int sw = tp.sw;
+    constexpr int sw = Roll ? 6 : 3;
     double xo[3] = {0.0, 0.0, 0.0}, xro[3] = {0.0, 0.0, 0.0};
     pold = -1;
     if (tp.key_old) {
@@ -172,7 +154,7 @@ __device__ __forceinline__ void vjp_of_pair(const DevParams &P, const BoxParams 
         if (pold >= 0)
             for (int c = 0; c < 3; ++c) {
                 xo[c] = tp.xi_old[sw * pold + c];
-                if (sw == 6) xro[c] = tp.xi_old[sw * pold + 3 + c];
+                if (Roll) xro[c] = tp.xi_old[sw * pold + 3 + c];
             }
     }
     PairBar bar;
@@ -191,19 +173,19 @@ __device__ __forceinline__ void vjp_of_pair(const DevParams &P, const BoxParams 
         const long long pn = canon_find(tp.key_new, tp.cnt_new, P.M, a, b);
         f_contact = pn >= 0 ? 1 : 0;
         f_capped = pn >= 0 ? ((tp.key_new[pn] & kCapBit) ? 1 : 0) : 0;
-        f_rcapped = pn >= 0 ? ((tp.key_new[pn] & kRollCapBit) ? 1 : 0) : 0;
+        if (Roll) f_rcapped = pn >= 0 ? ((tp.key_new[pn] & kRollCapBit) ? 1 : 0) : 0;
         if (pn >= 0 && xib_new)
             for (int c = 0; c < 3; ++c) {
                 bar.xi[c] = xib_new[sw * pn + c];
-                if (sw == 6) bar.xr[c] = xib_new[sw * pn + 3 + c];
+                if (Roll) bar.xr[c] = xib_new[sw * pn + 3 + c];
             }
     }
-    for (int c = 0; c < 9; ++c) bar.S[c] = Sb ? Sb[c] : 0.0;
+    for (int c = 0; c < 9; ++c) bar.S[c] = Stress ? Sb[c] : 0.0;
     PairConst C;
     C.k6 = P.k6; C.kn = P.kn; C.kt = P.kt; C.gn = P.gn; C.mu = P.mu; C.fer = P.fer; C.a0 = P.a0;
     C.lamd = P.lamd; C.ham = P.ham; C.eps_vdw = P.eps_vdw; C.eps_lub = P.eps_lub; C.dt = P.dt;
     C.ec = P.ec; C.cf = P.cf; C.rep_rng = P.rep_rng; C.att_rng = P.att_rng;
-    C.roll = sw == 6 ? 1 : 0; C.kr = P.kr; C.mu_r = P.mu_r;
+    C.roll = Roll ? 1 : 0; C.kr = P.kr; C.mu_r = P.mu_r;
     pair_vjp(C, G.gd, r, tp.rad[a], tp.rad[b], xa[1], xb[1], tp.u + 3LL * a, tp.u + 3LL * b, tp.w + 3LL * a,
              tp.w + 3LL * b, xo, bar, g, nullptr, f_contact, f_capped, xro, f_rcapped);
 }
@@ -227,11 +209,17 @@ __device__ __forceinline__ void adj_push(int id, int code, int cap, int *__restr
         ovf[atomicAdd(ovf_n, 1u)] = make_int2(id, code);
 }
 
-__global__ void __launch_bounds__(kBlock) k_pairs_vjp(DevParams P, BoxParams G, long long step, int npairs,
+// Bounds: latency of the gathers by id and the FP64 chain of the pair; two wavefronts per SIMD (256
+// VGPRs; three, at 168, spill 48: 54.9 us against 50.7 at N = 50k, 17.1 against 14.3 at N = 2000).
+// The rolling stretch and the stress weights of the evaluations that are sampled are template
+// parameters: without them in the common kernel it needs 196 VGPRs, with them 256 and 14 AGPRs,
+// which left one wavefront per SIMD (62 us at N = 50k).
+template <bool Roll, bool Stress>
+__global__ void __launch_bounds__(kBlock, 2) k_pairs_vjp(DevParams P, BoxParams G, long long step, int npairs,
                                                       VjpTape tp, const double *__restrict__ xib_new,
                                                       double *__restrict__ xib_old, const double *__restrict__ Fb,
                                                       const double *__restrict__ Tb, const double *__restrict__ Sb,
-                                                      double *__restrict__ gpair, double *__restrict__ theta_b,
+                                                      double *__restrict__ gpair, double *__restrict__ theta_part,
                                                       int cap, int *__restrict__ pos, int *__restrict__ adj,
                                                       unsigned *__restrict__ ovf_n, int2 *__restrict__ ovf)
 {
@@ -246,7 +234,7 @@ __global__ void __launch_bounds__(kBlock) k_pairs_vjp(DevParams P, BoxParams G, 
         int a, b;
         long long pold;
         PairGrad g = {};
-        vjp_of_pair(P, G, step, k, tp, xib_new, Fb, Tb, Sb, a, b, pold, g);
+        vjp_of_pair<Roll, Stress>(P, G, step, k, tp, xib_new, Fb, Tb, Sb, a, b, pold, g);
         // the two sides: (x, u, w) cotangents of a, then of b
         const double o[18] = {-g.r[0], -g.r[1] + g.yi, -g.r[2], g.ui[0], g.ui[1], g.ui[2], g.wi[0], g.wi[1], g.wi[2],
                               g.r[0],  g.r[1] + g.yj,  g.r[2],  g.uj[0], g.uj[1], g.uj[2], g.wj[0], g.wj[1], g.wj[2]};
@@ -255,8 +243,8 @@ __global__ void __launch_bounds__(kBlock) k_pairs_vjp(DevParams P, BoxParams G, 
         for (int c = 0; c < 9; ++c) q[c] = make_double2(o[2 * c], o[2 * c + 1]);
         if (pold >= 0 && xib_old)
             for (int c = 0; c < 3; ++c) {
-                xib_old[tp.sw * pold + c] = g.xo[c];
-                if (tp.sw == 6) xib_old[tp.sw * pold + 3 + c] = g.xro[c];
+                xib_old[(Roll ? 6 : 3) * pold + c] = g.xo[c];
+                if (Roll) xib_old[(Roll ? 6 : 3) * pold + 3 + c] = g.xro[c];
             }
         gmu = g.mu;
         gfer = g.fer;
@@ -275,26 +263,37 @@ __global__ void __launch_bounds__(kBlock) k_pairs_vjp(DevParams P, BoxParams G, 
             s0 += red[q][0];
             s1 += red[q][1];
         }
-        atomicAdd(theta_b, s0);
-        atomicAdd(theta_b + 1, s1);
+        theta_part[2 * blockIdx.x] = s0;
+        theta_part[2 * blockIdx.x + 1] = s1;
     }
 }
 
-// Per particle: the cotangents of its listed codes added in list order to its adjoints (the
-// list positions cleared for the next evaluation); the codes of the overflow list, beyond full
-// lists, are added by the same grid with FP64 atomics, and so are the list sums of the
-// particles that overflowed, whose adjoints have more than one writer.  k_integrate_vjp
-// clears the overflow count afterwards.
+// Per particle: the cotangents of its listed codes added to its adjoints (the list positions
+// cleared for the next evaluation), kSumLanes lanes to a particle, each over its share of the
+// list, their sums combined in a fixed order (one lane to a particle waited for code after code:
+// 10.4 us at N = 2000, 4.8 us so; at N = 50k, where the 144 B of every pair bound it, 15 us both);
+// the codes of the overflow list, beyond full lists, are added
+// by the same grid with FP64 atomics, and so are the list sums of the particles that overflowed,
+// whose adjoints have more than one writer.  k_integrate_vjp clears the overflow count
+// afterwards.  The first workgroup adds the np partial parameter gradients to theta.
+constexpr int kSumLanes = 4;
+
 __global__ void __launch_bounds__(kBlock) k_pairs_vjp_sum(int N, int cap, int *__restrict__ pos,
                                                           const int *__restrict__ adj,
                                                           const unsigned *__restrict__ ovf_n,
                                                           const int2 *__restrict__ ovf,
                                                           const double *__restrict__ gpair, double *__restrict__ ax,
-                                                          double *__restrict__ au, double *__restrict__ aw)
+                                                          double *__restrict__ au, double *__restrict__ aw,
+                                                          const double *__restrict__ theta_part, int np,
+                                                          double *__restrict__ theta)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double red[kBlock / 64][2];
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = t / kSumLanes, sub = t % kSumLanes;
     const unsigned no = *ovf_n;
-    for (unsigned e = p; e < no; e += gridDim.x * blockDim.x) {
+    const bool on = p < N;
+    const int m = on ? pos[p] : 0;
+    for (unsigned e = t; e < no; e += gridDim.x * blockDim.x) {
         const int2 v = ovf[e];
         const double *g = gpair + 18LL * (v.y >> 1) + 9 * (v.y & 1);
         for (int c = 0; c < 3; ++c) {
@@ -303,29 +302,52 @@ __global__ void __launch_bounds__(kBlock) k_pairs_vjp_sum(int N, int cap, int *_
             atomicAdd(&aw[3LL * v.x + c], g[6 + c]);
         }
     }
-    if (p >= N) return;
-    const int m = pos[p];
-    pos[p] = 0;
     const int n = m < cap ? m : cap;
     double s[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const int *lst = adj + (long long)p * cap;
-    for (int e = 0; e < n; ++e) {
+    const int *lst = adj + (long long)(on ? p : 0) * cap;
+    for (int e = sub; e < n; e += kSumLanes) {
         const int code = lst[e];
         const double *g = gpair + 18LL * (code >> 1) + 9 * (code & 1);
 #pragma unroll
         for (int c = 0; c < 9; ++c) s[c] += g[c];
     }
-    if (m > cap) {
-        for (int c = 0; c < 3; ++c) {
-            atomicAdd(&ax[3LL * p + c], s[c]);
-            atomicAdd(&au[3LL * p + c], s[3 + c]);
-            atomicAdd(&aw[3LL * p + c], s[6 + c]);
+#pragma unroll
+    for (int o = 1; o < kSumLanes; o <<= 1)
+#pragma unroll
+        for (int c = 0; c < 9; ++c) s[c] += __shfl_xor(s[c], o, 64);
+    if (on && sub == 0) {
+        pos[p] = 0;
+        if (m > cap) {
+            for (int c = 0; c < 3; ++c) {
+                atomicAdd(&ax[3LL * p + c], s[c]);
+                atomicAdd(&au[3LL * p + c], s[3 + c]);
+                atomicAdd(&aw[3LL * p + c], s[6 + c]);
+            }
+        } else {
+            for (int c = 0; c < 3; ++c) {
+                ax[3LL * p + c] += s[c];
+                au[3LL * p + c] += s[3 + c];
+                aw[3LL * p + c] += s[6 + c];
+            }
         }
-    } else {
-        for (int c = 0; c < 3; ++c) {
-            ax[3LL * p + c] += s[c];
-            au[3LL * p + c] += s[3 + c];
-            aw[3LL * p + c] += s[6 + c];
+    }
+    if (blockIdx.x == 0) {
+        double a = 0.0, b = 0.0;
+        for (int q = threadIdx.x; q < np; q += kBlock) {
+            a += theta_part[2 * q];
+            b += theta_part[2 * q + 1];
+        }
+        a = warp_sum(a);
+        b = warp_sum(b);
+        if ((threadIdx.x & 63) == 0) {
+            red[threadIdx.x >> 6][0] = a;
+            red[threadIdx.x >> 6][1] = b;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double v = 0.0;
+            for (int w = 0; w < kBlock / 64; ++w) v += red[w][threadIdx.x];
+            theta[threadIdx.x] += v;
         }
     }
 }
@@ -357,7 +379,7 @@ __global__ void __launch_bounds__(kBlock) k_integrate_vjp(DevParams P, double gd
     // of its earlier history (the buffer this step's pair VJP has finished reading)
     if (zcnt) {
         double *r = zbuf + (long long)p * M * sw;
-        const int n = sw * zcnt[p];
+        const int n = sw * (zcnt[p] < M ? zcnt[p] : M);
         for (int k = 0; k < n; ++k) r[k] = 0.0;
     }
     const double a = rad[p];

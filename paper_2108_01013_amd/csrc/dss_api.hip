@@ -908,7 +908,6 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
         HIPTRY(hipGetLastError());
         h->vel_is_half = false;
         h->own_total = false;
-        h->own_total = false;
         return DSS_OK;
     }
     launch_sort(h, h->vel_is_half, advance, advance, nullptr);
@@ -2063,6 +2062,9 @@ dss_status dss_get_box_info(dss_handle *h, int32_t box, dss_box_info *info)
 // ======================================================================================
 namespace {
 
+// Largest tape of an adjoint run that is recorded whole (N = 50k: about 30 steps).
+constexpr size_t kTapeBytes = size_t(2) << 30;
+
 // Device copy of everything a time step, or an evaluation in place, reads from the
 // previous one (including cell_start, which must match the sorted order of the records).
 struct Snapshot {
@@ -2209,14 +2211,11 @@ dss_status tape_alloc(dss_handle *h, TapeEntry &t)
 dss_status tape_rows(dss_handle *h, TapeEntry &t, bool cleared = false)
 {
     const int N = (int)h->N, M = h->P.M;
-    const int grid = (N + kBlock - 1) / kBlock;
     if (!cleared) HIPTRY(hipMemsetAsync(t.ccnt, 0, N * sizeof(int), h->stream));
     const int sw = stretch_width(h);
     auto fill = sw == 6 ? k_canon_fill<6> : k_canon_fill<3>;
-    auto sort = sw == 6 ? k_canon_sort<6> : k_canon_sort<3>;
-    hipLaunchKernelGGL(fill, dim3(grid), dim3(kBlock), 0, h->stream, N, M, h->hown[h->hh], h->hkey[h->hh],
+    hipLaunchKernelGGL(fill, dim3((unsigned)((4LL * N + kBlock - 1) / kBlock)), dim3(kBlock), 0, h->stream, N, M, h->hown[h->hh], h->hkey[h->hh],
                        h->hxi[h->hh], h->hxr[h->hh], h->hcnt[h->hh], t.ckey, t.cxi, t.ccnt, h->clk);
-    hipLaunchKernelGGL(sort, dim3(grid), dim3(kBlock), 0, h->stream, N, M, t.ckey, t.cxi, t.ccnt);
     HIPTRY(hipGetLastError());
     return DSS_OK;
 }
@@ -2315,7 +2314,8 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
                                       "dss_set_particles or dss_compute_forces");
     if (n_steps < 1 || stress_every < 1 || ckpt_every < 1 || !weight)
         return fail(h, DSS_ERR_ARG, "n_steps, stress_every, ckpt_every must be >= 1 and weight non-null");
-    const int64_t n0 = h->step, K = n_steps, C = ckpt_every;
+    const int64_t n0 = h->step, K = n_steps;
+    int64_t C = std::min(ckpt_every, n_steps);
     const int64_t first = ((n0 / stress_every) + 1) * stress_every;
     if (first > n0 + K) return fail(h, DSS_ERR_ARG, "no stress sample in the run (n_steps < stress_every)");
     const int64_t ns = (n0 + K - first) / stress_every + 1;
@@ -2336,7 +2336,11 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
             h->P.pair_cap = cap;
         }
     }
-    const int64_t nck = (K + C - 1) / C;
+    // a run whose tape fits kTapeBytes is recorded as it runs, in one segment without checkpoints;
+    // a longer one runs forward with checkpoints, and each segment runs again to be recorded
+    const size_t entry = 9 * (size_t)N * sizeof(double) + 2 * (size_t)h->P.pair_cap * sizeof(int) +
+                         (size_t)N * (M + 1) * sizeof(int) + stretch_width(h) * (size_t)N * M * sizeof(double);
+    bool whole = (size_t)(K + 1) <= kTapeBytes / entry;
     {
         // the workspace of the last call serves when its shapes are these
         const int64_t key[8] = {N, M, h->ncell_total, h->hxr[h->hh] ? 1 : 0, h->P.pair_cap, stretch_width(h), 0, 0};
@@ -2348,7 +2352,52 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     }
     AdjointScratch &W = *h->adj_ws;
     W.bufs.rewind();
-    if ((int64_t)W.ck.size() < nck) W.ck.resize(nck);
+    const size_t n3 = 3 * (size_t)N;
+    const int sw = stretch_width(h);
+    double *xb, *ub, *wb, *ax, *au, *aw, *Fb, *Tb, *Fb2, *Tb2, *theta, *rad, *Sb, *xibA, *xibB;
+    int *bkey, *bcnt;
+    unsigned long long *slots;
+    HIPTRY(W.get(&slots, (size_t)(whole ? K : C) + 1));
+    HIPTRY(W.get(&xb, n3)); HIPTRY(W.get(&ub, n3)); HIPTRY(W.get(&wb, n3));
+    HIPTRY(W.get(&ax, n3)); HIPTRY(W.get(&au, n3)); HIPTRY(W.get(&aw, n3));
+    HIPTRY(W.get(&Fb, n3)); HIPTRY(W.get(&Tb, n3)); HIPTRY(W.get(&Fb2, n3)); HIPTRY(W.get(&Tb2, n3));
+    HIPTRY(W.get(&theta, 2)); HIPTRY(W.get(&rad, N)); HIPTRY(W.get(&Sb, 9));
+    HIPTRY(W.get(&xibA, sw * (size_t)N * M)); HIPTRY(W.get(&xibB, sw * (size_t)N * M));
+    HIPTRY(W.get(&bkey, (size_t)N * M)); HIPTRY(W.get(&bcnt, N));
+    // the recorded pairs by particle (per evaluation): lists of acap codes, their fill counts,
+    // and the overflow list of the codes beyond a full list (at most every code)
+    const int acap = h->tune.adj_cap > 0 ? h->tune.adj_cap : kAdjCap;
+    const size_t ncode = 2 * (size_t)std::max<int64_t>(h->P.pair_cap, 1);
+    int *apos = nullptr, *aadj = nullptr;
+    unsigned *aovf_n = nullptr;
+    int2 *aovf = nullptr;
+    HIPTRY(W.get(&apos, (size_t)N)); HIPTRY(W.get(&aadj, (size_t)N * acap));
+    HIPTRY(W.get(&aovf_n, 1)); HIPTRY(W.get(&aovf, ncode));
+    double *agrad = nullptr;  // 18 cotangents per recorded pair
+    HIPTRY(W.get(&agrad, 18 * (size_t)std::max<int64_t>(h->P.pair_cap, 1)));
+    double *tpart = nullptr;  // parameter gradients of each k_pairs_vjp workgroup
+    HIPTRY(W.get(&tpart, 2 * (size_t)((std::max<int64_t>(h->P.pair_cap, 1) + kBlock - 1) / kBlock)));
+    // tape entries 0 .. n
+    auto tape_entries = [&](int64_t n) {
+        if ((int64_t)W.tape.size() < n + 1) W.tape.resize(n + 1);
+        for (int64_t k = 0; k <= n; ++k) {
+            if (W.tape[k].cxi) continue;  // allocated last: the entry is whole
+            W.tape[k].release();
+            const dss_status q = tape_alloc(h, W.tape[k]);
+            if (q) return q;
+        }
+        return DSS_OK;
+    };
+    if (whole && tape_entries(K) != DSS_OK) {  // not the memory for it: checkpoints after all
+        (void)hipGetLastError();
+        for (auto &t : W.tape) t.release();
+        whole = false;
+    }
+    if (whole) C = K;
+    const int64_t nck = whole ? 1 : (K + C - 1) / C;
+    s = whole ? DSS_OK : tape_entries(C);
+    if (s) return s;
+    if (!whole && (int64_t)W.ck.size() < nck) W.ck.resize(nck);
 
     // ---------------- forward run with checkpoints and stress samples
     if (ns > h->sample_cap_alloc) {
@@ -2370,7 +2419,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     const unsigned fwd_timed = h->timing & ~((1u << 5) | (1u << 6));
     const bool graphs = h->tune.graph && !h->graph_broken && fwd_timed == 0 && !h->P.record_pairs;
     const StepRuns R(K, stress_every, h->step, 0);
-    for (int64_t k = 0; k < K;) {
+    for (int64_t k = whole ? K : 0; k < K;) {
         if (k % C == 0) {
             s = snap_save(h, W.ck[k / C]);
             if (s) return s;
@@ -2384,39 +2433,21 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
         k += n;
         if (s) return s;
     }
-    double last[9], mean[9];
-    int64_t nsr = 0;
-    s = dss_read_stress_batch(h, last, mean, &nsr);
-    if (s) return s;
     double Jv = 0.0;
-    for (int k = 0; k < 9; ++k) Jv += weight[k] * mean[k];
-    s = snap_save(h, W.fin);
-    if (s) return s;
+    auto read_J = [&]() {
+        double last[9], mean[9];
+        int64_t nsr = 0;
+        const dss_status q = dss_read_stress_batch(h, last, mean, &nsr);  // synchronises
+        for (int k = 0; q == DSS_OK && k < 9; ++k) Jv += weight[k] * mean[k];
+        return q;
+    };
+    if (!whole) {
+        s = snap_save(h, W.fin);
+        if (!s) s = read_J();
+        if (s) return s;
+    }
 
     // ---------------- reverse sweep
-    const size_t n3 = 3 * (size_t)N;
-    double *xb, *ub, *wb, *ax, *au, *aw, *Fb, *Tb, *Fb2, *Tb2, *theta, *rad, *Sb, *xibA, *xibB;
-    int *bkey, *bcnt;
-    unsigned long long *slots;
-    HIPTRY(W.get(&slots, (size_t)C + 1));
-    HIPTRY(W.get(&xb, n3)); HIPTRY(W.get(&ub, n3)); HIPTRY(W.get(&wb, n3));
-    HIPTRY(W.get(&ax, n3)); HIPTRY(W.get(&au, n3)); HIPTRY(W.get(&aw, n3));
-    HIPTRY(W.get(&Fb, n3)); HIPTRY(W.get(&Tb, n3)); HIPTRY(W.get(&Fb2, n3)); HIPTRY(W.get(&Tb2, n3));
-    HIPTRY(W.get(&theta, 2)); HIPTRY(W.get(&rad, N)); HIPTRY(W.get(&Sb, 9));
-    const int sw = stretch_width(h);
-    HIPTRY(W.get(&xibA, sw * (size_t)N * M)); HIPTRY(W.get(&xibB, sw * (size_t)N * M));
-    HIPTRY(W.get(&bkey, (size_t)N * M)); HIPTRY(W.get(&bcnt, N));
-    // the recorded pairs by particle (per evaluation): lists of acap codes, their fill counts,
-    // and the overflow list of the codes beyond a full list (at most every code)
-    const int acap = h->tune.adj_cap > 0 ? h->tune.adj_cap : kAdjCap;
-    const size_t ncode = 2 * (size_t)std::max<int64_t>(h->P.pair_cap, 1);
-    int *apos = nullptr, *aadj = nullptr;
-    unsigned *aovf_n = nullptr;
-    int2 *aovf = nullptr;
-    HIPTRY(W.get(&apos, (size_t)N)); HIPTRY(W.get(&aadj, (size_t)N * acap));
-    HIPTRY(W.get(&aovf_n, 1)); HIPTRY(W.get(&aovf, ncode));
-    double *agrad = nullptr;  // 18 cotangents per recorded pair
-    HIPTRY(W.get(&agrad, 18 * (size_t)std::max<int64_t>(h->P.pair_cap, 1)));
     HIPTRY(hipMemsetAsync(apos, 0, (size_t)N * sizeof(int), h->stream));
     HIPTRY(hipMemsetAsync(aovf_n, 0, sizeof(unsigned), h->stream));
     double *zero_list[] = {xb, ub, wb, ax, au, aw, Fb, Tb, Fb2, Tb2};
@@ -2431,13 +2462,6 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
         HIPTRY(hipMemcpyAsync(Sb, sb, sizeof(sb), hipMemcpyHostToDevice, h->stream));
     }
     hipLaunchKernelGGL(k_rad_by_id, dim3(grid), dim3(kBlock), 0, h->stream, N, h->pa[h->cur], h->omg[h->cur], rad);
-    if ((int64_t)W.tape.size() < C + 1) W.tape.resize(C + 1);
-    for (int64_t k = 0; k <= C; ++k) {
-        if (W.tape[k].cxi) continue;  // allocated last: the entry is whole
-        W.tape[k].release();
-        s = tape_alloc(h, W.tape[k]);
-        if (s) return s;
-    }
     DevParams Prec = h->P;
     Prec.record_pairs = 1;
     const BoxParams G = h->boxes[0];
@@ -2449,13 +2473,15 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
         const int pg = std::max(1, (np + kBlock - 1) / kBlock);
         {
             TimedLaunch tl(h, 5);
-            hipExtLaunchKernelGGL(k_pairs_vjp, dim3(pg), dim3(kBlock), 0, h->stream, tl.e0, tl.e1, 0, Prec, G,
-                                  (long long)n, np, tp, xin, xout, Fb, Tb, sb, agrad, theta, acap, apos, aadj, aovf_n,
+            auto kernel = sw == 6 ? (sb ? k_pairs_vjp<true, true> : k_pairs_vjp<true, false>)
+                                  : (sb ? k_pairs_vjp<false, true> : k_pairs_vjp<false, false>);
+            hipExtLaunchKernelGGL(kernel, dim3(pg), dim3(kBlock), 0, h->stream, tl.e0, tl.e1, 0, Prec, G,
+                                  (long long)n, np, tp, xin, xout, Fb, Tb, sb, agrad, tpart, acap, apos, aadj, aovf_n,
                                   aovf);
         }
-        hipLaunchKernelGGL(k_pairs_vjp_sum, dim3(grid), dim3(kBlock), 0, h->stream, (int)N, acap, apos,
-                           (const int *)aadj, (const unsigned *)aovf_n, (const int2 *)aovf, (const double *)agrad,
-                           ax, au, aw);
+        hipLaunchKernelGGL(k_pairs_vjp_sum, dim3((unsigned)(((int64_t)N * kSumLanes + kBlock - 1) / kBlock)), dim3(kBlock),
+                           0, h->stream, (int)N, acap, apos, (const int *)aadj, (const unsigned *)aovf_n,
+                           (const int2 *)aovf, (const double *)agrad, ax, au, aw, (const double *)tpart, pg, theta);
         return hipGetLastError();
     };
     double *xib_in = xibA, *xib_out = xibB;
@@ -2464,7 +2490,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     for (int64_t seg = nck - 1; seg >= 0; --seg) {
         const int64_t s0 = n0 + seg * C;
         const int64_t len = std::min<int64_t>(C, K - seg * C);
-        s = snap_restore(h, W.ck[seg]);
+        if (!whole) s = snap_restore(h, W.ck[seg]);
         if (s) break;
         s = tape_rows(h, W.tape[0]);
         if (s) break;
@@ -2484,7 +2510,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
             h->tape_u = prev ? W.tape[k - 1].u : nullptr;
             h->tape_w = prev ? W.tape[k - 1].w : nullptr;
             h->tape_zero = W.tape[k].ccnt;  // the counts of this step's canonical rows
-            s = evaluate(h, EVAL_STEP, false);
+            s = evaluate(h, EVAL_STEP, whole && R.finish_at(k - 1));
             h->tape_x = h->tape_u = h->tape_w = nullptr;
             h->tape_zero = nullptr;
             if (s) break;
@@ -2495,6 +2521,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
         s = tape_state(h, W.tape[len]);  // the segment's last evaluation
         if (s) break;
         s = tape_counts(h, W.tape, slots, seg == 0 ? 0 : 1, (int)len);
+        if (!s && whole) s = read_J();
         if (s) break;
         if (seg < nck - 1) {
             // stretch adjoints at the segment boundary: rows of the later segment -> this one
@@ -2510,7 +2537,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
             if (k == len)
                 hipLaunchKernelGGL(sw == 6 ? k_canon_zero<6> : k_canon_zero<3>, dim3(grid), dim3(kBlock), 0, h->stream,
                                    N, M, T0.ccnt, xib_out);
-            VjpTape tp{T1.pairs, T1.x, T1.u, T1.w, rad, T0.ckey, T0.ccnt, T0.cxi, T1.ckey, T1.ccnt, sw};
+            VjpTape tp{T1.pairs, T1.x, T1.u, T1.w, rad, T0.ckey, T0.ccnt, T0.cxi, T1.ckey, T1.ccnt};
             const bool sampled = n >= first && (n - first) % stress_every == 0;
             HIPTRY(pairs_vjp(T1, tp, n, xib_in, xib_out, sampled ? Sb : (const double *)nullptr));
             const double c = (n - 1 == n0) ? 0.5 : 1.0;
@@ -2535,7 +2562,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     {
         // the evaluation at the initial state; the stretch of the initial history is held fixed
         const TapeEntry &T0 = W.tape[0];
-        VjpTape tp{T0.pairs, T0.x, T0.u, T0.w, rad, T0.ckey, T0.ccnt, T0.cxi, nullptr, nullptr, sw};
+        VjpTape tp{T0.pairs, T0.x, T0.u, T0.w, rad, T0.ckey, T0.ccnt, T0.cxi, nullptr, nullptr};
         HIPTRY(pairs_vjp(T0, tp, n0, (const double *)nullptr, (double *)nullptr, (const double *)nullptr));
         hipLaunchKernelGGL(k_integrate_vjp, dim3(grid), dim3(kBlock), 0, h->stream, Prec, G.gd, N, 0.0, 1, rad, Fb, Tb,
                            ax, au, aw, xb, ub, wb, Fb2, Tb2, aovf_n, (const int *)nullptr, (double *)nullptr, M, sw);
@@ -2551,7 +2578,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     double th[2];
     HIPTRY(hipMemcpyAsync(th, theta, sizeof(th), hipMemcpyDeviceToHost, h->stream));
     // leave the handle at the end of the run, as dss_step would
-    s = snap_restore(h, W.fin);
+    if (!whole) s = snap_restore(h, W.fin);
     if (s) return s;
     HIPTRY(hipStreamSynchronize(h->stream));
     if (J) *J = Jv;
