@@ -18,6 +18,10 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-munsafe-fp-atomics",                                   # native global/LDS FP64 atomic add
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # no hoisting of instructions out of loops after selection: it moves the literal constants of
+    # log and exp into registers for the whole loop, and the pair kernels spill (k_list, FP64, a
+    # stress step at N = 100k 37.5 us with it, 27.9 without; at N = 500k 166 and 107)
+    "-mllvm", "-disable-machine-licm",
     "-Wall", "-Wno-unused-function",
 ]
 
