@@ -280,13 +280,13 @@ void destroy_graphs(dss_handle *h)
     h->run_graphs.clear();
 }
 
-void free_lattice(dss_handle *h)
+void free_lists(dss_handle *h)
 {
     auto F = [](void *p) {
         if (p) (void)hipFree(p);
     };
-    destroy_graphs(h);
-    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross); F(h->lof); F(h->lown); F(h->lfar); F(h->lfar_n); F(h->lfar_f);
+    F(h->lblocks); F(h->lent); F(h->lxi); F(h->lxr); F(h->ldsum); F(h->lpartials); F(h->ln); F(h->lcross);
+    F(h->lof); F(h->lown); F(h->lfar); F(h->lfar_n); F(h->lfar_f);
     F(h->lrec[0]); F(h->lrec[1]);
     h->lblocks = nullptr;
     h->lent = nullptr;
@@ -296,6 +296,15 @@ void free_lattice(dss_handle *h)
     h->lfar = h->lfar_n = nullptr;
     h->lfar_f = nullptr;
     h->lrec[0] = h->lrec[1] = nullptr;
+}
+
+void free_lattice(dss_handle *h)
+{
+    auto F = [](void *p) {
+        if (p) (void)hipFree(p);
+    };
+    destroy_graphs(h);
+    free_lists(h);
     F(h->count); F(h->cell_start); F(h->tile_sum); F(h->cs_local); F(h->partials); F(h->d_boxes); F(h->d_row_box);
     h->cs_local = nullptr;
     h->count = h->cell_start = h->tile_sum = h->d_row_box = nullptr;
@@ -1101,6 +1110,16 @@ dss_status setup_lists(dss_handle *h)
     return DSS_OK;
 }
 
+// Without the memory for them the steps are full steps.
+void setup_lists_or_none(dss_handle *h)
+{
+    if (setup_lists(h) == DSS_OK) return;
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(h->stream);
+    free_lists(h);
+    h->list_window = 0;
+}
+
 // Stress partial records of a list step: one per block, then those of the far pairs' pass.
 int list_records(const dss_handle *h) { return h->list_blocks + h->ec_grid; }
 
@@ -1313,9 +1332,12 @@ dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
 {
     const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
     dss_status s = DSS_OK;
-    if (lists_on(h) && n_steps >= kListWindowMin) s = setup_lists(h);
-    if (s) return s;
-    const StepRuns R(n_steps, stress_every, h->step, lists_on(h) ? h->list_window : 0);
+    // a caller's capture takes full steps: the host cannot take a stopped window of its replays again
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (n_steps >= kListWindowMin && hipStreamIsCapturing(h->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    const bool windows = capture == hipStreamCaptureStatusNone && n_steps >= kListWindowMin && lists_on(h);
+    if (windows) setup_lists_or_none(h);
+    const StepRuns R(n_steps, stress_every, h->step, windows && lists_on(h) ? h->list_window : 0);
     for (int64_t k = 0; k < n_steps;) {
         bool lists;
         int n = R.length_at(k, lists);
@@ -1791,8 +1813,7 @@ dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_ever
     if (!graphs || h->tune_pending) return DSS_OK;  // direct launches, or a lattice change comes first
     // walk the call's runs as dss_step will, capturing the graphs it does not have yet; only
     // the handle's bookkeeping of the buffers advances, and it is put back
-    if (lists_on(h) && n_steps >= kListWindowMin) s = setup_lists(h);
-    if (s) return s;
+    if (lists_on(h) && n_steps >= kListWindowMin) setup_lists_or_none(h);
     const int cur = h->cur, hh = h->hh;
     const bool vih = h->vel_is_half, total = h->own_total;
     const int64_t step = h->step;
