@@ -242,7 +242,12 @@ dss_status dss_compute_forces(dss_handle *h);
  * are returned by dss_read_stress.  The stress and the pair and contact counters are
  * summed only on those steps and on the last step of the call (the other steps skip the
  * stresslet; their forces, torques and history are the same).  Does not synchronise
- * unless sync != 0 (then device error flags are checked). */
+ * unless sync != 0 (then device error flags are checked).
+ * Runs of 5 and more steps are taken in windows of up to 64 on pair lists (pairs inside the
+ * cutoff plus a margin, tested at every step's positions: the pair sets are those of a search
+ * at every step).  A window that a particle would leave the margin in stops on the device, and
+ * its steps are taken again from its start; after a call with sync = 0 that happens in the next
+ * call on the handle, so a caller that times or orders work by the stream alone passes sync = 1. */
 dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sync);
 
 /* Capture, without running anything, the HIP graphs that dss_step(h, n_steps, stress_every, .)
@@ -314,8 +319,9 @@ dss_status dss_get_box_info(dss_handle *h, int32_t box, dss_box_info *info);
  * a segment of ckpt_every recorded steps).  A run whose recorded steps fit 2 GiB together, and
  * the device's free memory, is recorded as it runs, without checkpoints and second runs.  This
  * device workspace stays with the handle and serves the next call of the same particle count,
- * lattice and recording capacity without allocating; dss_set_particles and dss_destroy free it.  On return the handle stands at the end of the
- * run, as after dss_step(h, n_steps, stress_every, 1).  Requires a single-box handle whose
+ * lattice and recording capacity without allocating; dss_set_particles and dss_destroy free
+ * it.  On return the handle stands at the end of the run, as after dss_step(h, n_steps,
+ * stress_every, 1).  Requires a single-box handle whose
  * forces were evaluated at u^n (right after dss_set_particles or dss_compute_forces: else
  * DSS_ERR_STATE) and at least one stress sample in the run (else DSS_ERR_ARG).  Takes the
  * electro-chemical ranges (which pair is inside which range is held fixed) and rolling
@@ -343,8 +349,9 @@ dss_status dss_load_state(dss_handle *h, const void *blob, size_t bytes);
  * the kernels selected by enable (bit k: kernel k; -1: all; 0: off); every call starts a
  * new accumulation.  dss_get_timing synchronises and returns, for kernel k (0 predict or
  * velocity completion, 1 scan, 2 scatter, 3 pairs, 4 finish, 5 pair adjoint, 6 integrator
- * adjoint, 7 electro-chemical pairs beyond the lubrication list; with size-class stencils 3
- * is their one pair kernel), the summed duration in ms and the number of timed launches. */
+ * adjoint, 7 electro-chemical pairs beyond the lubrication list, 8 the searches at the start
+ * of a window of steps; with size-class stencils 3 is their one pair kernel, and within a
+ * window 3 and 7 are the evaluations of the pair lists), the summed duration in ms and the number of timed launches. */
 dss_status dss_set_timing(dss_handle *h, int enable);
 dss_status dss_get_timing(dss_handle *h, int kernel, double *total_ms, int64_t *launches);
 
