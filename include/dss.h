@@ -247,7 +247,10 @@ dss_status dss_compute_forces(dss_handle *h);
  * cutoff plus a margin, tested at every step's positions: the pair sets are those of a search
  * at every step).  A window that a particle would leave the margin in stops on the device, and
  * its steps are taken again from its start; after a call with sync = 0 that happens in the next
- * call on the handle, so a caller that times or orders work by the stream alone passes sync = 1. */
+ * call on the handle, so a caller that times or orders work by the stream alone passes sync = 1.
+ * A caller that captures its stream (graph = 0, sync = 0, an even number of steps, so that a replay
+ * ends in the buffers it began in) captures full steps, and the handle takes only full steps
+ * from then on, until a new lattice or new particles end the use of what was captured. */
 dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sync);
 
 /* Capture, without running anything, the HIP graphs that dss_step(h, n_steps, stress_every, .)

@@ -241,6 +241,12 @@ struct dss_handle {
     };
     std::vector<Run> runs;
     int64_t call_every = 0;
+    // a stream beside the caller's, which waits (by event) for the last runs of a call that did not
+    hipStream_t side = nullptr;
+    hipEvent_t tail = nullptr;
+    // a caller has captured time steps: its replays run without the host, on these buffers and
+    // with the force records of a full step, so no window may come between them
+    bool captured = false;
 };
 
 namespace {
@@ -305,6 +311,7 @@ void free_lattice(dss_handle *h)
     };
     destroy_graphs(h);
     free_lists(h);
+    h->captured = false;  // what was captured held the buffers freed here
     F(h->count); F(h->cell_start); F(h->tile_sum); F(h->cs_local); F(h->partials); F(h->d_boxes); F(h->d_row_box);
     h->cs_local = nullptr;
     h->count = h->cell_start = h->tile_sum = h->d_row_box = nullptr;
@@ -999,11 +1006,11 @@ void commit_run(dss_handle *h, int n, bool lists)
 // Whether the time steps of the handle can go as windows on pair lists: the row tiles or the
 // size-class stencils, with the electro-chemical ranges where the far pairs have a pass of their own
 // (else the whole pair set, more than a list holds, is on the lattice), no recording of pairs, no
-// wavy shear.
+// wavy shear, no steps captured by a caller.
 bool lists_on(const dss_handle *h)
 {
     return h->list_window >= kListWindowMin && (h->tune.tiled || h->P.sized) && (!h->P.ec || h->P.ec_split) && !h->P.record_pairs &&
-           h->P.wave_amp == 0.0;
+           h->P.wave_amp == 0.0 && !h->captured;
 }
 
 // Blocks of the pair lists and the memory of a window, on the handle's first window.  A block
@@ -1332,10 +1339,7 @@ dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
 {
     const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
     dss_status s = DSS_OK;
-    // a caller's capture takes full steps: the host cannot take a stopped window of its replays again
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (n_steps >= kListWindowMin && hipStreamIsCapturing(h->stream, &capture) != hipSuccess) (void)hipGetLastError();
-    const bool windows = capture == hipStreamCaptureStatusNone && n_steps >= kListWindowMin && lists_on(h);
+    const bool windows = n_steps >= kListWindowMin && lists_on(h);
     if (windows) setup_lists_or_none(h);
     const StepRuns R(n_steps, stress_every, h->step, windows && lists_on(h) ? h->list_window : 0);
     for (int64_t k = 0; k < n_steps;) {
@@ -1397,6 +1401,45 @@ dss_status settle(dss_handle *h, DevClock *out)
         dss_status s = enqueue_steps(h, target - h->step, h->call_every);
         if (s) return s;
     }
+}
+
+// The partner records as zeros after a window on pair lists (the own records hold the whole force):
+// for snapshots and captured steps, which take every record.
+dss_status whole_records(dss_handle *h)
+{
+    if (h->own_total) HIPTRY(hipMemsetAsync(h->ft_nb, 0, 24 * h->N * sizeof(double), h->stream));
+    h->own_total = false;
+    return DSS_OK;
+}
+
+dss_status side_stream(dss_handle *h)
+{
+    if (!h->side) HIPTRY(hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking));
+    return DSS_OK;
+}
+
+// A caller captures the stream: its steps are full steps, from a state that a replay finds as a full
+// step leaves it.  What is under way is waited for and completed, and the records of a window
+// made whole, beside the capture, on the side stream (every replay comes after this; a stream
+// that is captured, and an event of it, cannot be waited for).
+dss_status ready_for_capture(dss_handle *h)
+{
+    h->captured = true;
+    if (h->runs.empty() && !h->own_total) return DSS_OK;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HIPTRY(hipThreadExchangeStreamCaptureMode(&mode));
+    dss_status s = side_stream(h);
+    if (!s) {
+        const hipStream_t of_caller = h->stream;
+        h->stream = h->side;
+        if (!h->runs.empty()) s = settle(h);
+        if (!s) s = whole_records(h);
+        const hipError_t e = hipStreamSynchronize(h->side);
+        h->stream = of_caller;
+        if (!s && e != hipSuccess) s = fail(h, DSS_ERR_HIP, hipGetErrorString(e));
+    }
+    HIPTRY(hipThreadExchangeStreamCaptureMode(&mode));
+    return s;
 }
 
 }  // namespace
@@ -1494,6 +1537,8 @@ void dss_destroy(dss_handle *h)
     if (!h) return;
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     for (auto e : h->ev_pool) (void)hipEventDestroy(e);
+    if (h->tail) (void)hipEventDestroy(h->tail);
+    if (h->side) (void)hipStreamDestroy(h->side);
     free_all(h);
     if (h->own_stream) (void)hipStreamDestroy(h->stream);
     delete h;
@@ -1763,6 +1808,12 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
     dss_status s = require_loaded(h, false);
     if (s) return s;
     if (n_steps < 0 || stress_every < 0) return fail(h, DSS_ERR_ARG, "negative n_steps or stress_every");
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture == hipStreamCaptureStatusActive) {
+        s = ready_for_capture(h);
+        if (s) return s;
+    }
     // a new lattice, larger sample buffers and a long queue of runs wait for the steps under way
     if (!h->runs.empty() && (h->tune_pending || h->runs.size() >= kMaxOpenRuns ||
                              (stress_every > 0 && n_steps / stress_every + 1 > h->sample_cap_alloc))) {
@@ -1801,6 +1852,13 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
     s = enqueue_steps(h, n_steps, stress_every);
     if (s) return s;
     if (sync) return check_flags(h);
+    if (!h->runs.empty()) {
+        s = side_stream(h);
+        if (s) return s;
+        if (!h->tail) HIPTRY(hipEventCreateWithFlags(&h->tail, hipEventDisableTiming));
+        HIPTRY(hipEventRecord(h->tail, h->stream));
+        HIPTRY(hipStreamWaitEvent(h->side, h->tail, 0));
+    }
     return DSS_OK;
 }
 
@@ -2115,15 +2173,6 @@ struct Snapshot {
         *this = Snapshot{};
     }
 };
-
-// The partner records as zeros after a window on pair lists (the own records hold the whole force):
-// for snapshots, which carry every record.
-dss_status whole_records(dss_handle *h)
-{
-    if (h->own_total) HIPTRY(hipMemsetAsync(h->ft_nb, 0, 24 * h->N * sizeof(double), h->stream));
-    h->own_total = false;
-    return DSS_OK;
-}
 
 dss_status snap_save(dss_handle *h, Snapshot &s)
 {
@@ -2722,7 +2771,10 @@ dss_status dss_load_state(dss_handle *h, const void *blob, size_t bytes)
     }
     h->cur = 0;
     h->hh = 0;
-    h->step = hd.step;
+    // the clock's index: the host's stays behind where a caller replayed captured steps
+    DevClock c;
+    HIPTRY(hipMemcpy(&c, h->clk, sizeof(c), hipMemcpyDeviceToHost));
+    h->step = c.step;
     h->vel_is_half = hd.vel_is_half != 0;
     h->own_total = false;
     h->listable = false;  // the snapshot does not say; the next full step settles it
