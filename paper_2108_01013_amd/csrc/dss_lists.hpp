@@ -29,7 +29,10 @@
 // history row or a force out of range) sets a flag in
 // the clock's error word, every later kernel of the stream's queue then returns at once, and the
 // committed state at the window's start, which a window writes only in its last list step, is
-// where the host resumes (dss_api.hip, settle).
+// where the host resumes (dss_api.hip, settle).  The kernels that set the flag run beside workgroups of
+// their own launch that are still to start: one lane of a workgroup reads it, and after a barrier
+// all go on or all return (read by each wavefront, some would leave and the others find the
+// counters and queues in LDS unset).
 //
 // Work split.  One workgroup per block of consecutive sorted slots (about one x-row of cells; the
 // blocks of one box never span another).  It evaluates the pairs inside its block once and
@@ -301,10 +304,13 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_search(DevParams P, const 
                                                               DevClock *__restrict__ clk)
 {
     __shared__ ListTasks T;
+    __shared__ unsigned stop;
     // the blocks of the largest particles, which scan most, first
     const ListBlock K = L.blocks[gridDim.x - 1 - blockIdx.x];
     const DevClock c0 = *clk;
-    if (c0.err & kErrListMask) return;
+    if (threadIdx.x == 0) stop = c0.err & kErrListMask;
+    __syncthreads();
+    if (stop) return;
     const BoxParams G = boxes[K.box];
     const double delta = le_offset(P, G, c0.step);
     // largest radius of a class (with a margin for the rounding of its number)
@@ -341,19 +347,23 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
     extern __shared__ int2 q_lds[];
     __shared__ ListTasks T;
     __shared__ int qn, cnt[kClasses + 1], pos[kClasses];
+    __shared__ unsigned stop;
     const int t = threadIdx.x;
     const int blk = xcd_row(blockIdx.x, gridDim.x);
     const ListBlock K = L.blocks[blk];
     const DevClock c0 = *clk;
-    if (c0.err & kErrListMask) return;
     const BoxParams G = boxes[K.box];
     const int cap = K.cap;
     const double skin = G.skin;
     if (t <= kClasses) cnt[t] = 0;
-    if (t == 0) qn = P.sized ? L.n[blk] : 0;
+    if (t == 0) {
+        qn = P.sized ? L.n[blk] : 0;
+        stop = c0.err & kErrListMask;
+    }
     const double delta = le_offset(P, G, c0.step);
     const double icw[3] = {1.0 / G.cw[0], 1.0 / G.cw[1], 1.0 / G.cw[2]};
     __syncthreads();
+    if (stop) return;
     if (P.sized) {
         for (int k = t; k < min(qn, cap); k += kBeginBlock) q_lds[k] = L.ent[K.e0 + k];
     } else {
@@ -445,13 +455,15 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_far_begin(DevParams P, con
 {
     __shared__ ListTasks T;
     __shared__ int cnt[kListOwnMax];
+    __shared__ unsigned stop;
     const int t = threadIdx.x;
     const ListBlock K = L.blocks[xcd_row(blockIdx.x, gridDim.x)];
     const DevClock c0 = *clk;
-    if (c0.err & kErrListMask) return;
     const BoxParams G = boxes[K.box];
     if (t < kListOwnMax) cnt[t] = 0;
+    if (t == 0) stop = c0.err & kErrListMask;
     __syncthreads();
+    if (stop) return;
     list_collect<true>(P, G, le_offset(P, G, c0.step), cell_start, pa, K, G.amax, G.amax, G.cell_off, T, clk,
                        [&](int il, int j, double, double) {
                            const int e = atomicAdd(&cnt[il], 1);
@@ -559,14 +571,15 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
     double *const acc = reinterpret_cast<double *>(rec + L.own_cap);
     int *const cnt = reinterpret_cast<int *>(acc + 6 * L.own_cap);
     __shared__ double red[kListBlock / 64][12];
+    __shared__ unsigned stop;
     const int t = threadIdx.x;
     const int blk = xcd_row(blockIdx.x, gridDim.x);
     // everything the block's number leads to is requested before the first use
     const ListBlock K = L.blocks[blk];
     const int ne = L.n[blk];
     const DevClock c0 = *clk;
-    if (c0.err & kErrListMask) return;
     const BoxParams G = P.nbox > 1 ? boxes[K.box] : G0;
+    if (t == 0) stop = c0.err & kErrListMask;
     {
         const double2 *const src = reinterpret_cast<const double2 *>(in + K.start);
         double2 *const dst = reinterpret_cast<double2 *>(rec);
@@ -584,6 +597,7 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
     tally.fill = 0;
     bool bad = false;
     __syncthreads();
+    if (stop) return;
     // the entry of the lane's next round is requested a round ahead, and the stretch with the
     // records: one memory latency per round instead of three
     int2 next = t < ne ? L.ent[K.e0 + t] : make_int2(0, 0);
