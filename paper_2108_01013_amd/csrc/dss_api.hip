@@ -960,7 +960,7 @@ dss_status graph_step(dss_handle *h, bool finish)
     if (!h->graph[key]) {
         hipGraph_t g = nullptr;
         const int cur = h->cur, hh = h->hh;
-        const bool vih = h->vel_is_half, total = h->own_total;
+        const bool vih = h->vel_is_half, total = h->own_total, listable = h->listable;
         const int64_t step = h->step;
         HIPTRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
         dss_status s = evaluate(h, EVAL_STEP, finish);
@@ -970,6 +970,7 @@ dss_status graph_step(dss_handle *h, bool finish)
         h->hh = hh;
         h->vel_is_half = vih;
         h->own_total = total;
+        h->listable = listable;
         h->step = step;
         if (s) {
             if (g) (void)hipGraphDestroy(g);
@@ -985,6 +986,7 @@ dss_status graph_step(dss_handle *h, bool finish)
     }
     HIPTRY(hipGraphLaunch(h->graph[key], h->stream));
     commit_eval(h, true);
+    h->listable = true;
     return DSS_OK;
 }
 
@@ -1247,7 +1249,7 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
         h->run_graphs.clear();
     }
     const int cur = h->cur, hh = h->hh;
-    const bool vih = h->vel_is_half, total = h->own_total;
+    const bool vih = h->vel_is_half, total = h->own_total, listable = h->listable;
     const int64_t step = h->step;
     hipGraph_t g = nullptr;
     HIPTRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
@@ -1261,6 +1263,7 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
     h->hh = hh;
     h->vel_is_half = vih;
     h->own_total = total;
+    h->listable = listable;
     h->step = step;
     if (s) {
         if (g) (void)hipGraphDestroy(g);
@@ -1285,6 +1288,7 @@ dss_status graph_run(dss_handle *h, int n, bool lists, uint64_t finish)
     if (s) return s;
     HIPTRY(hipGraphLaunch(ge, h->stream));
     commit_run(h, n, lists);
+    h->listable = true;
     return DSS_OK;
 }
 
@@ -1849,7 +1853,9 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
     }
     // the stress and counters are summed only when a sample is due and after the last step
     h->call_every = stress_every;
+    const bool listable = h->listable;
     s = enqueue_steps(h, n_steps, stress_every);
+    if (capture == hipStreamCaptureStatusActive) h->listable = listable;  // nothing has run
     if (s) return s;
     if (sync) return check_flags(h);
     if (!h->runs.empty()) {
