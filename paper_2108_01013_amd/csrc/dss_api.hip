@@ -2641,6 +2641,13 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     h->pair_count = guard.count;
     h->P.record_pairs = rec0;
     if (s) return s;
+    if (whole && rec0) {
+        // the listed pairs of the run's last evaluation, which went to the tape
+        HIPTRY(hipMemcpyAsync(h->pairs, W.tape[K].pairs, 2 * W.tape[K].npairs * sizeof(int), hipMemcpyDeviceToDevice,
+                              h->stream));
+        HIPTRY(hipMemcpyAsync(h->pair_count, slots + K, sizeof(unsigned long long), hipMemcpyDeviceToDevice,
+                              h->stream));
+    }
     {
         // the evaluation at the initial state; the stretch of the initial history is held fixed
         const TapeEntry &T0 = W.tape[0];
