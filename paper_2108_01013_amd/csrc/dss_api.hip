@@ -2381,6 +2381,25 @@ struct PairRecordGuard {
     }
 };
 
+// The handle's force records replaced by other memory (36 N doubles; none: not replaced) while in scope.
+struct RecordsAside {
+    dss_handle *h;
+    double *own, *nb, *x;
+    RecordsAside(dss_handle *h_, double *mem) : h(h_), own(h_->ft_own), nb(h_->ft_nb), x(h_->ft_x)
+    {
+        if (!mem) return;
+        h->ft_own = mem;
+        h->ft_nb = mem + 6 * h->N;
+        h->ft_x = mem + 30 * h->N;
+    }
+    ~RecordsAside()
+    {
+        h->ft_own = own;
+        h->ft_nb = nb;
+        h->ft_x = x;
+    }
+};
+
 }  // namespace
 
 extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress_every, int64_t ckpt_every,
@@ -2459,6 +2478,8 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     HIPTRY(W.get(&agrad, 18 * (size_t)std::max<int64_t>(h->P.pair_cap, 1)));
     double *tpart = nullptr;  // parameter gradients of each k_pairs_vjp workgroup
     HIPTRY(W.get(&tpart, 2 * (size_t)((std::max<int64_t>(h->P.pair_cap, 1) + kBlock - 1) / kBlock)));
+    double *first_ft = nullptr;  // force records of the evaluation at the first state
+    if (whole) HIPTRY(W.get(&first_ft, 36 * (size_t)N));
     // tape entries 0 .. n
     auto tape_entries = [&](int64_t n) {
         if ((int64_t)W.tape.size() < n + 1) W.tape.resize(n + 1);
@@ -2580,7 +2601,12 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
             // the evaluation at the initial state (its pairs; its state by id is written by the
             // next step's k_predict, which reads that state)
             record_into(h, W.tape[0], slots);
-            s = evaluate(h, EVAL_INPLACE);
+            {
+                // a run recorded as it runs starts with the forces the handle holds, as a time step
+                // does (not these, after dss_set_step): its records stay aside
+                RecordsAside aside(h, whole ? first_ft : nullptr);
+                s = evaluate(h, EVAL_INPLACE);
+            }
             if (s) break;
         }
         for (int64_t k = 1; k <= len; ++k) {

@@ -25,3 +25,27 @@ def test_listed_pairs():
             out.append(s.pairs())
             s.close()
         assert np.array_equal(*out) and not np.array_equal(out[0], first)
+
+
+def test_after_set_step():
+    """dss_set_step moves the Lees-Edwards offset under the forces, and a run without an evaluation in
+    between starts with those forces: J is the mean of the step call's samples, and the state its
+    state.  Sums of the same pairs in another order over 20 steps: 1e-10, as against the oracle."""
+    from paper_2108_01013_amd.dss import Simulation
+    w = synth.bidisperse_box(1200, 0.5, seed=3)
+    out = []
+    for adjoint in (True, False):
+        s = Simulation(w.params)
+        s.set_particles(w.x, w.rad)
+        s.set_step(777)
+        if adjoint:
+            J = s.adjoint(20, 5, 7)["J"]
+        else:
+            s.step(20, 5)
+            J = s.read_stress()[1][0, 1]
+        out.append((J, s.state()))
+        s.close()
+    (a, x), (b, y) = out
+    assert abs(a - b) <= 1e-10 * abs(b)
+    for k in ("u", "w", "F", "T"):
+        assert np.max(np.abs(x[k] - y[k])) <= 1e-10 * np.max(np.abs(y[k])), k
