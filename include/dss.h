@@ -262,6 +262,13 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
  * that time or schedule the steps. */
 dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_every);
 
+/* The windows of dss_step on this handle: how many were taken and how many stopped (and were
+ * taken again), and the longest that the next call would take (0: full steps; each nullable).
+ * After a stop the windows are half as long, down to 8 steps, and lengthen again as they do not
+ * stop; when a window of 8 stops, or its lists do not fit, 64 steps and more are full steps before
+ * the next one. */
+dss_status dss_get_windows(dss_handle *h, int64_t *taken, int64_t *stopped, int32_t *length);
+
 /* Stress of the last force evaluation (sigma_last, 9 values, row-major Sigma_ab) and the
  * mean over the samples of the last dss_step call (sigma_mean, nullable); n_samples
  * receives the sample count (nullable).  Sigma = 2 eta0 E_inf + (1/V)(sum_i S^S_i +

@@ -109,6 +109,14 @@ struct AdjointScratch;
 // ones are as fast.
 constexpr int kListWindow = 64;
 constexpr int kListWindowMin = 5;
+// A window that stops is taken again from its start, so its length is halved, down to
+// kListWindowShort, and doubled again after list_need windows in a row that did not (twice as many after
+// every stop: a stop costs up to a window).  A stop of a shortest window, or lists that do not fit, give
+// full steps for a while: kListRest of them, twice as many after every such stop up to
+// kListRestMax (a search in vain is about a full step and the empty launches of a window).
+constexpr int kListWindowShort = 8;
+constexpr int kListGood = 4, kListGoodMax = 64;
+constexpr int64_t kListRest = 64, kListRestMax = 4096;
 // Margin of the lists of a box beyond its cutoff, in smallest radii: what particles moving at a
 // few shear rates use up over a window of kListWindow steps, with a floor.
 // `reach`: the box's cutoff radius in the same units, which the shear shortens by up to
@@ -230,14 +238,19 @@ struct dss_handle {
     int far_cap = 0;
     ListRec *lrec[2] = {nullptr, nullptr};
     int list_blocks = 0, list_own_cap = 0, list_cap = 0;
-    int list_window = kListWindow;   // longest window (0: off); halved when one stopped early
-    int list_good = 0;               // calls since then without a stop
+    bool lists_never = false;        // lists of this lattice are too large
+    int list_window = kListWindow;   // longest window
+    int list_good = 0;               // windows in a row that did not stop
+    int list_need = kListGood;       // and how many of them double the length
+    int64_t list_rest = 0;           // full steps before the next window
+    int64_t list_rest_next = kListRest;
+    int64_t windows_done = 0, windows_stopped = 0;
     // the runs of steps enqueued since the host last read the clock: the state each began from,
     // where the host resumes when a window stopped; and the end and sampling of the last call
     struct Run {
         int64_t step;
         int cur, hh;
-        bool vel_is_half, own_total;
+        bool vel_is_half, own_total, lists;
     };
     std::vector<Run> runs;
     int64_t call_every = 0;
@@ -302,6 +315,8 @@ void free_lists(dss_handle *h)
     h->lfar = h->lfar_n = nullptr;
     h->lfar_f = nullptr;
     h->lrec[0] = h->lrec[1] = nullptr;
+    h->lists_never = false;
+    h->list_rest = 0;
 }
 
 void free_lattice(dss_handle *h)
@@ -354,6 +369,8 @@ void free_all(dss_handle *h)
     h->runs.clear();
     h->list_window = kListWindow;
     h->list_good = 0;
+    h->list_need = kListGood;
+    h->list_rest_next = kListRest;
     h->loaded = false;
 }
 
@@ -1011,7 +1028,7 @@ void commit_run(dss_handle *h, int n, bool lists)
 // wavy shear, no steps captured by a caller.
 bool lists_on(const dss_handle *h)
 {
-    return h->list_window >= kListWindowMin && (h->tune.tiled || h->P.sized) && (!h->P.ec || h->P.ec_split) && !h->P.record_pairs &&
+    return !h->lists_never && (h->tune.tiled || h->P.sized) && (!h->P.ec || h->P.ec_split) && !h->P.record_pairs &&
            h->P.wave_amp == 0.0 && !h->captured;
 }
 
@@ -1059,7 +1076,7 @@ dss_status setup_lists(dss_handle *h)
                 const int per_own = kListPerOwn + paper_capacity(top[k], h->a_min) / 4;
                 const int most = std::max(1, std::min(own, (kListCapMax - kListSpare) / per_own));
                 if (per_own + kListSpare > kListCapMax) {
-                    h->list_window = 0;  // one particle's list would not fit a workgroup
+                    h->lists_never = true;  // one particle's list would not fit a workgroup
                     return DSS_OK;
                 }
                 if (count[k]) add(start, count[k], b, k, most, per_own);
@@ -1071,7 +1088,7 @@ dss_status setup_lists(dss_handle *h)
         G.blk_n = (int)blocks.size() - G.blk_off;
     }
     if (ent > (int64_t)0x7fffffff) {
-        h->list_window = 0;  // lists of this size are not indexed
+        h->lists_never = true;  // lists of this size are not indexed
         return DSS_OK;
     }
     h->list_blocks = (int)blocks.size();
@@ -1083,7 +1100,7 @@ dss_status setup_lists(dss_handle *h)
         const double mean = (double)h->N / (G.L[0] * G.L[1] * G.L[2]) * (4.0 / 3.0) * kPi * r * r * r;
         h->far_cap = ((int)std::min(1.6 * mean + 32.0, 1.0e6) + 7) / 8 * 8;
         if ((double)h->N * h->far_cap > 4.0e9) {
-            h->list_window = 0;  // 16 GB of far lists
+            h->lists_never = true;  // 16 GB of far lists
             return DSS_OK;
         }
         G.blk_n += h->ec_grid;
@@ -1119,14 +1136,15 @@ dss_status setup_lists(dss_handle *h)
     return DSS_OK;
 }
 
-// Without the memory for them the steps are full steps.
-void setup_lists_or_none(dss_handle *h)
+// The lists of the handle's windows; without the memory for them the next steps are full steps.
+bool lists_ready(dss_handle *h)
 {
-    if (setup_lists(h) == DSS_OK) return;
+    if (setup_lists(h) == DSS_OK) return !h->lists_never;
     (void)hipGetLastError();
     (void)hipStreamSynchronize(h->stream);
     free_lists(h);
-    h->list_window = 0;
+    h->list_rest = kListRestMax;
+    return false;
 }
 
 // Stress partial records of a list step: one per block, then those of the far pairs' pass.
@@ -1298,20 +1316,19 @@ dss_status graph_run(dss_handle *h, int n, bool lists, uint64_t finish)
 // long as the sampling period (2 .. 16) when there is one, else kRunSteps / 2.  Windows: the rest
 // of the call (or of a sampling period longer than a window) in the fewest equal parts, rounded up
 // to whole sampling periods where they fit, so that the graphs of a call repeat; what is too short
-// for a window (the search and the full step would cost more than they save) goes as full steps.
+// for a window goes as full steps.
 struct StepRuns {
     int64_t n_steps, stress_every, step0;
-    int full, longest;
-    StepRuns(int64_t n, int64_t se, int64_t s0, int longest_)
-        : n_steps(n), stress_every(se), step0(s0), full(se >= 2 && se <= kRunSteps ? (int)se : kRunSteps / 2),
-          longest(longest_)
+    int full;
+    StepRuns(int64_t n, int64_t se, int64_t s0)
+        : n_steps(n), stress_every(se), step0(s0), full(se >= 2 && se <= kRunSteps ? (int)se : kRunSteps / 2)
     {
     }
     bool finish_at(int64_t k) const  // k: the step's index within the call
     {
         return k == n_steps - 1 || (stress_every > 0 && (step0 + k + 1) % stress_every == 0);
     }
-    int length_at(int64_t k, bool &lists) const
+    int length_at(int64_t k, int longest, bool &lists) const  // longest: of a window, 0 for none
     {
         const int64_t left = n_steps - k;
         lists = longest >= kListWindowMin && left >= kListWindowMin;
@@ -1336,6 +1353,18 @@ struct StepRuns {
         for (int j = 0; j < n; ++j) mask |= (uint64_t)(finish_at(k + j) ? 1 : 0) << j;
         return mask;
     }
+    // The run that the handle takes at k, with `rest` full steps to take before a window.
+    int next(const dss_handle *h, int64_t k, int64_t rest, bool listable, bool graphs, bool &lists) const
+    {
+        int n = length_at(k, lists_on(h) && rest == 0 ? h->list_window : 0, lists);
+        if (lists && !listable) {  // a full step first
+            lists = false;
+            return 1;
+        }
+        if (lists) return n;
+        if (rest > 0) n = (int)std::min<int64_t>(n, rest);
+        return graphs ? n : 1;
+    }
 };
 
 // Enqueue n_steps time steps from the current state (graphs, or direct launches).
@@ -1343,34 +1372,78 @@ dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
 {
     const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
     dss_status s = DSS_OK;
-    const bool windows = n_steps >= kListWindowMin && lists_on(h);
-    if (windows) setup_lists_or_none(h);
-    const StepRuns R(n_steps, stress_every, h->step, windows && lists_on(h) ? h->list_window : 0);
+    const StepRuns R(n_steps, stress_every, h->step);
     for (int64_t k = 0; k < n_steps;) {
         bool lists;
-        int n = R.length_at(k, lists);
-        if (lists && !h->listable) {  // a full step first
-            lists = false;
-            n = 1;
-        }
-        if (!graphs && !lists) n = 1;
-        if (lists || !h->runs.empty()) h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half, h->own_total});
+        const int n = R.next(h, k, h->list_rest, h->listable, graphs, lists);
+        if (lists && !lists_ready(h)) continue;  // other runs, then
+        if (lists || !h->runs.empty())
+            h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half, h->own_total, lists});
         if (graphs && n >= 2)
             s = graph_run(h, n, lists, R.mask_at(k, n));
         else if (lists)
             s = list_window(h, n, R.mask_at(k, n));
         else
             s = graphs ? graph_step(h, R.finish_at(k)) : evaluate(h, EVAL_STEP, R.finish_at(k));
+        if (!lists) h->list_rest = std::max<int64_t>(0, h->list_rest - n);
         k += n;
         if (s) return s;
     }
     return DSS_OK;
 }
 
-// Read the clock.  When a window stopped early (its lists no longer held every pair, or did not
-// fit), the state on the device is the committed one of that window's start and nothing later has
-// run: the host goes back to it and takes the remaining steps, with shorter windows (none when the
-// lists did not fit).
+// The first n runs of the log have run without a stop.
+void runs_done(dss_handle *h, size_t n)
+{
+    for (size_t k = 0; k < n; ++k) {
+        if (!h->runs[k].lists) continue;
+        ++h->windows_done;
+        if (++h->list_good < h->list_need) continue;
+        h->list_good = 0;
+        if (h->list_window < kListWindow) {
+            h->list_window = std::min(2 * h->list_window, kListWindow);
+        } else {
+            h->list_need = kListGood;
+            h->list_rest_next = kListRest;
+        }
+    }
+    h->runs.erase(h->runs.begin(), h->runs.begin() + n);
+}
+
+// A window stopped early (its lists no longer held every pair, or did not fit; c: the clock): the
+// state on the device is the committed one of that window's start, and nothing later has run.  The
+// host goes back to it, the device's flag is cleared behind all that is enqueued, and the windows get
+// shorter.
+dss_status resume_at_stop(dss_handle *h, DevClock c)
+{
+    size_t at = h->runs.size();
+    while (at > 0 && h->runs[at - 1].step != c.step) --at;
+    if (at == 0) return fail(h, DSS_ERR_HIP, "a window of time steps stopped at an unknown step");
+    runs_done(h, at - 1);
+    const dss_handle::Run r = h->runs.front();
+    h->runs.clear();
+    h->step = r.step;
+    h->cur = r.cur;
+    h->hh = r.hh;
+    h->vel_is_half = r.vel_is_half;
+    h->own_total = r.own_total;
+    ++h->windows_stopped;
+    h->list_good = 0;
+    h->list_need = std::min(2 * h->list_need, kListGoodMax);
+    if (!(c.err & kErrListFull) && h->list_window > kListWindowShort) {
+        h->list_window = std::max(h->list_window / 2, kListWindowShort);
+    } else {
+        h->list_rest = h->list_rest_next;
+        h->list_rest_next = std::min(2 * h->list_rest_next, kListRestMax);
+    }
+    c.err &= ~kErrListMask;
+    HIPTRY(hipMemcpyAsync(h->clk, &c, sizeof(c), hipMemcpyHostToDevice, h->stream));
+    HIPTRY(hipMemsetAsync(h->ln, 0, h->list_blocks * sizeof(int), h->stream));
+    HIPTRY(hipStreamSynchronize(h->stream));
+    return DSS_OK;
+}
+
+// Read the clock; the steps after a window that stopped early are taken again.
 dss_status settle(dss_handle *h, DevClock *out)
 {
     for (;;) {
@@ -1378,31 +1451,13 @@ dss_status settle(dss_handle *h, DevClock *out)
         HIPTRY(hipMemcpyAsync(&c, h->clk, sizeof(c), hipMemcpyDeviceToHost, h->stream));
         HIPTRY(hipStreamSynchronize(h->stream));
         if (!(c.err & kErrListMask)) {
-            if (!h->runs.empty() && h->list_window > 0 && h->list_window < kListWindow && ++h->list_good >= 4) {
-                h->list_window = std::min(2 * h->list_window, kListWindow);
-                h->list_good = 0;
-            }
-            h->runs.clear();
+            runs_done(h, h->runs.size());
             if (out) *out = c;
             return DSS_OK;
         }
-        auto at = h->runs.rbegin();
-        while (at != h->runs.rend() && at->step != c.step) ++at;
-        if (at == h->runs.rend()) return fail(h, DSS_ERR_HIP, "a window of time steps stopped at an unknown step");
         const int64_t target = h->step;
-        h->step = at->step;
-        h->cur = at->cur;
-        h->hh = at->hh;
-        h->vel_is_half = at->vel_is_half;
-        h->own_total = at->own_total;
-        h->runs.clear();
-        h->list_good = 0;
-        h->list_window = (c.err & kErrListFull) || h->list_window < 2 * kListWindowMin ? 0 : h->list_window / 2;
-        c.err &= ~kErrListMask;
-        HIPTRY(hipMemcpyAsync(h->clk, &c, sizeof(c), hipMemcpyHostToDevice, h->stream));
-        HIPTRY(hipMemsetAsync(h->ln, 0, h->list_blocks * sizeof(int), h->stream));
-        HIPTRY(hipStreamSynchronize(h->stream));
-        dss_status s = enqueue_steps(h, target - h->step, h->call_every);
+        dss_status s = resume_at_stop(h, c);
+        if (!s) s = enqueue_steps(h, target - h->step, h->call_every);
         if (s) return s;
     }
 }
@@ -1877,24 +1932,25 @@ dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_ever
     if (!graphs || h->tune_pending) return DSS_OK;  // direct launches, or a lattice change comes first
     // walk the call's runs as dss_step will, capturing the graphs it does not have yet; only
     // the handle's bookkeeping of the buffers advances, and it is put back
-    if (lists_on(h) && n_steps >= kListWindowMin) setup_lists_or_none(h);
     const int cur = h->cur, hh = h->hh;
     const bool vih = h->vel_is_half, total = h->own_total;
     const int64_t step = h->step;
-    const StepRuns R(n_steps, stress_every, h->step, lists_on(h) ? h->list_window : 0);
+    const StepRuns R(n_steps, stress_every, h->step);
     bool listable = h->listable;
+    int64_t rest = h->list_rest;
     for (int64_t k = 0; k < n_steps && !s;) {
         bool lists;
-        int n = R.length_at(k, lists);
-        if (lists && !listable) {
-            lists = false;
-            n = 1;
+        const int n = R.next(h, k, rest, listable, graphs, lists);
+        if (lists && !lists_ready(h)) {
+            rest = h->list_rest;
+            continue;
         }
         listable = true;
         if (n >= 2) {
             hipGraphExec_t ge = nullptr;
             s = run_graph(h, n, lists, R.mask_at(k, n), &ge);
         }
+        if (!lists) rest = std::max<int64_t>(0, rest - n);
         commit_run(h, n, lists);
         k += n;
     }
@@ -1904,6 +1960,16 @@ dss_status dss_prepare_steps(dss_handle *h, int64_t n_steps, int64_t stress_ever
     h->own_total = total;
     h->step = step;
     return s;
+}
+
+dss_status dss_get_windows(dss_handle *h, int64_t *taken, int64_t *stopped, int32_t *length)
+{
+    dss_status s = require_loaded(h);
+    if (s) return s;
+    if (taken) *taken = h->windows_done;
+    if (stopped) *stopped = h->windows_stopped;
+    if (length) *length = lists_on(h) && h->list_rest == 0 ? h->list_window : 0;
+    return DSS_OK;
 }
 
 dss_status dss_read_stress_batch(dss_handle *h, double *sigma_last, double *sigma_mean, int64_t *n_samples)
@@ -2521,7 +2587,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
     // reverse kernels does not stop them)
     const unsigned fwd_timed = h->timing & ~((1u << 5) | (1u << 6));
     const bool graphs = h->tune.graph && !h->graph_broken && fwd_timed == 0 && !h->P.record_pairs;
-    const StepRuns R(K, stress_every, h->step, 0);
+    const StepRuns R(K, stress_every, h->step);
     for (int64_t k = whole ? K : 0; k < K;) {
         if (k % C == 0) {
             s = snap_save(h, W.ck[k / C]);
@@ -2817,6 +2883,7 @@ dss_status dss_load_state(dss_handle *h, const void *blob, size_t bytes)
     h->vel_is_half = hd.vel_is_half != 0;
     h->own_total = false;
     h->listable = false;  // the snapshot does not say; the next full step settles it
+    h->list_rest = 0;
     return DSS_OK;
 }
 

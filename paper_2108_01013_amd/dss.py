@@ -24,7 +24,7 @@ DSS_FLAG_EC_RANGES = 2
 STATUS = {0: "DSS_OK", 1: "DSS_ERR_ARG", 2: "DSS_ERR_HIP", 3: "DSS_ERR_CAPACITY", 4: "DSS_ERR_BOX",
           5: "DSS_ERR_UNSTABLE", 6: "DSS_ERR_STATE"}
 
-EXPORTS = ["dss_create", "dss_create_batch", "dss_set_particles", "dss_set_particles_batch", "dss_set_step", "dss_build_neighbours", "dss_compute_forces", "dss_step", "dss_prepare_steps",
+EXPORTS = ["dss_create", "dss_create_batch", "dss_set_particles", "dss_set_particles_batch", "dss_set_step", "dss_build_neighbours", "dss_compute_forces", "dss_step", "dss_prepare_steps", "dss_get_windows",
            "dss_read_stress", "dss_read_stress_batch", "dss_get_box_info", "dss_get_state", "dss_get_eval_velocities", "dss_get_pairs", "dss_get_cells", "dss_get_rolling_history",
            "dss_observe_start", "dss_observe", "dss_phi_profile", "dss_phi_profile_noalloc", "dss_contact_clusters",
            "dss_get_history", "dss_get_info", "dss_save_state", "dss_load_state", "dss_set_timing",
@@ -100,6 +100,7 @@ def load_library():
         "dss_compute_forces": (st, [H]),
         "dss_step": (st, [H, i64, i64, ctypes.c_int]),
         "dss_prepare_steps": (st, [H, i64, i64]),
+        "dss_get_windows": (st, [H, ctypes.POINTER(i64), ctypes.POINTER(i64), ctypes.POINTER(ctypes.c_int32)]),
         "dss_read_stress": (st, [H, vp, vp, ctypes.POINTER(i64)]),
         "dss_get_state": (st, [H, vp, vp, vp, vp, vp, ctypes.c_int]),
         "dss_get_eval_velocities": (st, [H, vp, vp, ctypes.c_int]),
@@ -238,6 +239,13 @@ class Simulation:
         """Capture the graphs that step(n, stress_every) from the current state will replay,
         without running anything."""
         self._check(self.lib.dss_prepare_steps(self.h, int(n), int(stress_every)))
+
+    def windows(self) -> dict:
+        """The windows of step() on this handle: taken, stopped (and taken again), and the longest
+        that the next call would take (0: full steps)."""
+        taken, stopped, length = ctypes.c_int64(0), ctypes.c_int64(0), ctypes.c_int32(0)
+        self._check(self.lib.dss_get_windows(self.h, ctypes.byref(taken), ctypes.byref(stopped), ctypes.byref(length)))
+        return {"taken": taken.value, "stopped": stopped.value, "length": length.value}
 
     def read_stress(self):
         last = np.zeros(9)
