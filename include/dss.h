@@ -246,7 +246,7 @@ dss_status dss_compute_forces(dss_handle *h);
  * Runs of 5 and more steps are taken in windows of up to 64 on pair lists (pairs inside the
  * cutoff plus a margin, tested at every step's positions: the pair sets are those of a search
  * at every step).  A window that a particle would leave the margin in stops on the device, and
- * its steps are taken again from its start; after a call with sync = 0 that happens in the next
+ * its steps are taken again from its start; after a call with sync = 0 that may happen in the next
  * call on the handle, so a caller that times or orders work by the stream alone passes sync = 1.
  * A caller that captures its stream (graph = 0, sync = 0, an even number of steps, so that a replay
  * ends in the buffers it began in) captures full steps, and the handle takes only full steps

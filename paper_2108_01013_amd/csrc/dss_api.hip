@@ -117,6 +117,10 @@ constexpr int kListWindowMin = 5;
 constexpr int kListWindowShort = 8;
 constexpr int kListGood = 4, kListGoodMax = 64;
 constexpr int64_t kListRest = 64, kListRestMax = 4096;
+// The host looks at the clock every so many steps of windows (a copy of 16 bytes and an event in the
+// stream), two looks behind what it enqueues: a stop in a long call leaves few empty launches behind it,
+// and the windows lengthen again within the call.
+constexpr int64_t kLookSteps = 512;
 // Margin of the lists of a box beyond its cutoff, in smallest radii: what particles moving at a
 // few shear rates use up over a window of kListWindow steps, with a floor.
 // `reach`: the box's cutoff radius in the same units, which the shear shortens by up to
@@ -254,6 +258,14 @@ struct dss_handle {
     };
     std::vector<Run> runs;
     int64_t call_every = 0;
+    struct Look {
+        hipEvent_t ev = nullptr;
+        bool on = false;
+        size_t runs = 0;  // runs of the log that the clock was read after
+    } look[2];
+    DevClock *looked = nullptr;  // pinned, one for each
+    int look_next = 0;
+    int64_t look_steps = 0;
     // a stream beside the caller's, which waits (by event) for the last runs of a call that did not
     hipStream_t side = nullptr;
     hipEvent_t tail = nullptr;
@@ -367,6 +379,8 @@ void free_all(dss_handle *h)
     h->sigma_last = h->samples = nullptr;
     h->sample_cap_alloc = 0;
     h->runs.clear();
+    h->look[0].on = h->look[1].on = false;
+    h->look_steps = 0;
     h->list_window = kListWindow;
     h->list_good = 0;
     h->list_need = kListGood;
@@ -1367,31 +1381,6 @@ struct StepRuns {
     }
 };
 
-// Enqueue n_steps time steps from the current state (graphs, or direct launches).
-dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every)
-{
-    const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
-    dss_status s = DSS_OK;
-    const StepRuns R(n_steps, stress_every, h->step);
-    for (int64_t k = 0; k < n_steps;) {
-        bool lists;
-        const int n = R.next(h, k, h->list_rest, h->listable, graphs, lists);
-        if (lists && !lists_ready(h)) continue;  // other runs, then
-        if (lists || !h->runs.empty())
-            h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half, h->own_total, lists});
-        if (graphs && n >= 2)
-            s = graph_run(h, n, lists, R.mask_at(k, n));
-        else if (lists)
-            s = list_window(h, n, R.mask_at(k, n));
-        else
-            s = graphs ? graph_step(h, R.finish_at(k)) : evaluate(h, EVAL_STEP, R.finish_at(k));
-        if (!lists) h->list_rest = std::max<int64_t>(0, h->list_rest - n);
-        k += n;
-        if (s) return s;
-    }
-    return DSS_OK;
-}
-
 // The first n runs of the log have run without a stop.
 void runs_done(dss_handle *h, size_t n)
 {
@@ -1408,6 +1397,12 @@ void runs_done(dss_handle *h, size_t n)
         }
     }
     h->runs.erase(h->runs.begin(), h->runs.begin() + n);
+}
+
+void no_looks(dss_handle *h)
+{
+    h->look[0].on = h->look[1].on = false;
+    h->look_steps = 0;
 }
 
 // A window stopped early (its lists no longer held every pair, or did not fit; c: the clock): the
@@ -1436,10 +1431,75 @@ dss_status resume_at_stop(dss_handle *h, DevClock c)
         h->list_rest = h->list_rest_next;
         h->list_rest_next = std::min(2 * h->list_rest_next, kListRestMax);
     }
-    c.err &= ~kErrListMask;
-    HIPTRY(hipMemcpyAsync(h->clk, &c, sizeof(c), hipMemcpyHostToDevice, h->stream));
-    HIPTRY(hipMemsetAsync(h->ln, 0, h->list_blocks * sizeof(int), h->stream));
-    HIPTRY(hipStreamSynchronize(h->stream));
+    no_looks(h);
+    hipLaunchKernelGGL(k_list_resume, dim3((h->list_blocks + kBeginBlock - 1) / kBeginBlock), dim3(kBeginBlock), 0,
+                       h->stream, h->list_blocks, h->ln, h->clk);
+    HIPTRY(hipGetLastError());
+    return DSS_OK;
+}
+
+// Look at the clock, and find whether a window of two looks ago has stopped (wait: wait for that one; else
+// it counts only if the device is there already).
+dss_status look_at_clock(dss_handle *h, bool wait, bool &stopped)
+{
+    stopped = false;
+    if (!h->looked) HIPTRY(hipHostMalloc((void **)&h->looked, 2 * sizeof(DevClock), hipHostMallocDefault));
+    dss_handle::Look &l = h->look[h->look_next];
+    if (!l.ev) HIPTRY(hipEventCreateWithFlags(&l.ev, hipEventDisableTiming));
+    if (l.on) {
+        if (!wait && hipEventQuery(l.ev) != hipSuccess) {
+            (void)hipGetLastError();
+            return DSS_OK;
+        }
+        HIPTRY(hipEventSynchronize(l.ev));
+        l.on = false;
+        const DevClock c = h->looked[h->look_next];
+        if (c.err & kErrListMask) {
+            stopped = true;
+            return resume_at_stop(h, c);
+        }
+        runs_done(h, l.runs);
+        h->look[1 - h->look_next].runs -= l.runs;
+    }
+    HIPTRY(hipMemcpyAsync(&h->looked[h->look_next], h->clk, sizeof(DevClock), hipMemcpyDeviceToHost, h->stream));
+    HIPTRY(hipEventRecord(l.ev, h->stream));
+    l.on = true;
+    l.runs = h->runs.size();
+    h->look_next = 1 - h->look_next;
+    h->look_steps = 0;
+    return DSS_OK;
+}
+
+// Enqueue n_steps time steps from the current state (graphs, or direct launches); wait: the caller
+// waits for them.
+dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every, bool wait)
+{
+    const bool graphs = h->tune.graph && !h->graph_broken && h->timing == 0 && !h->P.record_pairs;
+    dss_status s = DSS_OK;
+    const int64_t target = h->step + n_steps;
+    StepRuns R(n_steps, stress_every, h->step);
+    while (h->step < target) {
+        const int64_t k = h->step - R.step0;
+        bool lists;
+        const int n = R.next(h, k, h->list_rest, h->listable, graphs, lists);
+        if (lists && !lists_ready(h)) continue;  // other runs, then
+        if (lists || !h->runs.empty())
+            h->runs.push_back({h->step, h->cur, h->hh, h->vel_is_half, h->own_total, lists});
+        if (graphs && n >= 2)
+            s = graph_run(h, n, lists, R.mask_at(k, n));
+        else if (lists)
+            s = list_window(h, n, R.mask_at(k, n));
+        else
+            s = graphs ? graph_step(h, R.finish_at(k)) : evaluate(h, EVAL_STEP, R.finish_at(k));
+        if (s) return s;
+        if (!lists) h->list_rest = std::max<int64_t>(0, h->list_rest - n);
+        if (lists && (h->look_steps += n) >= kLookSteps) {
+            bool stopped;
+            s = look_at_clock(h, wait, stopped);
+            if (s) return s;
+            if (stopped) R = StepRuns(target - h->step, stress_every, h->step);
+        }
+    }
     return DSS_OK;
 }
 
@@ -1451,13 +1511,14 @@ dss_status settle(dss_handle *h, DevClock *out)
         HIPTRY(hipMemcpyAsync(&c, h->clk, sizeof(c), hipMemcpyDeviceToHost, h->stream));
         HIPTRY(hipStreamSynchronize(h->stream));
         if (!(c.err & kErrListMask)) {
+            no_looks(h);
             runs_done(h, h->runs.size());
             if (out) *out = c;
             return DSS_OK;
         }
         const int64_t target = h->step;
         dss_status s = resume_at_stop(h, c);
-        if (!s) s = enqueue_steps(h, target - h->step, h->call_every);
+        if (!s) s = enqueue_steps(h, target - h->step, h->call_every, true);
         if (s) return s;
     }
 }
@@ -1597,6 +1658,9 @@ void dss_destroy(dss_handle *h)
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     for (auto e : h->ev_pool) (void)hipEventDestroy(e);
     if (h->tail) (void)hipEventDestroy(h->tail);
+    for (auto &l : h->look)
+        if (l.ev) (void)hipEventDestroy(l.ev);
+    if (h->looked) (void)hipHostFree(h->looked);
     if (h->side) (void)hipStreamDestroy(h->side);
     free_all(h);
     if (h->own_stream) (void)hipStreamDestroy(h->stream);
@@ -1909,7 +1973,7 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
     // the stress and counters are summed only when a sample is due and after the last step
     h->call_every = stress_every;
     const bool listable = h->listable;
-    s = enqueue_steps(h, n_steps, stress_every);
+    s = enqueue_steps(h, n_steps, stress_every, sync != 0);
     if (capture == hipStreamCaptureStatusActive) h->listable = listable;  // nothing has run
     if (s) return s;
     if (sync) return check_flags(h);

@@ -106,6 +106,14 @@ struct CommittedView {
     int *img;
 };
 
+// After a window that stopped: the flag and the lists' counts are cleared, and what follows runs.
+__global__ void __launch_bounds__(kBeginBlock) k_list_resume(int nblock, int *__restrict__ n, DevClock *__restrict__ clk)
+{
+    const int k = blockIdx.x * kBeginBlock + threadIdx.x;
+    if (k < nblock) n[k] = 0;
+    if (k == 0) clk->err &= ~kErrListMask;
+}
+
 // Largest displacement sum of a particle with which the lists hold every pair after n steps.
 __device__ __forceinline__ double list_budget(const DevParams &P, const BoxParams &G, double skin, int n)
 {

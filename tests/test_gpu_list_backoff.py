@@ -71,3 +71,55 @@ def test_snapshots_do_not_stop_windows():
         s.step(40, stress_every=5)
         assert s.windows()["taken"] == 2 + k, s.windows()
     s.close()
+
+
+def test_windows_lengthen_within_a_call():
+    """One call of 20 000 steps that is waited for: its windows are short only around the violent start
+    (20 000 steps are 313 windows of 64).  (A call that is not waited for lengthens them as far as the
+    device has come when its steps are enqueued.)"""
+    from paper_2108_01013_amd.dss import Simulation
+    p, x, rad, u = fast_start()
+    s = Simulation(p)
+    s.set_particles(x, rad, u)
+    print("case: one long call", flush=True)
+    s.step(20000, stress_every=100)
+    _, mean, ns = s.read_stress()
+    w = s.windows()
+    assert s.info()["step"] == 20000 and ns == 200 and np.all(np.isfinite(mean))
+    assert w["stopped"] > 0 and w["length"] == 64
+    assert w["taken"] < 800, w
+    s.close()
+
+
+@pytest.mark.parametrize("calls,sync", [(1, True), (1, False), (4, False)])
+def test_stop_within_a_long_call(calls, sync):
+    """A large particle hits a small one after about 1000 steps in a thin fluid, and drives it off faster than
+    the margin allows for 64 steps: a window stops when later ones, and later calls, are enqueued.
+    The state and the samples of the last call are those of steps taken one call at a time (three
+    particles, one collision: 1e-9)."""
+    from paper_2108_01013_amd.dss import Simulation
+    p = synth.default_params([40.0, 16.0, 16.0], shear_rate=0.02, eta0=1e-3)
+    x = np.array([[4.0, 6.0, 6.0], [7.6, 6.1, 6.0], [20.0, 2.0, 2.0]])
+    rad = np.array([2.0, 1.0, 1.0])
+    u = np.array([[6.0, 0.0, 0.0], [0.12, 0.0, 0.0], [0.04, 0.0, 0.0]])
+    print(f"case: a stop within {calls} long calls, sync={sync}", flush=True)
+    a, b = Simulation(p), Simulation(p)
+    for s in (a, b):
+        s.set_particles(x, rad, u)
+    for c in range(calls):
+        a.step(2400, stress_every=30, sync=sync and c == calls - 1)
+    last, mean, ns = a.read_stress()
+    samples = []
+    for k in range(2400 * calls):
+        b.step(1)
+        if (k + 1) % 30 == 0 and k >= 2400 * (calls - 1):
+            samples.append(b.read_stress()[0])
+    assert ns == len(samples) and a.info()["step"] == b.info()["step"]
+    for got, want in ((last, b.read_stress()[0]), (mean, np.mean(samples, axis=0))):
+        assert np.max(np.abs(got - want)) <= 1e-9 * np.max(np.abs(want))
+    sa, sb = a.state(), b.state()
+    for k in ("u", "w", "F", "T"):
+        assert np.max(np.abs(sa[k] - sb[k])) <= 1e-9 * np.max(np.abs(sb[k])), k
+    assert a.windows()["stopped"] > 0
+    a.close()
+    b.close()
