@@ -326,8 +326,9 @@ dss_status dss_get_box_info(dss_handle *h, int32_t box, dss_box_info *info);
  * (the step is smooth between these events); the contact history at the call is held
  * fixed.  State is checkpointed every ckpt_every steps and each segment is recomputed
  * forward before its reverse sweep (memory: one state and history copy per checkpoint plus
- * a segment of ckpt_every recorded steps).  A run whose recorded steps fit 2 GiB together, and
- * the device's free memory, is recorded as it runs, without checkpoints and second runs.  This
+ * a segment of ckpt_every recorded steps).  A run whose recorded steps fit 2 GiB together (or
+ * what dss_set_adjoint_tape allows), and the device's free memory, is recorded as it runs, without
+ * checkpoints and second runs.  This
  * device workspace stays with the handle and serves the next call of the same particle count,
  * lattice and recording capacity without allocating; dss_set_particles and dss_destroy free
  * it.  On return the handle stands at the end of the run, as after dss_step(h, n_steps,
@@ -340,6 +341,11 @@ dss_status dss_get_box_info(dss_handle *h, int32_t box, dss_box_info *info);
  * (DSS_ERR_STATE). */
 dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress_every, int64_t ckpt_every, const double *weight,
                        double *J, double *dJ_dparams, double *dJ_dx, double *dJ_du, double *dJ_dw, int on_device);
+
+/* Memory that dss_adjoint may take for the recorded steps of a run that it does not checkpoint
+ * (2 GiB unless set; 0: every run is checkpointed every ckpt_every steps, and takes the memory of
+ * its checkpoints and one segment).  A smaller value than before frees the adjoint's workspace. */
+dss_status dss_set_adjoint_tape(dss_handle *h, int64_t bytes);
 
 /* Snapshot of the whole time-stepping state into host memory: particle records (sorted
  * order), force records of the last evaluation, cell_start, committed contact history,

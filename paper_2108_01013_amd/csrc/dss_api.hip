@@ -129,6 +129,9 @@ inline double list_skin(double shear_rate, double dt, double reach)
 {
     return std::min(0.1 + (10.0 + reach) * std::fabs(shear_rate) * dt * kListWindow, 0.6);
 }
+// Largest tape of an adjoint run that is recorded whole, unless the caller sets another (N = 50k: about
+// 30 steps).
+constexpr size_t kTapeBytes = size_t(2) << 30;
 constexpr size_t kMaxOpenRuns = 4096;  // runs enqueued without a read of the clock
 }  // namespace
 
@@ -229,6 +232,7 @@ struct dss_handle {
     // spins) by particle id: the adjoint's tape entry of the previous evaluation
     double *tape_x = nullptr, *tape_u = nullptr, *tape_w = nullptr;
     int *tape_zero = nullptr;  // while set, k_predict also clears these N counts
+    size_t tape_bytes = kTapeBytes;
     DevList obs_ws;  // work buffers of the observables, kept between calls
 
     // windows on pair lists: the blocks, the lists and the particle records of a window
@@ -2291,9 +2295,6 @@ dss_status dss_get_box_info(dss_handle *h, int32_t box, dss_box_info *info)
 // ======================================================================================
 namespace {
 
-// Largest tape of an adjoint run that is recorded whole (N = 50k: about 30 steps).
-constexpr size_t kTapeBytes = size_t(2) << 30;
-
 // Device copy of everything a time step, or an evaluation in place, reads from the
 // previous one (including cell_start, which must match the sorted order of the records).
 struct Snapshot {
@@ -2575,11 +2576,11 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
             h->P.pair_cap = cap;
         }
     }
-    // a run whose tape fits kTapeBytes is recorded as it runs, in one segment without checkpoints;
+    // a run whose tape fits tape_bytes is recorded as it runs, in one segment without checkpoints;
     // a longer one runs forward with checkpoints, and each segment runs again to be recorded
     const size_t entry = 9 * (size_t)N * sizeof(double) + 2 * (size_t)h->P.pair_cap * sizeof(int) +
                          (size_t)N * (M + 1) * sizeof(int) + stretch_width(h) * (size_t)N * M * sizeof(double);
-    bool whole = (size_t)(K + 1) <= kTapeBytes / entry;
+    bool whole = (size_t)(K + 1) <= h->tape_bytes / entry;
     {
         // the workspace of the last call serves when its shapes are these
         const int64_t key[8] = {N, M, h->ncell_total, h->hxr[h->hh] ? 1 : 0, h->P.pair_cap, stretch_width(h), 0, 0};
@@ -2839,6 +2840,20 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
         dJ_dparams[0] = th[0];
         dJ_dparams[1] = th[1];
     }
+    return DSS_OK;
+}
+
+extern "C" dss_status dss_set_adjoint_tape(dss_handle *h, int64_t bytes)
+{
+    if (!h) return DSS_ERR_ARG;
+    if (bytes < 0) return fail(h, DSS_ERR_ARG, "negative size of the tape");
+    if ((size_t)bytes < h->tape_bytes && h->adj_ws) {
+        dss_status s = require_loaded(h);
+        if (s) return s;
+        HIPTRY(hipStreamSynchronize(h->stream));
+        release_adjoint_ws(h);  // may hold a longer tape
+    }
+    h->tape_bytes = (size_t)bytes;
     return DSS_OK;
 }
 

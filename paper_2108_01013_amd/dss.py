@@ -28,7 +28,7 @@ EXPORTS = ["dss_create", "dss_create_batch", "dss_set_particles", "dss_set_parti
            "dss_read_stress", "dss_read_stress_batch", "dss_get_box_info", "dss_get_state", "dss_get_eval_velocities", "dss_get_pairs", "dss_get_cells", "dss_get_rolling_history",
            "dss_observe_start", "dss_observe", "dss_phi_profile", "dss_phi_profile_noalloc", "dss_contact_clusters",
            "dss_get_history", "dss_get_info", "dss_save_state", "dss_load_state", "dss_set_timing",
-           "dss_get_timing", "dss_set_tuning", "dss_get_tuning", "dss_adjoint", "dss_last_error",
+           "dss_get_timing", "dss_set_tuning", "dss_get_tuning", "dss_adjoint", "dss_set_adjoint_tape", "dss_last_error",
            "dss_status_string", "dss_destroy"]
 
 
@@ -122,6 +122,7 @@ def load_library():
         "dss_get_tuning": (st, [H, ctypes.POINTER(Tuning)]),
         "dss_adjoint": (st, [H, i64, i64, i64, vp, ctypes.POINTER(ctypes.c_double), vp, vp, vp, vp,
                              ctypes.c_int]),
+        "dss_set_adjoint_tape": (st, [H, i64]),
         "dss_last_error": (ctypes.c_char_p, [H]),
         "dss_status_string": (ctypes.c_char_p, [st]),
         "dss_destroy": (None, [H]),
@@ -374,6 +375,11 @@ class Simulation:
                                          vp(wt.ctypes.data), ctypes.byref(J), vp(th.ctypes.data),
                                          vp(dx.ctypes.data), vp(du.ctypes.data), vp(dw.ctypes.data), 0))
         return {"J": J.value, "dmu": th[0], "dF_ER": th[1], "dx": dx, "du": du, "dw": dw}
+
+    def set_adjoint_tape(self, nbytes: int):
+        """Memory that adjoint() may take for the steps of a run without checkpoints (2 GiB unless set;
+        0: every run is checkpointed every ckpt_every steps)."""
+        self._check(self.lib.dss_set_adjoint_tape(self.h, int(nbytes)))
 
     def adjoint_into(self, n_steps, stress_every, ckpt_every, weight, dx, du, dw):
         """As adjoint(), writing the state gradients into device tensors; returns (J, dmu, dF_ER)."""
