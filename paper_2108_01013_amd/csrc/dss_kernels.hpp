@@ -29,7 +29,7 @@ constexpr unsigned kErrRowOverflow = 1u;
 constexpr unsigned kErrNonFinite = 2u;
 constexpr unsigned kErrPairBuffer = 4u;
 // a window of pair lists (dss_lists.hpp) stopped: its lists no longer hold every pair, or do not
-// fit.  Every kernel of a time step returns at once while one of them is set; the host resumes
+// fit (or a particle is outside the box).  Every kernel of a time step returns at once while one of them is set; the host resumes
 // from the committed state and clears them.
 constexpr unsigned kErrListStop = 0x100u;
 constexpr unsigned kErrListFull = 0x200u;

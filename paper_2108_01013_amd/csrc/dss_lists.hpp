@@ -255,6 +255,12 @@ __device__ __forceinline__ void list_collect(const DevParams &P, const BoxParams
             const int il = k >> sh, q = k & ((1 << sh) - 1), qz = q / R.ny, qy = q - qz * R.ny;
             if (qz >= R.nz) continue;
             const double4 Xi = pa[K.start + il];
+            // a particle outside the box (a velocity of more than a box length per step, or none that
+            // is a number) has no rows to search: its cell numbers would be anything
+            if (!(Xi.x >= 0.0 && Xi.x <= G.L[0] && Xi.y >= 0.0 && Xi.y <= G.L[1] && Xi.z >= 0.0 && Xi.z <= G.L[2])) {
+                atomicOr(&clk->err, kErrListFull);
+                continue;
+            }
             list_row(G, icw, delta, cell_start, R, cell0, il, Xi, reach(Xi.w + amax), qy, qz,
                      [&](const ListTask &a) { T.task[atomicAdd(&T.n, 1)] = a; });
         }

@@ -57,3 +57,45 @@ def test_after_set_step(prepare):
     assert np.max(np.abs(xa - xb)) <= 1e-9 * np.max(np.abs(xb))
     for k in ("u", "w", "F", "T"):
         assert np.max(np.abs(a[k] - b[k])) <= 1e-10 * np.max(np.abs(b[k])), k
+
+
+@pytest.mark.parametrize("path", ["plain", "sized", "far"])
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 1e7])
+def test_particles_outside_the_box(path, bad):
+    """Velocities that are no numbers, or that carry a particle out of the box in one step: no window
+    begins where the search would take their cells for indices, the steps are full ones and the
+    error is reported as it is for single steps."""
+    from paper_2108_01013_amd.dss import DssError, Simulation
+    ec = dict(ec_ranges=True, hamaker=1e-3) if path == "far" else {}
+    w = synth.bidisperse_box(4500, 0.45, 23, **ec)
+    u = np.zeros_like(w.x)
+    u[:, 0] = w.x[:, 1]
+    u[1::700] = bad
+    u[2::700] = -bad
+    print(f"case: particles outside the box, {path}, {bad}", flush=True)
+    s = Simulation(w.params)
+    if path == "sized":
+        s.set_tuning(sized=True)
+    if np.isfinite(bad):
+        s.set_particles(w.x, w.rad, u)
+    else:
+        with pytest.raises(DssError):      # its forces are not finite; the particles are loaded
+            s.set_particles(w.x, w.rad, u)
+
+    def steps(n):
+        try:
+            s.step(n)
+        except DssError as e:
+            assert e.status == 5, e
+            return True
+        return False
+
+    failed = steps(1)                  # a full step: its positions begin the windows of the next calls
+    for n in (20, 80):
+        failed = steps(n) or failed
+    assert failed == (not np.isfinite(bad))
+    if failed:
+        with pytest.raises(DssError):
+            s.read_stress()
+    assert s.info()["step"] == 101 and s.windows()["taken"] == 0 and s.windows()["stopped"] > 0
+    s.close()
