@@ -9,7 +9,8 @@
 //              a stress sample and on the last step of a dss_step call)
 // The history rows written by k_pairs become the committed history of the step.
 // Runs of five and more steps go as windows on pair lists (dss_lists.hpp): k_list_begin, one
-// k_list per step, and a step as above at the end.
+// k_list per step, and the counting sort of the last state (k_predict's cell ids, k_scan, k_scatter, and
+// k_history_move for its rows).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -103,10 +104,14 @@ struct DevList {
 
 struct AdjointScratch;
 
-// Steps of a window on pair lists.  A window of n steps costs a search, n - 1 list steps and a full
-// step (N = 100k, FP64: 53 + 24 (n - 1) + 65 us against 64 n): longer is better until the margin is
-// used up (a sheared box of N = 100k uses a third of it in 64 steps), and below five steps full
-// ones are as fast.
+// Steps of a window on pair lists.  A window of n steps costs a search, n list steps and a sort, and
+// longer is better until the margin is used up (a sheared box of N = 100k uses a third of it in
+// 64 steps).  Calls of n steps, us: N = 1000 62 + 5.8 n on lists against 37 + 24 n in full steps; N = 100k,
+// FP64, 118 + 22 n against 52 + 54 n; N = 500k 570 + 80 n against 100 + 316 n; N = 100k with
+// attraction 290 + 78 n against 120 + 357 n; N = 500k, size ratio 10, 1150 + 96 n against 140 + 2270 n.
+// So the lists win from two or three steps on everywhere (N = 100k: 162 against 161 us at two, 184
+// against 214 at three, by these lines); five is the shortest call they have been measured to win
+// at (230 against 320 us), and shorter ones are full steps.
 constexpr int kListWindow = 64;
 constexpr int kListWindowMin = 5;
 // A window that stops is taken again from its start, so its length is halved, down to
@@ -122,7 +127,8 @@ constexpr int64_t kListRest = 64, kListRestMax = 4096;
 // and the windows lengthen again within the call.
 constexpr int64_t kLookSteps = 512;
 // Margin of the lists of a box beyond its cutoff, in smallest radii: what particles moving at a
-// few shear rates use up over a window of kListWindow steps, with a floor.
+// few shear rates use up over a window of kListWindow steps, with a floor (for shorter windows too: the
+// lists' room and the kernels' box table are laid out once).
 // `reach`: the box's cutoff radius in the same units, which the shear shortens by up to
 // reach x strain.
 inline double list_skin(double shear_rate, double dt, double reach)
@@ -1044,6 +1050,8 @@ bool lists_on(const dss_handle *h)
 // Blocks of the pair lists and the memory of a window, on the handle's first window.  A block
 // holds about as many particles as fill the workgroup slots once (1 / 64 of them kept free, as
 // for the cell rows), at least 16 and at most kListOwnMax; the blocks of a box are of one size.
+// Slots: four workgroups per CU, what k_list reaches with 129 to 168 VGPRs (every instantiation
+// but the mixed ones without rolling and stress: 117 to 120 VGPRs, five; their steps with stress 139 to 144).
 // With size-class stencils the slots of a class are one range: its blocks hold fewer particles the
 // larger these are, by the list entries allotted to one (a quarter of the paper's estimate of the
 // particles around it beyond kListPerOwn).
@@ -1268,10 +1276,11 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
 }
 
 // n consecutive time steps through one HIP graph, on pair lists (lists) or as n full steps
-// (n <= kRunSteps): bit k of `finish` sums the stress at step k.  One launch for the run, so the steps follow each other without the gap
-// that separates two graph launches on the device.  run_graph finds or captures the graph of
-// the run from the current buffers (capturing records the launches without running them, and
-// leaves the handle's state as it was); graph_run launches it and advances the state.
+// (n <= kRunSteps): bit k of `finish` sums the stress at step k.  One launch for the run, so the
+// steps follow each other without the gap that separates two graph launches on the device.
+// run_graph finds or captures the graph of the run from the current buffers (capturing records the
+// launches without running them, and leaves the handle's state as it was); graph_run launches it
+// and advances the state.
 constexpr int kRunSteps = 16;
 constexpr size_t kMaxRunGraphs = 64;  // graphs of runs kept per handle
 dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraphExec_t *out)

@@ -456,10 +456,10 @@ __device__ __forceinline__ double advance_particle(const DevParams &P, const Box
 }
 
 // ----------------------------------------------------------------------------------
-// k_predict: velocity-Verlet drift + half kick to time index clk->step + advance (advance >= 1;
-// the steps since the clock's index were taken on pair lists) or velocity completion only
-// (advance = 0), Lees-Edwards wrap, cell id and histogram rank.  advance = 0 with vel_is_half = 0 is
-// the cell id and rank alone (the sort at the end of a window: velocities as they are).
+// k_predict: velocity-Verlet drift + half kick to time index clk->step + 1 (advance = 1) or velocity
+// completion only (advance = 0), Lees-Edwards wrap, cell id and histogram rank.  advance = 0 with
+// vel_is_half = 0 is the cell id and rank alone (the sort at the end of a window: velocities as
+// they are).
 //   vel_is_half = 1: vel holds the half-step velocity u^{n-1/2} of the forces, and
 //   u^n = u^{n-1/2} + dt/2 F^n / m completes the previous step.
 // The atomic force record is read, and cleared for the next evaluation, only when the last
@@ -515,7 +515,7 @@ __global__ void __launch_bounds__(kBlock) k_predict(DevParams P, const BoxParams
     }
     if (advance) {
         int cross;
-        advance_particle(P, G, X, V, W, f, vel_is_half != 0, c0.step + advance, cross);
+        advance_particle(P, G, X, V, W, f, vel_is_half != 0, c0.step + 1, cross);
         if (cross) img[(int)W.w] += cross;  // y-face crossings, for the unwrapped shear-wise position
         pa[p] = X;
     } else if (vel_is_half) {
