@@ -2446,7 +2446,9 @@ __global__ void __launch_bounds__(kBlock) k_pairs_ec(DevParams P, const BoxParam
         const bool whole = span >= nxc;
         span = whole ? nxc : span;
         const int w0 = xlo >= 0 ? xlo / nxc : -((-xlo + nxc - 1) / nxc);  // floor(xlo / n_x)
-        int xl = xlo - w0 * nxc;
+        // (within the row also for a position that no cell number holds: one that is not finite, or whose
+        // wrap rounded)
+        int xl = min(max(xlo - w0 * nxc, 0), nxc - 1);
         const double sy = cross > 0 ? G.L[1] : (cross < 0 ? -G.L[1] : 0.0);
         const double sxd = cross > 0 ? delta : (cross < 0 ? -delta : 0.0);
         const double sz = zu >= nzc ? G.L[2] : (zu < 0 ? -G.L[2] : 0.0);

@@ -99,3 +99,24 @@ def test_particles_outside_the_box(path, bad):
             s.read_stress()
     assert s.info()["step"] == 101 and s.windows()["taken"] == 0 and s.windows()["stopped"] > 0
     s.close()
+
+
+@pytest.mark.parametrize("bad", [1e7, 1e200])
+def test_far_forces_of_particles_outside_the_box(bad):
+    """Full steps with the far pairs on a pass of their own: a particle whose position no cell number holds
+    is searched around within the lattice, and all step on."""
+    from paper_2108_01013_amd.dss import Simulation
+    w = synth.bidisperse_box(4500, 0.45, 23, ec_ranges=True, hamaker=1e-3)
+    u = np.zeros_like(w.x)
+    u[:, 0] = w.x[:, 1]
+    lone = np.array([7, 1234, 4000])
+    u[lone] = [[bad, 0.0, 0.0], [-bad, 0.0, -bad], [0.0, bad, 0.0]]
+    print(f"case: far forces, particles outside the box, {bad}", flush=True)
+    s = Simulation(w.params)
+    s.set_particles(w.x, w.rad, u)
+    assert s.box_info(0)["ec_far_rows"][0] > 0
+    for _ in range(3):
+        s.step(1)
+    f = s.state()["F"]
+    assert s.info()["error_flags"] == 0 and np.all(np.isfinite(f))
+    s.close()
