@@ -80,6 +80,8 @@ __global__ void __launch_bounds__(kBlock) k_phi_profile(int N, double Ly, int nb
         const double4 X = pa[p];
         const double dy = Ly / (double)nb;
         const int g = X.w > a_split ? 1 : 0;
+        // in no slab: a height that no slab number holds (the loop would not end)
+        if (fabs(X.y) > 1.0e5 * Ly) continue;
         // slabs touched by [y - a, y + a), unwrapped bin indices, periodic in y
         const int b0 = (int)floor((X.y - X.w) / dy), b1 = (int)floor((X.y + X.w) / dy);
         for (int b = b0; b <= b1; ++b) {
