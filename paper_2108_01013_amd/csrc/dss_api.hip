@@ -247,7 +247,7 @@ struct dss_handle {
     ListBlock *lblocks = nullptr;
     int2 *lent = nullptr;
     double *lxi = nullptr, *lxr = nullptr, *ldsum = nullptr, *lpartials = nullptr;
-    int *ln = nullptr, *lcross = nullptr, *lof = nullptr;
+    int *ln = nullptr, *lcross = nullptr, *lof = nullptr, *lx_used = nullptr;
     double *lown = nullptr;
     int *lfar = nullptr, *lfar_n = nullptr;  // electro-chemical far pairs by slot
     double *lfar_f = nullptr;
@@ -906,14 +906,15 @@ void commit_eval(dss_handle *h, bool advance)
     }
 }
 
-// The counting sort of the current buffers into the others: kick and drift (advance = 1) or velocity
-// completion (half) of k_predict with the cell ids and ranks, the scan, the scatter (own: force
-// records that move with their particles into ft_own).  clock: time steps the clock advances by.
-void launch_sort(dss_handle *h, bool half, int advance, int clock, const double *own)
+// The counting sort of buffers c into the others: kick and drift (advance = 1) or velocity completion
+// (half) of k_predict with the cell ids and ranks, the scan, the scatter (own: at the end of a window
+// on pair lists, its force records, which move with their particles into ft_own).  clock: time
+// steps the clock advances by.
+void launch_sort(dss_handle *h, int c, bool half, int advance, int clock, const double *own)
 {
     const int N = (int)h->N;
     const int grid = (N + kBlock - 1) / kBlock;
-    const int c = h->cur, o = 1 - h->cur;
+    const int o = 1 - c;
     {
         TimedLaunch t(h, 0);
         hipExtLaunchKernelGGL(k_predict, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, h->P, h->d_boxes,
@@ -940,7 +941,8 @@ void launch_sort(dss_handle *h, bool half, int advance, int clock, const double 
     hipExtLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, h->stream, t.e0, t.e1, 0, N, h->cell, h->rank,
                           tiles ? h->cs_local : h->cell_start, h->tile_sum, tiles ? h->scan_c4 : 0,
                           h->ncell_total + 1, h->cell_start, h->clk, clock, h->pa[c], h->vel[c], h->omg[c],
-                          h->pa[o], h->vel[o], h->omg[o], h->prev, own, h->ft_own);
+                          h->pa[o], h->vel[o], h->omg[o], h->prev, own, h->ft_own, h->lcross, h->img, h->lx_used,
+                          h->ft_x);
 }
 
 dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
@@ -964,7 +966,7 @@ dss_status evaluate(dss_handle *h, EvalMode mode, bool finish = true)
         h->own_total = false;
         return DSS_OK;
     }
-    launch_sort(h, h->vel_is_half, advance, advance, nullptr);
+    launch_sort(h, c, h->vel_is_half, advance, advance, nullptr);
     if (mode != EVAL_RESORT) h->listable = true;
     if (mode == EVAL_RESORT) {
         // the committed rows follow their particles; the pair kernels then find them in place
@@ -1023,15 +1025,13 @@ dss_status graph_step(dss_handle *h, bool finish)
 }
 
 // The host's bookkeeping of a run of n steps: the particles are in the other buffers after every
-// full step, and so is the history; a window on pair lists sorts once, and its rows return to
-// where they were.
+// full step, and so is the history; a window on pair lists leaves both where they were.
 void commit_run(dss_handle *h, int n, bool lists)
 {
     if (!lists) {
         for (int k = 0; k < n; ++k) commit_eval(h, true);
         return;
     }
-    h->cur = 1 - h->cur;
     h->vel_is_half = true;
     h->own_total = true;
     h->step += n;
@@ -1140,6 +1140,7 @@ dss_status setup_lists(dss_handle *h)
         carve(&h->ln, nb);
         carve(&h->ldsum, N);
         carve(&h->lcross, N);
+        carve(&h->lx_used, 1);
         carve(&h->lown, 6 * N);
         carve(&h->lpartials, 12 * (nb + h->ec_grid));
         carve(&h->lrec[0], N);
@@ -1213,14 +1214,17 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
     L.far_cap = h->far_cap;
     L.dsum = h->ldsum;
     L.cross = h->lcross;
+    L.x_used = h->lx_used;
     L.own_cap = h->list_own_cap;
     CommittedView C;
     C.pa = h->pa[h->cur];
     C.vel = h->vel[h->cur];
     C.omg = h->omg[h->cur];
     C.B = h->fb();
-    C.own = h->lown;
-    C.img = h->img;
+    C.pa_end = h->pa[1 - h->cur];
+    C.vel_end = h->vel[1 - h->cur];
+    C.omg_end = h->omg[1 - h->cur];
+    C.own_end = h->lown;
     HistView H{};
     H.key_old = h->hkey[h->hh];
     H.xi_old = h->hxi[h->hh];
@@ -1265,8 +1269,9 @@ dss_status list_window(dss_handle *h, int n, uint64_t finish)
                                   h->lpartials, list_records(h), h->clk, h->run, 1, k);
         }
     }
-    // sort the last state; its rows, committed to the other history buffers, move back with it
-    launch_sort(h, false, 0, n, h->lown);
+    // sort the last state, from the other buffers over the committed one; its rows, in the other history
+    // buffers, move back with it
+    launch_sort(h, 1 - h->cur, false, 0, n, h->lown);
     hipLaunchKernelGGL(k_history_move, dim3((unsigned)((h->N + kBlock - 1) / kBlock)), dim3(kBlock), 0, h->stream,
                        (int)h->N, h->P.M, h->prev, H.key_new, H.xi_new, H.xr_new, H.cnt_new, H.own_new,
                        h->hkey[h->hh], h->hxi[h->hh], h->hxr[h->hh], h->hcnt[h->hh], h->hown[h->hh], h->clk);

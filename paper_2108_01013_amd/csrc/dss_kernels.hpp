@@ -608,7 +608,9 @@ __global__ void __launch_bounds__(kBlock) k_scatter(int N, const int *__restrict
                                                      const double4 *__restrict__ omg_in, double4 *__restrict__ pa_out,
                                                      double4 *__restrict__ vel_out, double4 *__restrict__ omg_out,
                                                      int *__restrict__ prev, const double *__restrict__ own_in,
-                                                     double *__restrict__ own_out)
+                                                     double *__restrict__ own_out, const int *__restrict__ cross_in,
+                                                     int *__restrict__ img, const int *__restrict__ x_used,
+                                                     double *__restrict__ ft_x)
 {
     __shared__ int off[16];
     const int t = threadIdx.x;
@@ -637,10 +639,18 @@ __global__ void __launch_bounds__(kBlock) k_scatter(int N, const int *__restrict
     vel_out[dst] = vel_in[p];
     omg_out[dst] = omg_in[p];
     prev[dst] = p;
-    if (own_in) {  // the force record of the sorted state moves with its particle
+    if (own_in) {
+        // the end of a window on pair lists: the force record of the sorted state moves with its particle,
+        // the y-face crossings of the window are counted, the atomic record of the evaluation before
+        // it is cleared
         double f[6];
         load_ft(own_in + 6LL * p, f);
         store_ft(own_out + 6LL * dst, f);
+        if (cross_in[p]) img[(int)omg_in[p].w] += cross_in[p];
+        if (*x_used) {
+            const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            store_ft(ft_x + 6LL * p, z);
+        }
     }
 }
 

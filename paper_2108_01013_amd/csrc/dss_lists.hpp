@@ -7,11 +7,12 @@
 //                         state, with their stored stretches, and the first kick and drift (with
 //                         size-class stencils k_list_search finds the pairs first);
 //   k_list x n            one launch per step: the pair physics over the lists, the Stokes terms,
-//                         the finishing kick and the next kick, drift and wrap; the last one commits
-//                         the state, the force records and the sorted history rows instead;
-//   a counting sort       at the last state (k_predict's cell ids alone, k_scan, k_scatter, and
-//                         k_history_move for the rows), which leaves the order, cells, rows and
-//                         records of an ordinary step.  (A full step at the end instead cost 61 us
+//                         the finishing kick and the next kick, drift and wrap; the last one writes
+//                         the state, the force records and the sorted history rows (beside the
+//                         committed ones) instead;
+//   a counting sort       of the last state (k_predict's cell ids alone, k_scan, k_scatter, and
+//                         k_history_move for the rows) over the committed one, which leaves the
+//                         order, cells, rows and records of an ordinary step.  (A full step at the end instead cost 61 us
 //                         against 47 at N = 100k, and 2.3 ms against 0.3 at N = 500k, size ratio 10.)
 // The listed-pair test of every step is the FP64 one at the step's own positions: the list only
 // holds more candidates than the test accepts, so the pair set, forces and history are those of a
@@ -28,8 +29,9 @@
 // of a step of 100k particles); a particle that finds the next step beyond the bound (or a list, a
 // history row or a force out of range) sets a flag in
 // the clock's error word, every later kernel of the stream's queue then returns at once, and the
-// committed state at the window's start, which a window writes only in its last list step, is
-// where the host resumes (dss_api.hip, settle).  The searches, which set the flag too, run beside
+// committed state at the window's start, which only the sort writes, is where the host resumes
+// (dss_api.hip, settle).  (A history row may overflow in the last list step too, with the owners that
+// the pairs had at the window's start where those of the step itself would fit.)  The searches, which set the flag too, run beside
 // workgroups of their own launch that are still to start: one lane of a workgroup reads it, and after a
 // barrier all go on or all return (read by each wavefront, some would leave and the others find the
 // counters and queues in LDS unset, and take them for indices).
@@ -95,15 +97,17 @@ struct ListView {
     double *far_f;
     int far_cap;
     int *cross;           // y-face crossings of the window by slot
+    int *x_used;          // whether the evaluation before the window used the atomic force record
     int own_cap;          // largest block
 };
 
-// The committed state of a handle: read by k_list_begin, written by the last list step.
+// The committed state of a handle, read by k_list_begin, and the state after the last list step, in the
+// same slots (before the sort).
 struct CommittedView {
-    double4 *pa, *vel, *omg;
+    const double4 *pa, *vel, *omg;
     ForceBufs B;    // of the evaluation before the window
-    double *own;    // the force records of the last list step (before the sort)
-    int *img;
+    double4 *pa_end, *vel_end, *omg_end;
+    double *own_end;
 };
 
 // After a window that stopped: the flag and the lists' counts are cleared, and what follows runs.
@@ -565,7 +569,7 @@ __global__ void __launch_bounds__(kBlock) k_list_far(DevParams P, BoxParams G, L
 // k_list: time step n of the window (1 .. length) of one block: the listed pairs at the records
 // `in` (the physics and history of the pair kernels), the Stokes terms, then the finishing kick
 // and the next step's kick, drift and wrap into `out`; with Last, instead, the state, the force
-// record and the sorted history rows of the step are committed.  Sum: the block's stress and
+// record and the sorted history rows of the step go to the buffers that the sort reads.  Sum: the block's stress and
 // counters go to its partial record.
 // Bound by FP64 issue and by the latency of the partner gathers: three wavefronts per workgroup
 // and four workgroups per CU keep twelve wavefronts per CU in flight (the register file's limit
@@ -586,17 +590,22 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
     double *const acc = reinterpret_cast<double *>(rec + L.own_cap);
     int *const cnt = reinterpret_cast<int *>(acc + 6 * L.own_cap);
     __shared__ double red[kListBlock / 64][12];
+    __shared__ unsigned stop;  // with Last
     const int t = threadIdx.x;
     const int blk = xcd_row(blockIdx.x, gridDim.x);
     // everything the block's number leads to is requested before the first use
     const ListBlock K = L.blocks[blk];
     const int ne = L.n[blk];
     const DevClock c0 = *clk;
-    // by wavefronts: without Last another workgroup may set the flag meanwhile, and what is left of
-    // this one then works on records that nobody loaded.  Its indices all come from the lists, and
-    // what it writes belongs to a window that is given up (decided by the workgroup behind the
-    // barrier below, the N = 100k step took 1.4 % more).  No launch sets the flag beside Last.
-    if (c0.err & kErrListMask) return;
+    // by wavefronts: another workgroup may set the flag meanwhile, and what is left of this one then
+    // works on records and counts that nobody has set.  Without Last its indices all come from the lists,
+    // and what it writes belongs to a window that is given up (decided by the workgroup behind
+    // the barrier below, the N = 100k step took 1.4 % more); with Last the counts are indices.
+    if constexpr (Last) {
+        if (t == 0) stop = c0.err & kErrListMask;
+    } else {
+        if (c0.err & kErrListMask) return;
+    }
     const BoxParams G = P.nbox > 1 ? boxes[K.box] : G0;
     {
         const double2 *const src = reinterpret_cast<const double2 *>(in + K.start);
@@ -615,6 +624,9 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
     tally.fill = 0;
     bool bad = false;
     __syncthreads();
+    if constexpr (Last) {
+        if (stop) return;
+    }
     // the entry of the lane's next round is requested a round ahead, and the stretch with the
     // records: one memory latency per round instead of three
     int2 next = t < ne ? L.ent[K.e0 + t] : make_int2(0, 0);
@@ -683,10 +695,9 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
             if (!swap) {
                 ++tally.ncont;
                 const int slot = atomicAdd(&cnt[il], 1);
+                bad = bad || slot >= P.M;  // the row would overflow: a full step reports it, if it does there
                 if constexpr (Last)
-                    store_history<Roll>(H, P.M, own, slot, (int)Wi.w, (int)Wj.w, o, clk);
-                else
-                    bad = bad || slot >= P.M;  // the row would overflow: the full step reports it
+                    if (slot < P.M) store_history<Roll>(H, P.M, own, slot, (int)Wi.w, (int)Wj.w, o, clk);
             }
         }
     }
@@ -705,15 +716,10 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
         }
         tally.fill = max(tally.fill, cnt[il]);
         if constexpr (Last) {
-            C.pa[i] = X;
-            C.vel[i] = V;
-            C.omg[i] = W;
-            store_ft(C.own + 6LL * i, f);
-            if (c0.deferred || P.ec_split) {
-                const double z[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-                store_ft(C.B.x + 6LL * i, z);  // of the evaluation before the window
-            }
-            if (L.cross[i]) C.img[(int)W.w] += L.cross[i];
+            C.pa_end[i] = X;
+            C.vel_end[i] = V;
+            C.omg_end[i] = W;
+            store_ft(C.own_end + 6LL * i, f);
             if (!finite6(f)) atomicOr(&clk->err, kErrNonFinite);
             finish_row<Roll>(H, P.M, i, cnt[il], (int)W.w);
         } else {
@@ -728,10 +734,12 @@ __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxPa
         }
     }
     if constexpr (Sum) reduce_fill(tally.fill, red, partials, pstride, blk);
+    if (bad) atomicOr(&clk->err, kErrListStop);
     if constexpr (Last) {
-        if (t == 0) L.n[blk] = 0;  // of the next window's search (every lane has read its count)
-    } else {
-        if (bad) atomicOr(&clk->err, kErrListStop);
+        if (t == 0) {
+            L.n[blk] = 0;  // of the next window's search (every lane has read its count)
+            if (blk == 0) *L.x_used = c0.deferred || P.ec_split ? 1 : 0;
+        }
     }
 }
 
