@@ -116,16 +116,18 @@ constexpr int kListWindow = 64;
 constexpr int kListWindowMin = 5;
 // A window that stops is taken again from its start, so its length is halved, down to
 // kListWindowShort, and doubled again after list_need windows in a row that did not (twice as many after
-// every stop: a stop costs up to a window).  A stop of a shortest window, or lists that do not fit, give
+// every stop, which costs up to a window, half as many after as many windows of full length).  A stop of a shortest window, or lists that do not fit, give
 // full steps for a while: kListRest of them, twice as many after every such stop up to
 // kListRestMax (a search in vain is about a full step and the empty launches of a window).
 constexpr int kListWindowShort = 8;
 constexpr int kListGood = 4, kListGoodMax = 64;
 constexpr int64_t kListRest = 64, kListRestMax = 4096;
 // The host looks at the clock every so many steps of windows (a copy of 16 bytes and an event in the
-// stream), two looks behind what it enqueues: a stop in a long call leaves few empty launches behind it,
-// and the windows lengthen again within the call.
-constexpr int64_t kLookSteps = 512;
+// stream, about 3 us), two looks behind what it enqueues: a stop in a long call leaves few empty launches
+// behind it, and the windows lengthen again within the call.  Calls of 1000 steps of a sheared
+// box, of which one or two stop: N = 20 000 12.96 us a step with a look every 512 steps, 11.82 so; N = 100k
+// mixed 26.8 and 24.3; without stops (N = 1000) 6.77 and 6.79.
+constexpr int64_t kLookSteps = 64;
 // Margin of the lists of a box beyond its cutoff, in smallest radii: what particles moving at a
 // few shear rates use up over a window of kListWindow steps, with a floor (for shorter windows too: the
 // lists' room and the kernels' box table are laid out once).
@@ -1418,7 +1420,7 @@ void runs_done(dss_handle *h, size_t n)
         if (h->list_window < kListWindow) {
             h->list_window = std::min(2 * h->list_window, kListWindow);
         } else {
-            h->list_need = kListGood;
+            h->list_need = std::max(h->list_need / 2, kListGood);
             h->list_rest_next = kListRest;
         }
     }
