@@ -115,8 +115,9 @@ struct AdjointScratch;
 constexpr int kListWindow = 64;
 constexpr int kListWindowMin = 5;
 // A window that stops is taken again from its start, so its length is halved, down to
-// kListWindowShort, and doubled again after list_need windows in a row that did not (twice as many after
-// every stop, which costs up to a window, half as many after as many windows of full length).  A stop of a shortest window, or lists that do not fit, give
+// kListWindowShort, and doubled again after list_need windows in a row that did not: twice as many after a
+// stop that ends a series of windows (a stop costs up to a window, and a sheared box of N = 100k stops in
+// about one window of 64 in ten), half as many once as many of full length have passed.  A stop of a shortest window, or lists that do not fit, give
 // full steps for a while: kListRest of them, twice as many after every such stop up to
 // kListRestMax (a search in vain is about a full step and the empty launches of a window).
 constexpr int kListWindowShort = 8;
@@ -260,6 +261,7 @@ struct dss_handle {
     int list_window = kListWindow;   // longest window
     int list_good = 0;               // windows in a row that did not stop
     int list_need = kListGood;       // and how many of them double the length
+    bool list_any = false;           // a window has not stopped since the last that did
     int64_t list_rest = 0;           // full steps before the next window
     int64_t list_rest_next = kListRest;
     int64_t windows_done = 0, windows_stopped = 0;
@@ -387,6 +389,7 @@ void free_all(dss_handle *h)
     h->list_window = kListWindow;
     h->list_good = 0;
     h->list_need = kListGood;
+    h->list_any = false;
     h->list_rest_next = kListRest;
     h->loaded = false;
 }
@@ -1415,6 +1418,7 @@ void runs_done(dss_handle *h, size_t n)
     for (size_t k = 0; k < n; ++k) {
         if (!h->runs[k].lists) continue;
         ++h->windows_done;
+        h->list_any = true;
         if (++h->list_good < h->list_need) continue;
         h->list_good = 0;
         if (h->list_window < kListWindow) {
@@ -1452,7 +1456,8 @@ dss_status resume_at_stop(dss_handle *h, DevClock c)
     h->own_total = r.own_total;
     ++h->windows_stopped;
     h->list_good = 0;
-    h->list_need = std::min(2 * h->list_need, kListGoodMax);
+    if (h->list_any) h->list_need = std::min(2 * h->list_need, kListGoodMax);
+    h->list_any = false;
     if (!(c.err & kErrListFull) && h->list_window > kListWindowShort) {
         h->list_window = std::max(h->list_window / 2, kListWindowShort);
     } else {
