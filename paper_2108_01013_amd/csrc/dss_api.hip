@@ -1476,9 +1476,13 @@ dss_status resume_at_stop(dss_handle *h, DevClock c)
 dss_status look_at_clock(dss_handle *h, bool wait, bool &stopped)
 {
     stopped = false;
-    if (!h->looked) HIPTRY(hipHostMalloc((void **)&h->looked, 2 * sizeof(DevClock), hipHostMallocDefault));
     dss_handle::Look &l = h->look[h->look_next];
-    if (!l.ev) HIPTRY(hipEventCreateWithFlags(&l.ev, hipEventDisableTiming));
+    if ((!h->looked && hipHostMalloc((void **)&h->looked, 2 * sizeof(DevClock), hipHostMallocDefault) != hipSuccess) ||
+        (!l.ev && hipEventCreateWithFlags(&l.ev, hipEventDisableTiming) != hipSuccess)) {
+        (void)hipGetLastError();  // without a look the call only runs further ahead
+        h->look_steps = 0;
+        return DSS_OK;
+    }
     if (l.on) {
         if (!wait && hipEventQuery(l.ev) != hipSuccess) {
             (void)hipGetLastError();
@@ -1526,7 +1530,7 @@ dss_status enqueue_steps(dss_handle *h, int64_t n_steps, int64_t stress_every, b
             s = graphs ? graph_step(h, R.finish_at(k)) : evaluate(h, EVAL_STEP, R.finish_at(k));
         if (s) return s;
         if (!lists) h->list_rest = std::max<int64_t>(0, h->list_rest - n);
-        if (lists && (h->look_steps += n) >= kLookSteps) {
+        if (lists && (h->look_steps += n) >= kLookSteps && h->step < target) {
             bool stopped;
             s = look_at_clock(h, wait, stopped);
             if (s) return s;
