@@ -2428,7 +2428,9 @@ __global__ void __launch_bounds__(kBlock) k_pairs_ec(DevParams P, const BoxParam
     const int nxc = G.nc[0], nyc = G.nc[1], nzc = G.nc[2];
     const int cy = cell_coord(Xi.y, G.cw[1], nyc), cz = cell_coord(Xi.z, G.cw[2], nzc);
     const double reach = Xi.w + P.ec_amax + P.rext;  // >= a_i + a_j + rext for every j
-    const int ny = 2 * P.ec_ry + 1, nrows = on ? ny * (2 * P.ec_rz + 1) : 0;
+    // (no rows around a position that no cell number holds: one that is not finite, or whose wrap rounded)
+    const bool in_x = Xi.x >= -G.L[0] && Xi.x <= 2.0 * G.L[0];
+    const int ny = 2 * P.ec_ry + 1, nrows = on && in_x ? ny * (2 * P.ec_rz + 1) : 0;
     for (int q = sub; q < nrows; q += kEcLanes) {
         const int dz = q / ny - P.ec_rz, dy = q - (q / ny) * ny - P.ec_ry;
         const int zu = cz + dz, yu = cy + dy;
@@ -2456,9 +2458,7 @@ __global__ void __launch_bounds__(kBlock) k_pairs_ec(DevParams P, const BoxParam
         const bool whole = span >= nxc;
         span = whole ? nxc : span;
         const int w0 = xlo >= 0 ? xlo / nxc : -((-xlo + nxc - 1) / nxc);  // floor(xlo / n_x)
-        // (within the row also for a position that no cell number holds: one that is not finite, or whose
-        // wrap rounded)
-        int xl = min(max(xlo - w0 * nxc, 0), nxc - 1);
+        int xl = xlo - w0 * nxc;
         const double sy = cross > 0 ? G.L[1] : (cross < 0 ? -G.L[1] : 0.0);
         const double sxd = cross > 0 ? delta : (cross < 0 ? -delta : 0.0);
         const double sz = zu >= nzc ? G.L[2] : (zu < 0 ? -G.L[2] : 0.0);

@@ -225,6 +225,23 @@ __device__ __forceinline__ void list_row(const BoxParams &G, const double icw[3]
     }
 }
 
+// Whether the workgroup of block K leaves a search: the window has stopped (err: the clock's word, that of
+// the first lane decides), or a particle of the block is outside the box (a velocity of more than a box
+// length per step, or none that is a number), whose cell numbers would be anything: the lists are
+// given up.  A barrier.
+__device__ __forceinline__ bool list_leave(const BoxParams &G, const ListBlock &K, const double4 *__restrict__ pa,
+                                           unsigned err, DevClock *__restrict__ clk)
+{
+    const int t = threadIdx.x;
+    bool out = false;
+    if (t < K.n) {  // K.n <= kListOwnMax <= kBeginBlock
+        const double4 X = pa[K.start + t];
+        out = !(X.x >= 0.0 && X.x <= G.L[0] && X.y >= 0.0 && X.y <= G.L[1] && X.z >= 0.0 && X.z <= G.L[2]);
+        if (out) atomicOr(&clk->err, kErrListFull);
+    }
+    return __syncthreads_or(out || (t == 0 && (err & kErrListMask)));
+}
+
 // The candidates of a block's particles among the cells from cell0 on (the box's, or a size
 // class's), partners of radius up to amax: push(il, j, a_i, a_j) for every one inside its cutoff (Far:
 // the electro-chemical ranges) plus the margin.  In batches of kBeginRows (particle, cell row) pairs the lanes write the candidate
@@ -259,12 +276,6 @@ __device__ __forceinline__ void list_collect(const DevParams &P, const BoxParams
             const int il = k >> sh, q = k & ((1 << sh) - 1), qz = q / R.ny, qy = q - qz * R.ny;
             if (qz >= R.nz) continue;
             const double4 Xi = pa[K.start + il];
-            // a particle outside the box (a velocity of more than a box length per step, or none that
-            // is a number) has no rows to search: its cell numbers would be anything
-            if (!(Xi.x >= 0.0 && Xi.x <= G.L[0] && Xi.y >= 0.0 && Xi.y <= G.L[1] && Xi.z >= 0.0 && Xi.z <= G.L[2])) {
-                atomicOr(&clk->err, kErrListFull);
-                continue;
-            }
             list_row(G, icw, delta, cell_start, R, cell0, il, Xi, reach(Xi.w + amax), qy, qz,
                      [&](const ListTask &a) { T.task[atomicAdd(&T.n, 1)] = a; });
         }
@@ -322,14 +333,11 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_search(DevParams P, const 
                                                               DevClock *__restrict__ clk)
 {
     __shared__ ListTasks T;
-    __shared__ unsigned stop;
     // the blocks of the largest particles, which scan most, first
     const ListBlock K = L.blocks[gridDim.x - 1 - blockIdx.x];
     const DevClock c0 = *clk;
-    if (threadIdx.x == 0) stop = c0.err & kErrListMask;
-    __syncthreads();
-    if (stop) return;
     const BoxParams G = boxes[K.box];
+    if (list_leave(G, K, pa, c0.err, clk)) return;
     const double delta = le_offset(P, G, c0.step);
     // largest radius of a class (with a margin for the rounding of its number)
     auto top = [&](int k) { return k == P.ncls - 1 ? G.amax : fmin(G.amax, (k + 1 - P.cls_add) / P.cls_mul * (1.0 + 1e-12)); };
@@ -365,7 +373,6 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
     extern __shared__ int2 q_lds[];
     __shared__ ListTasks T;
     __shared__ int qn, cnt[kClasses + 1], pos[kClasses];
-    __shared__ unsigned stop;
     const int t = threadIdx.x;
     const int blk = xcd_row(blockIdx.x, gridDim.x);
     const ListBlock K = L.blocks[blk];
@@ -374,14 +381,10 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_begin(DevParams P, const B
     const int cap = K.cap;
     const double skin = G.skin;
     if (t <= kClasses) cnt[t] = 0;
-    if (t == 0) {
-        qn = P.sized ? L.n[blk] : 0;
-        stop = c0.err & kErrListMask;
-    }
+    if (t == 0) qn = P.sized ? L.n[blk] : 0;
     const double delta = le_offset(P, G, c0.step);
     const double icw[3] = {1.0 / G.cw[0], 1.0 / G.cw[1], 1.0 / G.cw[2]};
-    __syncthreads();
-    if (stop) return;
+    if (list_leave(G, K, C.pa, c0.err, clk)) return;
     if (P.sized) {
         for (int k = t; k < min(qn, cap); k += kBeginBlock) q_lds[k] = L.ent[K.e0 + k];
     } else {
@@ -473,15 +476,12 @@ __global__ void __launch_bounds__(kBeginBlock) k_list_far_begin(DevParams P, con
 {
     __shared__ ListTasks T;
     __shared__ int cnt[kListOwnMax];
-    __shared__ unsigned stop;
     const int t = threadIdx.x;
     const ListBlock K = L.blocks[xcd_row(blockIdx.x, gridDim.x)];
     const DevClock c0 = *clk;
     const BoxParams G = boxes[K.box];
     if (t < kListOwnMax) cnt[t] = 0;
-    if (t == 0) stop = c0.err & kErrListMask;
-    __syncthreads();
-    if (stop) return;
+    if (list_leave(G, K, pa, c0.err, clk)) return;
     list_collect<true>(P, G, le_offset(P, G, c0.step), cell_start, pa, K, G.amax, G.amax, G.cell_off, T, clk,
                        [&](int il, int j, double, double) {
                            const int e = atomicAdd(&cnt[il], 1);
