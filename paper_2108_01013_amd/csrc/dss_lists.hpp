@@ -43,9 +43,9 @@
 // particle written and read back each step by the row tiles), no second launch.  A pair that
 // crosses blocks is evaluated by both workgroups from the same inputs in the same orientation, so
 // both hold the same stretch to the bit.
-// Measured (FP64, a sheared box): N = 100k, 21 us per list step against 64 us for a full step
-// (k_pairs 40, k_predict 9, k_scatter 6, k_scan 4, and their launches); N = 500k, 81 against
-// 360 us; N = 1000, 6.1 against 27 us.
+// Measured (FP64, a sheared box): N = 100k, 21 to 23 us per list step against 64 us for a full step
+// (k_pairs 40, k_predict 9, k_scatter 6, k_scan 4, and their launches); N = 500k, 81 to 88 against
+// 360 us; N = 1000, 6 against 27 us.
 #pragma once
 
 #include "dss_kernels.hpp"
@@ -574,8 +574,7 @@ __global__ void __launch_bounds__(kBlock) k_list_far(DevParams P, BoxParams G, L
 // Bound by FP64 issue and by the latency of the partner gathers: three wavefronts per workgroup
 // and four workgroups per CU keep twelve wavefronts per CU in flight (the register file's limit
 // at 168 VGPRs; sixteen, at 128, take 24.9 us instead of 23.1 at N = 100k and 112 instead of 96 at
-// N = 500k by events, and partners loaded straight into LDS a round ahead 26.2; 21.0 and 81 since the
-// lists, records and partials are one allocation).
+// N = 500k by events, and partners loaded straight into LDS a round ahead 26.2).
 // ----------------------------------------------------------------------------------
 template <typename Real, bool Roll, bool Sum, bool Last>
 __global__ void __launch_bounds__(kListBlock, 3) k_list(DevParams P, const BoxParams *__restrict__ boxes,
