@@ -176,6 +176,7 @@ struct dss_handle {
     // first step, the run length and which of its steps sum the stress)
     hipGraphExec_t graph[32] = {};
     std::vector<std::pair<std::pair<uint64_t, uint64_t>, hipGraphExec_t>> run_graphs;
+    std::vector<hipGraphExec_t> retired;  // out of use, perhaps still under way
     bool graph_broken = false;
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -316,15 +317,23 @@ hipError_t dalloc(T **p, size_t n)
     return hipMalloc((void **)p, std::max<size_t>(n, 1) * sizeof(T));
 }
 
-void destroy_graphs(dss_handle *h)
+// The graphs go out of use; they are destroyed when none of them can be under way any more.
+void retire_graphs(dss_handle *h)
 {
     for (auto &g : h->graph) {
-        if (g) (void)hipGraphExecDestroy(g);
+        if (g) h->retired.push_back(g);
         g = nullptr;
     }
     for (auto &g : h->run_graphs)
-        if (g.second) (void)hipGraphExecDestroy(g.second);
+        if (g.second) h->retired.push_back(g.second);
     h->run_graphs.clear();
+}
+
+// After a wait for the stream.
+void destroy_retired(dss_handle *h)
+{
+    for (auto g : h->retired) (void)hipGraphExecDestroy(g);
+    h->retired.clear();
 }
 
 void free_lists(dss_handle *h)
@@ -341,7 +350,7 @@ void free_lattice(dss_handle *h)
     auto F = [](void *p) {
         if (p) (void)hipFree(p);
     };
-    destroy_graphs(h);
+    retire_graphs(h);
     free_lists(h);
     h->captured = false;  // what was captured held the buffers freed here
     F(h->count); F(h->cell_start); F(h->tile_sum); F(h->cs_local); F(h->partials); F(h->d_boxes); F(h->d_row_box);
@@ -391,6 +400,8 @@ void free_all(dss_handle *h)
     h->list_need = kListGood;
     h->list_any = false;
     h->list_rest_next = kListRest;
+    (void)hipStreamSynchronize(h->stream);
+    destroy_retired(h);
     h->loaded = false;
 }
 
@@ -1309,9 +1320,11 @@ dss_status run_graph(dss_handle *h, int n, bool lists, uint64_t finish, hipGraph
         }
     if (h->run_graphs.size() >= kMaxRunGraphs) {
         // calls of many different shapes: start the collection afresh
-        for (auto &r : h->run_graphs)
-            if (r.second) (void)hipGraphExecDestroy(r.second);
-        h->run_graphs.clear();
+        retire_graphs(h);
+        if (h->retired.size() >= 4 * kMaxRunGraphs) {
+            HIPTRY(hipStreamSynchronize(h->stream));
+            destroy_retired(h);
+        }
     }
     const int cur = h->cur, hh = h->hh;
     const bool vih = h->vel_is_half, total = h->own_total, listable = h->listable;
@@ -1552,6 +1565,7 @@ dss_status settle(dss_handle *h, DevClock *out)
         if (!(c.err & kErrListMask)) {
             no_looks(h);
             runs_done(h, h->runs.size());
+            destroy_retired(h);
             if (out) *out = c;
             return DSS_OK;
         }
@@ -1912,7 +1926,7 @@ dss_status dss_set_tuning(dss_handle *h, const dss_tuning *t)
                          t->tiled != h->tune.tiled || t->sized != h->tune.sized ||
                          t->wave_class != h->tune.wave_class;
     // the captured graphs hold the queue length as a kernel argument
-    if (!t->graph || t->queue_cap != h->tune.queue_cap) destroy_graphs(h);
+    if (!t->graph || t->queue_cap != h->tune.queue_cap) retire_graphs(h);
     h->tune = *t;
     if (h->loaded && lattice) h->tune_pending = true;
     return DSS_OK;
@@ -2009,6 +2023,7 @@ dss_status dss_step(dss_handle *h, int64_t n_steps, int64_t stress_every, int sy
         if (s) return s;
         h->tune_pending = false;
     }
+    if (capture == hipStreamCaptureStatusActive) h->captured = true;  // with a new lattice too
     // the stress and counters are summed only when a sample is due and after the last step
     h->call_every = stress_every;
     const bool listable = h->listable;
@@ -2596,7 +2611,7 @@ extern "C" dss_status dss_adjoint(dss_handle *h, int64_t n_steps, int64_t stress
         for (size_t b = 0; b < h->boxes.size(); ++b) nb[b] = h->boxes[b].n_part;
         const int64_t cap = pair_record_capacity(h->P, h->boxes, h->box_amax, nb.data());
         if (h->P.pair_cap < cap) {
-            destroy_graphs(h);
+            retire_graphs(h);
             if (h->pairs) HIPTRY(hipFree(h->pairs));
             h->pairs = nullptr;
             HIPTRY(dalloc(&h->pairs, 2 * cap));
